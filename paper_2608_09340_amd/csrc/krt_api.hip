@@ -246,6 +246,17 @@ bool valid_bins(int nb, double lo, double hi) {
     return nb > 0 && nb < (1 << 24) && std::isfinite(lo) && std::isfinite(hi) && hi > lo;
 }
 
+// channel_of's margin: half a channel less a bound on how far, in channels, the
+// guess (x - lo) inv_w in binary32 and the rounded edges can be from the exact
+// position: one rounding each of the edges, of lo and of x - lo (units of
+// 2^-24 of the largest of them), and two of the product, doubled.  Channels so
+// narrow that the margin vanishes always go by their edges.
+float channel_safe(int nb, double lo, double hi) {
+    const double inv_w = nb / (hi - lo), big = std::max(std::fabs(lo), std::fabs(hi));
+    const double tol = 2.0 * std::ldexp(1.0, -24) * (inv_w * (3.0 * big + (hi - lo)) + 3.0 * nb);
+    return (float)std::max(0.0, 0.5 - tol);
+}
+
 // binary32 bin edges lo + (hi - lo) k / nb, k = 0..nb, evaluated in FP64
 void fill_edges(float *e, int nb, double lo, double hi) {
     for (int k = 0; k <= nb; ++k) e[k] = (float)(lo + (hi - lo) * (double)k / (double)nb);
@@ -686,7 +697,12 @@ static int mc_run_impl(krt_ctx *c, uint64_t n_packets, uint64_t seed, const krt_
     P.emis_nch = o->emis_nch;
     P.ch_inv_w = o->emis_nch > 0 ? (float)(o->emis_nch / (o->ch_hi - o->ch_lo)) : 0.0f;
     P.ch_edges = edges + kMaxSpecBins + 1;
+    if (o->emis_nch > 0) {
+        P.ch_lo = (float)o->ch_lo;
+        P.ch_safe = channel_safe(o->emis_nch, o->ch_lo, o->ch_hi);
+    }
     P.frac_scale = std::ldexp(1.0f, fb);
+    P.emis_frac_bits = fb;
     P.emis_w32 = fb <= 30 ? 1 : 0;
     P.jbar_scale = std::ldexp(1.0f, fj);
     P.spec_raw = t->spec_raw_dev;

@@ -26,9 +26,58 @@ __device__ __forceinline__ uint4 philox(uint4 c, uint32_t k0, uint32_t k1) {
     return c;
 }
 
-// uniform on (0,1): an odd multiple of 2^-24, exact in binary32
+// The two blocks of one event, philox((ev, id, 0)) and philox((ev, id, 1)).
+// Their first three rounds share most of their products: those of the packet's
+// id alone are kept per packet, those of the event alone are made once, so the
+// pair takes 34 wide multiplies instead of 40, and one three-way xor per output
+// word instead of two.
+struct PhiloxPacket {
+    uint32_t bk, hk, la;
+};
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+__device__ __forceinline__ PhiloxPacket philox_packet(uint32_t plo, uint32_t phi, uint32_t k0, uint32_t k1) {
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * phi;
+    const uint64_t q = (uint64_t)0xD2511F53u * ((uint32_t)(p1 >> 32) ^ plo ^ k0);
+    PhiloxPacket p;
+    p.bk = (uint32_t)p1 ^ (k0 + 0x9E3779B9u);
+    p.hk = (uint32_t)(q >> 32) ^ (k1 + 0xBB67AE85u);
+    p.la = (uint32_t)q;
+    return p;
+}
+__device__ __forceinline__ void philox_pair(const PhiloxPacket &pk, uint32_t ev, uint32_t k0, uint32_t k1, uint4 &A,
+                                            uint4 &B) {
+    const uint64_t p0 = (uint64_t)0xD2511F53u * ev;              // round 1
+    const uint32_t z = (uint32_t)(p0 >> 32) ^ k1;
+    const uint64_t pa = (uint64_t)0xCD9E8D57u * z, pb = (uint64_t)0xCD9E8D57u * (z ^ 1u);  // round 2
+    const uint64_t q = (uint64_t)0xCD9E8D57u * (pk.hk ^ (uint32_t)p0);                     // round 3
+    const uint64_t ra = (uint64_t)0xD2511F53u * ((uint32_t)(pa >> 32) ^ pk.bk);
+    const uint64_t rb = (uint64_t)0xD2511F53u * ((uint32_t)(pb >> 32) ^ pk.bk);
+    k0 += 2u * 0x9E3779B9u;
+    k1 += 2u * 0xBB67AE85u;
+    A = make_uint4(xor3((uint32_t)(q >> 32), (uint32_t)pa, k0), (uint32_t)q, xor3((uint32_t)(ra >> 32), pk.la, k1),
+                   (uint32_t)ra);
+    B = make_uint4(xor3((uint32_t)(q >> 32), (uint32_t)pb, k0), (uint32_t)q, xor3((uint32_t)(rb >> 32), pk.la, k1),
+                   (uint32_t)rb);
+#pragma unroll
+    for (int r = 3; r < 10; ++r) {
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+        const uint64_t a0 = (uint64_t)0xD2511F53u * A.x, a1 = (uint64_t)0xCD9E8D57u * A.z;
+        const uint64_t b0 = (uint64_t)0xD2511F53u * B.x, b1 = (uint64_t)0xCD9E8D57u * B.z;
+        A = make_uint4(xor3((uint32_t)(a1 >> 32), A.y, k0), (uint32_t)a1, xor3((uint32_t)(a0 >> 32), A.w, k1),
+                       (uint32_t)a0);
+        B = make_uint4(xor3((uint32_t)(b1 >> 32), B.y, k0), (uint32_t)b1, xor3((uint32_t)(b0 >> 32), B.w, k1),
+                       (uint32_t)b0);
+    }
+}
+
+// uniform on (0,1): the odd multiple (w >> 9) 2^-23 + 2^-24, exact in binary32;
+// the 23 bits go into the mantissa of a number in [1, 2), and the difference is
+// exact
 __device__ __forceinline__ float u01(uint32_t w) {
-    return (float)(w >> 9) * 0x1p-23f + 0x1p-24f;
+    return __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, w, 9)) - (1.0f - 0x1p-24f);
 }
 
 // ------------------------------------------------------------- fast math ---
@@ -64,22 +113,31 @@ __device__ __forceinline__ int bin_index(float x, const float *edges, int nb, fl
     return k + 1;
 }
 
+// The channel k (0 <= k < nb) that bin_index puts x in, or a number outside
+// [0, nb).  The guess floor((x - lo) / width) is the answer unless x is within
+// rounding of an edge: `safe` is one half less the bound on that rounding in
+// widths (channel_safe), so a guess whose fraction is nearer than that to one half
+// needs no look at the edges.
+__device__ __forceinline__ int channel_of(float x, const float *edges, int nb, float inv_w, float lo, float safe) {
+    const float t = (x - lo) * inv_w;
+    const float fl = floorf(t);
+    int k = (int)fl;
+    if (!(fabsf((t - fl) - 0.5f) < safe)) k = bin_index(x, edges, nb, inv_w) - 1;
+    return k;
+}
+
 // ----------------------------------------------------------- LDS lookups ---
+// H(a, |x|): the core and wing pieces share one address and one read
 __device__ __forceinline__ float voigt_lds(const float *T, float xa) {
-    if (xa < 8.0f) {
-        float t = xa * 64.0f;
-        int i = max(0, min((int)t, kVoigtCoreN - 1));
-        float f = t - (float)i;
-        float4 c = *reinterpret_cast<const float4 *>(T + kOffVoigtCore + 4 * i);
-        return fmaf(f, fmaf(f, fmaf(f, c.w, c.z), c.y), c.x);
-    }
-    float w = 8.0f * f_rcp(xa);
-    float t = w * (float)kVoigtWingN;
-    int j = max(0, min((int)t, kVoigtWingN - 1));
-    float f = t - (float)j;
-    float4 c = *reinterpret_cast<const float4 *>(T + kOffVoigtWing + 4 * j);
-    float G = fmaf(f, fmaf(f, fmaf(f, c.w, c.z), c.y), c.x);
-    return G * w * w * (1.0f / 64.0f);
+#pragma clang fp contract(off)
+    const bool core = xa < 8.0f;
+    const float w = 8.0f * f_rcp(xa);
+    const float t = core ? xa * 64.0f : w * (float)kVoigtWingN;
+    const int i = max(0, min((int)t, core ? kVoigtCoreN - 1 : kVoigtWingN - 1));
+    const float f = t - (float)i;
+    const float4 c = *reinterpret_cast<const float4 *>(T + (core ? kOffVoigtCore : kOffVoigtWing) + 4 * i);
+    const float G = fmaf(f, fmaf(f, fmaf(f, c.w, c.z), c.y), c.x);
+    return core ? G : G * w * w * (1.0f / 64.0f);
 }
 
 // Analytic approximation of H(a, u) that blends the Doppler core exp(-u^2) and
@@ -100,50 +158,41 @@ __device__ __forceinline__ float voigt_analytic(float a, float u0, float ua) {
 // (row of |x|, quantile node).
 __device__ __forceinline__ float upar_lds(const float *T, float x, float a, float thd,
                                           float r1, float r2) {
-    float xa = fabsf(x);
-    float c1 = 0.0f, c2 = 0.0f, c3 = 1.0f;
-    if (xa < 8.0f) {
-        float pm = xa * (float)(kMassN / 8);
-        int im = max(0, min((int)pm, kMassN - 1));
-        float fm = pm - (float)im;
-        float4 m0 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im);
-        float4 m1 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im + 4);
-        c1 = fmaf(fm, m1.x - m0.x, m0.x);
-        c2 = fmaf(fm, m1.y - m0.y, m0.y);
-        c3 = fmaf(fm, m1.z - m0.z, m0.z);
-    }
-    float p;
-    if (xa < 8.0f) p = xa * 6.0f;
-    else p = fminf(48.0f + f_log(xa * 0.125f) * kRowInvLog, 63.0f);
-    int j = max(0, min((int)p, kRows - 2));
-    float fr = p - (float)j;
-    int kind = (r1 < c1) ? 0 : ((r1 < c2) ? 1 : ((r1 < c3) ? 2 : 3));
-    int nq = (kind == 0) ? kQS : kQL1;  // kQL1 == kQL2 == kQR
-    int off = (kind == 0) ? kOffSpike : ((kind == 1) ? kOffL1 : ((kind == 2) ? kOffL2 : kOffRight));
+#pragma clang fp contract(off)
+    const float xa = fabsf(x);
+    const bool lin = xa < 8.0f;
+    // cumulative piece probabilities; beyond the table every draw is the bump's
+    const float pm = xa * (float)(kMassN / 8);
+    const int im = max(0, min((int)pm, kMassN - 1));
+    const float fm = pm - (float)im;
+    const float4 m0 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im);
+    const float4 m1 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im + 4);
+    const float c1 = lin ? fmaf(fm, m1.x - m0.x, m0.x) : 0.0f;
+    const float c2 = lin ? fmaf(fm, m1.y - m0.y, m0.y) : 0.0f;
+    const float c3 = lin ? fmaf(fm, m1.z - m0.z, m0.z) : 1.0f;
+    const float p = __builtin_unpredictable(lin) ? xa * 6.0f : fminf(fmaf(f_log(xa * 0.125f), kRowInvLog, 48.0f), 63.0f);
+    const int j = max(0, min((int)p, kRows - 2));
+    const float fr = p - (float)j;
+    const bool spike = r1 < c1, l1 = r1 < c2, l2 = r1 < c3;  // the first that holds names the piece
+    const int off = spike ? kOffSpike : (l1 ? kOffL1 : (l2 ? kOffL2 : kOffRight));
     // wing pieces: nodes at q = 4 xi^3 (xi < 1/2), 1 - 4 (1 - xi)^3 (xi >= 1/2)
-    float xi = r2;
-    if (kind != 0) {
-        float t = (r2 < 0.5f) ? r2 : 1.0f - r2;
-        float cb = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(0.25f * t) * (1.0f / 3.0f));
-        xi = (r2 < 0.5f) ? cb : 1.0f - cb;
-    }
-    float qp = xi * (float)(nq - 1);
-    int k = max(0, min((int)qp, nq - 2));
-    float fq = qp - (float)k;
-    const float *r0 = T + off + j * nq + k;
-    float v0 = fmaf(fq, r0[1] - r0[0], r0[0]);
-    float v1 = fmaf(fq, r0[nq + 1] - r0[nq], r0[nq]);
-    float v = fmaf(fr, v1 - v0, v0);
-    float u;
-    if (kind == 0) {
-        float th = v * thd * (1.0f / (2.0f * kPiF));
-        u = xa + a * sin_rev(th) * f_rcp(cos_rev(th));
-    } else if (kind == 2) {
-        u = v;
-    } else {
-        float s = (float)kDelta * f_exp(v);
-        u = (kind == 1) ? xa - s : xa + s;
-    }
+    const bool lo = r2 < 0.5f;
+    const float cb = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(0.25f * (lo ? r2 : 1.0f - r2)) * (1.0f / 3.0f));
+    const float xi = __builtin_unpredictable(spike) ? r2 : (lo ? cb : 1.0f - cb);
+    const float nq1 = spike ? (float)(kQS - 1) : (float)(kQL1 - 1);  // kQL1 == kQL2 == kQR
+    const int k = max(0, min((int)(xi * nq1), spike ? kQS - 2 : kQL1 - 2));
+    const float fq = fmaf(xi, nq1, -(float)k);
+    const float *r0 = T + off + (spike ? j * kQS : j * kQL1) + k;
+    const float *rn = r0 + (spike ? kQS : kQL1);
+    const float v0 = fmaf(fq, r0[1] - r0[0], r0[0]);
+    const float v1 = fmaf(fq, rn[1] - rn[0], rn[0]);
+    const float v = fmaf(fr, v1 - v0, v0);
+    // spike: u = x + a tan(theta); wings: x -+ DELTA e^v; bump: v itself
+    const float th = v * thd * (1.0f / (2.0f * kPiF));
+    const float us = fmaf(a * sin_rev(th), f_rcp(cos_rev(th)), xa);
+    const float s = (float)kDelta * f_exp(v);
+    const float uw = xa + (l1 ? -s : s);
+    const float u = spike ? us : ((l2 && !l1) ? v : uw);
     return (x < 0.0f) ? -u : u;  // p(u | -x) = p(-u | x)
 }
 

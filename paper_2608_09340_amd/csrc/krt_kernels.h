@@ -77,7 +77,9 @@ struct RunParams {
     float ch_inv_w;
     const float *ch_edges;    // [emis_nch + 1]
     float n_cam[3];
+    float ch_lo, ch_safe;  // channel_of: the first edge, half less the rounding of a guess in widths
     float frac_scale;  // 2^F, emissivity
+    int emis_frac_bits;  // F
     float jbar_scale;  // 2^Fj, mean intensity
     int64_t *spec_raw, *emis_raw, *jbar_raw, *counters;
     uint32_t *status;
@@ -87,6 +89,7 @@ struct RunParams {
     uint64_t n_packets, packet_offset, max_events;
     uint32_t key0, key1;
     unsigned long long *work_counter;
+    int first_lanes;  // packets a wave starts with (1..64)
     const uint4 *res_in;
     uint64_t n_res, new_lo;
     // parking (kernel mode kModePark): a packet whose scattering qualifies for a

@@ -13,6 +13,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <atomic>
+
 #include "krt_internal.h"
 #include "krt_kernels.h"
 #include "krt_device.h"
@@ -27,42 +30,67 @@ __device__ __forceinline__ void tally_add_i64(int64_t *p, int64_t v) {
     atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
 }
 
-// Four direct-mapped (channel -> fixed-point sum) slots, slot = channel & 3; a
-// slot is written back only when another channel takes it or the packet leaves
-// the cell.
-struct EmisCache {
-    int ch[4];
-    int64_t acc[4];
-};
+// Emissivity tally of a packet's visit to one cell: a window of eight
+// consecutive channels accumulates the scatterings; a channel outside it
+// writes the window back (one atomic per channel met) and moves it.  Consecutive
+// scatterings see camera frequencies within a few Doppler widths of the cell's,
+// so the window rarely moves.
+//
+// Isotropic phase: every scattering adds the same 2^F, so the window counts
+// scatterings, eight 8-bit counts in one register pair.  The wave writes all
+// its windows back every kEmisTicks iterations, before a count can pass 255.
+// Dipole phase: the contributions differ, so the window holds int64 sums, in
+// LDS ([slot][thread], each thread its own).
+// Against four direct-mapped (channel, int64 sum) register slots with a
+// four-way branch per scattering this takes 3 VGPRs instead of 12.
+constexpr int kEmisSlots = 8;
+constexpr int kEmisTicks = 255;
 
-__device__ __forceinline__ void emis_reset(EmisCache &E) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) { E.ch[s] = -1; E.acc[s] = 0; }
-}
+template <bool kSum>
+struct EmisWindow {
+    int w = 0;            // first channel of the window
+    uint64_t cnt = 0;     // 8-bit counts of channels w .. w + 7 (kSum: bit s = slot s in use)
+    int64_t *acc;         // kSum: this thread's LDS sums
+    int stride;           // ... and the distance between its slots
 
-__device__ __forceinline__ void emis_flush(EmisCache &E, int64_t *base) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        if (E.ch[s] >= 0) tally_add_i64(base + E.ch[s], E.acc[s]);
-        E.ch[s] = -1;
-        E.acc[s] = 0;
-    }
-}
-
-__device__ __forceinline__ void emis_add(EmisCache &E, int ch, int64_t v, int64_t *base) {
-    const int slot = ch & 3;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        if (s == slot) {
-            if (E.ch[s] != ch) {
-                if (E.ch[s] >= 0) tally_add_i64(base + E.ch[s], E.acc[s]);
-                E.ch[s] = ch;
-                E.acc[s] = 0;
+    // writes the window back to the tallies `cell` (of the window's cell)
+    __device__ __forceinline__ void flush(int64_t *cell, int frac_bits) {
+        while (cnt != 0) {
+            if constexpr (kSum) {
+                const int s = __ffs((unsigned)cnt) - 1;
+                tally_add_i64(cell + (w + s), acc[s * stride]);
+                acc[s * stride] = 0;
+                cnt &= cnt - 1;
+            } else {
+                const int s = (__ffsll((long long)cnt) - 1) & ~7;
+                const uint64_t n = (cnt >> s) & 255u;
+                tally_add_i64(cell + (w + (s >> 3)), (int64_t)(n << frac_bits));
+                cnt &= ~(255ull << s);
             }
-            E.acc[s] += v;
         }
     }
-}
+    // one scattering of weight v (kSum; 2^frac_bits otherwise) into channel ch;
+    // write_back flushes this window
+    template <class F>
+    __device__ __forceinline__ void add(int ch, int64_t v, F write_back) {
+        int d = ch - w;
+        if ((unsigned)d >= (unsigned)kEmisSlots) {
+            write_back();
+            w = ch - (kEmisSlots / 2 - 1);
+            d = kEmisSlots / 2 - 1;
+        }
+        if constexpr (kSum) {
+            __hip_atomic_fetch_add(acc + d * stride, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            cnt |= 1ull << d;
+        } else {
+            cnt += 1ull << (8 * d);
+        }
+    }
+};
+
+// Counters a workgroup keeps in LDS until it ends: the outcomes 1..3 of retired
+// packets first, then emissions and the retired packets' sums.
+enum { kLcEscaped = 0, kLcDestroyed, kLcStuck, kLcEmit, kLcScat, kLcCross, kLcDrop, kNLdsCounters };
 
 // wave-wide sum of a 64-bit value, then one atomic from the first active lane
 __device__ __forceinline__ void wave_add_counter(int64_t *dst, int64_t v) {
@@ -378,19 +406,12 @@ __device__ __forceinline__ float cont_voigt(const RunParams &P, int voff, float 
 }
 
 // --------------------------------------------------------------- kernel ---
-// Draws of the second random block of an event: the two u_perp components
-// (Box-Muller, N(0, 1/2) each), the cosine g of the scattering angle
-// (isotropic or dipole) with sqrt(1 - g^2), and cos, sin of the azimuth psi.
+// Draws of an event: the destruction uniform ue, the sampler's uniforms r1, r2,
+// the two u_perp components (Box-Muller, N(0, 1/2) each), the cosine g of the
+// scattering angle (isotropic or dipole) with sqrt(1 - g^2), and cos, sin of
+// the azimuth psi.
 struct SDraws {
     float up1, up2, g, sg, cp, sp;
-};
-
-// A prepared scattering: outgoing direction and gas-frame frequency, the
-// emissivity channel (1-based, out of range = dropped) and its contribution.
-struct ScatPrep {
-    float ox, oy, oz, xo;
-    int kb;
-    int64_t wq;
 };
 
 __device__ __forceinline__ void scatter_draws(uint4 B, bool dipole, SDraws &d) {
@@ -405,6 +426,28 @@ __device__ __forceinline__ void scatter_draws(uint4 B, bool dipole, SDraws &d) {
     d.sp = sin_rev(psi);
 }
 
+// ax bx + ay by + az bz in the one order every variant uses
+__device__ __forceinline__ float dot3(float ax, float bx, float ay, float by, float az, float bz) {
+    return fmaf(az, bz, fmaf(ax, bx, ay * by));
+}
+
+// x, y or z of the axis a crossing goes along; by value, since a conditional
+// between captured variables would select between their addresses and hold the
+// lane's state in memory
+template <class V>
+__device__ __forceinline__ V by_axis(bool ax0, bool ax1, V x, V y, V z) {
+    const V yz = ax1 ? y : z;
+    return ax0 ? x : yz;
+}
+
+// Distance along one axis to the face ahead: n the direction's component, f the
+// position in the cell, dx its width.  A zero component gives +inf, or NaN (0
+// times inf) for a packet exactly on the face; the minimum over the axes
+// ignores a NaN as it ignores +inf, and the direction has another component.
+__device__ __forceinline__ float face_dist(float n, float f, float dx) {
+    return (n > 0.0f ? 1.0f - f : f) * dx * f_rcp(fabsf(n));
+}
+
 // kProf: 0 tables in LDS (production); 1 the same tables read from global
 // memory (the workgroup still stages them, so occupancy is unchanged and only
 // the memory space of the lookups differs); 2 analytic opacity profile in the
@@ -413,8 +456,32 @@ __device__ __forceinline__ void scatter_draws(uint4 B, bool dipole, SDraws &d) {
 // damping a b_ref / b, and the class's own tables (global memory) serve the
 // opacity and the redistribution; frequencies return to reference units on
 // leaving the cell's frame.
-template <int kMode, int kMaxThreads, int kProf = 0>
+// kDip: dipole phase (plain walk; the learned escape is isotropic).
+//
+// A lane's iteration has three parts: the flight of every live lane (opacity,
+// distance to the face, position), then the cell change of the lanes that
+// cross, then the scattering of the lanes that interact, which also draws the
+// random words of their next event.  The walk is bound by instruction issue
+// when the waves are full and by the latency of one lane's chain when few
+// packets are left, so each part is written without branches: selects between
+// the table pieces, one LDS read per lookup, the tally bin from its guess
+// unless the frequency is within rounding of a bin edge.  Every product and sum
+// is a fixed one (fmaf where it is fused, contraction off otherwise), so that
+// all variants walk a packet through the same numbers.
+// The launch's parameters re-read where they are used: for the paths a packet
+// takes rarely (crossings, refills, retirements).  Read through P the compiler
+// keeps them all in scalar registers across the loop, which are too few, and
+// every scattering then pays for moving its own constants in and out.
+typedef const __attribute__((address_space(4))) RunParams *ColdParams;
+__device__ __forceinline__ ColdParams cold_params() {
+    ColdParams p = (ColdParams)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+template <int kMode, int kMaxThreads, int kProf = 0, bool kDip = false>
 __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) {
+#pragma clang fp contract(off)
     constexpr bool kEsc = kMode == kModeFused, kPark = kMode == kModePark;
     constexpr bool kTemp = kProf == 3 || kProf == 4;  // per-cell temperature: classes or continuum
     extern __shared__ float4 lds4[];
@@ -427,6 +494,10 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     float *ledges = reinterpret_cast<float *>(lds4) + kTabFloats;
     const float *sedges = kEsc ? P.spec_edges : ledges;  // spectrum edges
     float *cedges = ledges + kLdsSpec;                    // channel edges
+    // then the workgroup's counters, then the dipole windows
+    unsigned long long *lcnt =
+        reinterpret_cast<unsigned long long *>(lds4 + (kEsc ? kLdsMlp + kMlpFwdBytes / 4 : kTabFloats + kEdgeFloats) / 4);
+    EmisWindow<kDip> E;
     {
         const float4 *src = reinterpret_cast<const float4 *>(P.tab);
         for (int i = threadIdx.x; i < kTabFloats / 4; i += blockDim.x) lds4[i] = src[i];
@@ -437,6 +508,13 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             const float4 *ms = reinterpret_cast<const float4 *>(P.mlp_img);
             float4 *md = lds4 + kLdsMlp / 4;
             for (int i = threadIdx.x; i < kMlpFwdBytes / 16; i += blockDim.x) md[i] = ms[i];
+        }
+        if (threadIdx.x < kNLdsCounters) lcnt[threadIdx.x] = 0ull;
+        if constexpr (kDip) {
+            E.stride = (int)blockDim.x;
+            E.acc = reinterpret_cast<int64_t *>(lcnt + kNLdsCounters) + threadIdx.x;
+            if (P.emis_raw)
+                for (int k = 0; k < kEmisSlots; ++k) E.acc[k * E.stride] = 0;
         }
     }
     __syncthreads();
@@ -454,32 +532,38 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     int toff = 0, voff = 0;
     bool have = false, done = false;
     uint64_t pid = 0;
+    PhiloxPacket pk{};
     int ci = 0, cj = 0, ck = 0, cell = 0;
     float fx = 0.f, fy = 0.f, fz = 0.f;
     float nx = 0.f, ny = 0.f, nz = 1.f;
     float x = 0.f, tau = 0.f;
     uint32_t ev = 0, wa1 = 0, wa2 = 0, wa3 = 0;
+    uint4 wb = make_uint4(0u, 0u, 0u, 0u);
     float k0c = 0.f, vxc = 0.f, vyc = 0.f, vzc = 0.f, epsc = 0.f, kabsc = 0.f;
     uint32_t nscat_pkt = 0, ncross_pkt = 0;
+    uint32_t ndrop = 0;  // scatterings of the packet outside the channels, in this lane
     uint32_t seg = 0;  // plain scatterings of the packet in this launch (park mode)
     bool pend = false;   // fused mode: a qualifying scattering waits for its wave's next call batch
     uint32_t pwait = 0;  // ... for this many loop iterations so far
     int outcome = 0;  // 1 escaped, 2 destroyed, 3 stuck
     int64_t jacc = 0;
-    EmisCache E;
-    emis_reset(E);
-    // per-lane counters
-    int64_t c_emit = 0, c_esc = 0, c_des = 0, c_scat = 0, c_cross = 0, c_stuck = 0, c_drop = 0;
-    int64_t c_mlp = 0, c_skip = 0;
-    uint32_t *status = P.status;
+    int64_t c_mlp = 0, c_skip = 0, c_drop = 0;  // network calls
     const float jscale = P.jbar_scale * kInvSqrtPiF;
+    const bool destroys = P.eps != nullptr || P.kabs != nullptr;  // uniform
+    const uint32_t max_events = (uint32_t)P.max_events;
+    auto count = [&](int slot, uint64_t v) __attribute__((always_inline)) { atomicAdd(&lcnt[slot], (unsigned long long)v); };
 
-    // entering a cell with temperature classes or a continuum of widths: its
-    // frequency scale, damping, sampler threshold and table set
-    auto enter_cell = [&]() {
+    // entering a cell: its fields, and with temperature classes or a continuum
+    // of widths its frequency scale, damping, sampler threshold and table set
+    auto enter_cell = [&]() __attribute__((always_inline)) {
+        const ColdParams C = cold_params();
+        k0c = C->k0[cell];
+        if (C->vx) { vxc = C->vx[cell]; vyc = C->vy[cell]; vzc = C->vz[cell]; }
+        if (C->eps) epsc = C->eps[cell];
+        if (C->kabs) kabsc = C->kabs[cell];
         if constexpr (kProf == 3) {
-            const int k = P.tclass[cell];
-            const float4 cp = P.cls_par[k];
+            const int k = C->tclass[cell];
+            const float4 cp = C->cls_par[k];
             sc = cp.x; ac = cp.y; thdc = cp.z; isc = cp.w;
             sac = ac;
             toff = k * kTabFloats;
@@ -491,155 +575,167 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             voff = cc.voff; toff = cc.toff;
         }
     };
+    auto locate = [&]() __attribute__((always_inline)) {
+        const ColdParams C = cold_params();
+        ci = cell % C->n[0];
+        cj = (cell / C->n[0]) % C->n[1];
+        ck = cell / (C->n[0] * C->n[1]);
+    };
+    auto gas_freq = [&]() __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+        if constexpr (kTemp) return (x - dot3(ny, vyc, nx, vxc, nz, vzc)) * sc;
+        else return x - dot3(nx, vxc, ny, vyc, nz, vzc);
+    };
+    // random words of event ev: optical depth, destruction, sampler; then the
+    // second block's four
+    auto draw_event = [&]() __attribute__((always_inline)) {
+        uint4 A;
+        philox_pair(pk, ev, P.key0, P.key1, A, wb);
+        tau = -f_log(u01(A.x));
+        wa1 = A.y; wa2 = A.z; wa3 = A.w;
+    };
+    auto flush_emis = [&]() __attribute__((always_inline)) {
+        const ColdParams C = cold_params();
+        if (C->emis_raw) E.flush(C->emis_raw + (int64_t)cell * C->emis_nch, C->emis_frac_bits);
+    };
+    auto flush_jbar = [&]() __attribute__((always_inline)) {
+        if (jacc != 0) { tally_add_i64(cold_params()->jbar_raw + cell, jacc); jacc = 0; }
+    };
+    auto give_up = [&]() __attribute__((always_inline)) {
+        atomicOr(cold_params()->status, (uint32_t)KRT_ST_STUCK_BIT);
+        outcome = 3;
+        have = false;
+    };
 
     // one flight segment of a live lane: to the next interaction (scat = true,
     // or destruction) or across one cell face (escape / periodic wrap / next cell)
-    auto flight = [&](float ue, bool &scat, float &xc) {
-        xc = x - (nx * vxc + ny * vyc + nz * vzc);
-        if constexpr (kTemp) xc *= sc;
-        float H = 0.0f;
-        if (k0c > 0.0f) {
-            if constexpr (kProf == 2) H = voigt_analytic(a, P.voigt_u0, fabsf(xc));
-            else if constexpr (kProf == 4) H = cont_voigt(P, voff, tv, fabsf(xc));
-            else H = voigt_lds((kProf == 3) ? P.cls_tab + toff : T, fabsf(xc));
-        }
+    auto flight = [&](float xc, auto ue, bool &scat) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+        float H;
+        if constexpr (kProf == 2) H = voigt_analytic(a, P.voigt_u0, fabsf(xc));
+        else if constexpr (kProf == 4) H = cont_voigt(P, voff, tv, fabsf(xc));
+        else H = voigt_lds((kProf == 3) ? P.cls_tab + toff : T, fabsf(xc));
+        H = (k0c > 0.0f) ? H : 0.0f;
         // line opacity plus the cell's grey absorption (exactly k0 H without one)
-        float kap = fmaf(k0c, H, kabsc);
-        float tx = (nx > 0.0f) ? (1.0f - fx) * P.dx[0] * f_rcp(nx) : ((nx < 0.0f) ? fx * P.dx[0] * f_rcp(-nx) : INFINITY);
-        float ty = (ny > 0.0f) ? (1.0f - fy) * P.dx[1] * f_rcp(ny) : ((ny < 0.0f) ? fy * P.dx[1] * f_rcp(-ny) : INFINITY);
-        float tz = (nz > 0.0f) ? (1.0f - fz) * P.dx[2] * f_rcp(nz) : ((nz < 0.0f) ? fz * P.dx[2] * f_rcp(-nz) : INFINITY);
-        int ax = 0;
-        float dmin = tx;
-        if (ty < dmin) { dmin = ty; ax = 1; }
-        if (tz < dmin) { dmin = tz; ax = 2; }
-        dmin = fmaxf(dmin, 0.0f);
-
-        if (kap > 0.0f && kap * dmin >= tau) {
-            // interaction inside the cell
-            float l = tau * f_rcp(kap);
-            fx = fminf(fmaxf(fmaf(l * nx, P.inv_dx[0], fx), 0.0f), 1.0f);
-            fy = fminf(fmaxf(fmaf(l * ny, P.inv_dx[1], fy), 0.0f), 1.0f);
-            fz = fminf(fmaxf(fmaf(l * nz, P.inv_dx[2], fz), 0.0f), 1.0f);
-            if (P.jbar_raw) jacc += (int64_t)__float2ll_rn(l * H * jscale);
+        const float kap = fmaf(k0c, H, kabsc);
+        const float tx = face_dist(nx, fx, P.dx[0]), ty = face_dist(ny, fy, P.dx[1]), tz = face_dist(nz, fz, P.dx[2]);
+        const float tm = fminf(fminf(tx, ty), tz);
+        const bool ax0 = tx == tm, ax1 = !ax0 && ty == tm;  // ties go to the lower axis
+        const float dmin = fmaxf(tm, 0.0f);
+        const float dtau = kap * dmin;
+        const bool hit = kap > 0.0f && dtau >= tau;  // interaction inside the cell
+        const float l = hit ? tau * f_rcp(kap) : dmin;
+        fx = fminf(fmaxf(fmaf(l * nx, P.inv_dx[0], fx), 0.0f), 1.0f);
+        fy = fminf(fmaxf(fmaf(l * ny, P.inv_dx[1], fy), 0.0f), 1.0f);
+        fz = fminf(fmaxf(fmaf(l * nz, P.inv_dx[2], fz), 0.0f), 1.0f);
+        if (P.jbar_raw) {
+            asm volatile("");  // a branch: not computed and dropped by every run without the tally
+            jacc += (int64_t)__float2ll_rn(l * H * jscale);
+        }
+        scat = hit;
+        if (hit) {
             // an absorption with probability p_d = kabs / kap, else a line scattering
             // destroyed with probability eps: one uniform decides both
-            const float pd = (kabsc > 0.0f) ? kabsc * f_rcp(kap) : 0.0f;
-            if ((P.eps != nullptr || P.kabs != nullptr) && (ue < fmaf(1.0f - pd, epsc, pd))) {
-                c_des += 1;
-                outcome = 2;
-                have = false;
-            } else {
-                scat = true;
+            if (destroys) {
+                const float pd = (kabsc > 0.0f) ? kabsc * f_rcp(kap) : 0.0f;
+                if (ue() < fmaf(1.0f - pd, epsc, pd)) {
+                    scat = false;
+                    outcome = 2;
+                    have = false;
+                }
             }
         } else {
-            // cross the face of axis ax
-            tau -= kap * dmin;
-            if (P.jbar_raw) jacc += (int64_t)__float2ll_rn(dmin * H * jscale);
-            float adv = dmin;
-            if (ax != 0) fx = fminf(fmaxf(fmaf(adv * nx, P.inv_dx[0], fx), 0.0f), 1.0f);
-            if (ax != 1) fy = fminf(fmaxf(fmaf(adv * ny, P.inv_dx[1], fy), 0.0f), 1.0f);
-            if (ax != 2) fz = fminf(fmaxf(fmaf(adv * nz, P.inv_dx[2], fz), 0.0f), 1.0f);
-            c_cross += 1;
+            tau -= dtau;
             ncross_pkt += 1;
-            // leaving the cell: flush its register tallies
-            if (P.jbar_raw && jacc != 0) { tally_add_i64(P.jbar_raw + cell, jacc); jacc = 0; }
-            if (P.emis_raw) emis_flush(E, P.emis_raw + (int64_t)cell * P.emis_nch);
-            bool escaped = false;
-            if (ax == 0) {
-                int st = (nx > 0.0f) ? 1 : -1;
-                ci += st; fx = (st > 0) ? 0.0f : 1.0f;
-                if (ci < 0 || ci >= P.n[0]) { if (P.bc[0]) ci = (ci < 0) ? P.n[0] - 1 : 0; else escaped = true; }
-            } else if (ax == 1) {
-                int st = (ny > 0.0f) ? 1 : -1;
-                cj += st; fy = (st > 0) ? 0.0f : 1.0f;
-                if (cj < 0 || cj >= P.n[1]) { if (P.bc[1]) cj = (cj < 0) ? P.n[1] - 1 : 0; else escaped = true; }
-            } else {
-                int st = (nz > 0.0f) ? 1 : -1;
-                ck += st; fz = (st > 0) ? 0.0f : 1.0f;
-                if (ck < 0 || ck >= P.n[2]) { if (P.bc[2]) ck = (ck < 0) ? P.n[2] - 1 : 0; else escaped = true; }
-            }
-            if (escaped) {
-                c_esc += 1;
-                int b = bin_index(x, sedges, P.spec_nb, P.spec_inv_w);
-                if (b < 0) atomicOr(status, (uint32_t)KRT_ST_NAN_BIT);
-                else atomicAdd(reinterpret_cast<unsigned long long *>(P.spec_raw + b), 1ull);
+            // leaving the cell: flush its tallies
+            flush_jbar();
+            flush_emis();
+            const ColdParams C = cold_params();
+            const int gn0 = C->n[0], gn1 = C->n[1], gn2 = C->n[2];
+            const float na = by_axis(ax0, ax1, nx, ny, nz);
+            const int st = na > 0.0f ? 1 : -1;
+            const float fn = na > 0.0f ? 0.0f : 1.0f;
+            const int na_n = by_axis(ax0, ax1, gn0, gn1, gn2);
+            const bool periodic = by_axis(ax0, ax1, C->bc[0], C->bc[1], C->bc[2]) != 0;
+            int c = by_axis(ax0, ax1, ci, cj, ck) + st;
+            const bool out = (unsigned)c >= (unsigned)na_n;
+            c = out ? (st > 0 ? 0 : na_n - 1) : c;  // the wrapped cell of a periodic axis
+            fx = ax0 ? fn : fx;
+            fy = ax1 ? fn : fy;
+            fz = (ax0 || ax1) ? fz : fn;
+            if (out && !periodic) {
+                const int b = bin_index(x, sedges, C->spec_nb, C->spec_inv_w);
+                if (b < 0) atomicOr(C->status, (uint32_t)KRT_ST_NAN_BIT);
+                else atomicAdd(reinterpret_cast<unsigned long long *>(C->spec_raw + b), 1ull);
                 outcome = 1;
                 have = false;
             } else if (ncross_pkt > kMaxCrossings) {
-                c_stuck += 1;
-                atomicOr(status, (uint32_t)KRT_ST_STUCK_BIT);
-                outcome = 3;
-                have = false;
+                give_up();
             } else {
-                cell = (ck * P.n[1] + cj) * P.n[0] + ci;
-                k0c = P.k0[cell];
-                if (P.vx) { vxc = P.vx[cell]; vyc = P.vy[cell]; vzc = P.vz[cell]; }
-                epsc = P.eps ? P.eps[cell] : 0.0f;
-                kabsc = P.kabs ? P.kabs[cell] : 0.0f;
+                ci = ax0 ? c : ci;
+                cj = ax1 ? c : cj;
+                ck = (ax0 || ax1) ? ck : c;
+                cell = (ck * gn1 + cj) * gn0 + ci;
                 enter_cell();
             }
         }
     };
 
-    // A resonant scattering of a live lane at gas-frame frequency xc with the
-    // event's draws (sampler uniforms r1, r2; u_perp components; g, sin, cos psi)
-    // depends only on xc, the direction and the draws, not on where the flight
-    // ends: it is prepared before the flight resolves (so the sampler's LDS
-    // lookups overlap the flight's) and committed if the flight ends in a
-    // scattering.
-    auto prepare = [&](float xc, float r1, float r2, const SDraws &b, ScatPrep &q) {
+    // the resonant scattering of a live lane at gas-frame frequency xc with its
+    // event's draws (eq. riia-scatter), and its emissivity tally
+    auto scatter = [&](float xc, float r1, float r2, const SDraws &b) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
         const float up1 = b.up1, up2 = b.up2, g = b.g, sg = b.sg, cp = b.cp, sp = b.sp;
-        float upar = kTemp ? upar_lds(((kProf == 4) ? P.cs_tab : P.cls_tab) + toff, xc, sac, thdc, r1, r2)
-                           : upar_lds(T, xc, a, thd, r1, r2);
+        const float upar = kTemp ? upar_lds(((kProf == 4) ? P.cs_tab : P.cls_tab) + toff, xc, sac, thdc, r1, r2)
+                                 : upar_lds(T, xc, a, thd, r1, r2);
         // orthonormal basis about n (Duff et al. 2017)
-        float sgn = copysignf(1.0f, nz);
-        float A_ = -f_rcp(sgn + nz);
-        float B_ = nx * ny * A_;
-        float e1x = 1.0f + sgn * nx * nx * A_, e1y = sgn * B_, e1z = -sgn * nx;
-        float e2x = B_, e2y = sgn + ny * ny * A_, e2z = -ny;
-        float ox = g * nx + sg * (cp * e1x + sp * e2x);
-        float oy = g * ny + sg * (cp * e1y + sp * e2y);
-        float oz = g * nz + sg * (cp * e1z + sp * e2z);
-        float rn = f_rsq(ox * ox + oy * oy + oz * oz);
-        q.ox = ox * rn; q.oy = oy * rn; q.oz = oz * rn;
-        // eq. riia-scatter
-        q.xo = xc + upar * (g - 1.0f) + sg * (up1 * cp + up2 * sp);
-        if constexpr (kTemp) q.xo *= isc;  // back to reference units
-        q.kb = -1;
-        q.wq = 0;
+        const float sgn = copysignf(1.0f, nz);
+        const float A_ = -f_rcp(sgn + nz);
+        const float e2x = nx * ny * A_, e2y = fmaf(ny * ny, A_, sgn), e2z = -ny;
+        const float e1x = fmaf(A_, nx * (nx * sgn), 1.0f), e1y = sgn * e2x, e1z = -sgn * nx;
+        float ox = fmaf(g, nx, sg * fmaf(cp, e1x, sp * e2x));
+        float oy = fmaf(g, ny, sg * fmaf(cp, e1y, sp * e2y));
+        float oz = fmaf(g, nz, sg * fmaf(cp, e1z, sp * e2z));
+        const float rn = f_rsq(fmaf(oz, oz, fmaf(ox, ox, oy * oy)));
+        ox *= rn; oy *= rn; oz *= rn;
+        float xo = fmaf(sg, fmaf(up1, cp, up2 * sp), fmaf(upar, g - 1.0f, xc));
+        if constexpr (kTemp) xo *= isc;  // back to reference units
         if (P.emis_raw) {
-            float gc = nx * P.n_cam[0] + ny * P.n_cam[1] + nz * P.n_cam[2];
-            float upc = up1 * (e1x * P.n_cam[0] + e1y * P.n_cam[1] + e1z * P.n_cam[2]) +
-                        up2 * (e2x * P.n_cam[0] + e2y * P.n_cam[1] + e2z * P.n_cam[2]);
-            float xcam = xc + upar * (gc - 1.0f) + upc;
-            if constexpr (kTemp) xcam *= isc;
-            xcam += P.n_cam[0] * vxc + P.n_cam[1] * vyc + P.n_cam[2] * vzc;
-            q.kb = bin_index(xcam, cedges, P.emis_nch, P.ch_inv_w);
-            float wph = (P.phase == KRT_PHASE_DIPOLE_I) ? 0.75f * (1.0f + gc * gc) : 1.0f;
-            // contributions below 2^32 (F <= 30) convert through 32 bits
-            const float wf = wph * P.frac_scale;
-            q.wq = P.emis_w32 ? (int64_t)__float2uint_rn(wf) : (int64_t)__float2ll_rn(wf);
+            const float cx = P.n_cam[0], cy = P.n_cam[1], cz = P.n_cam[2];
+            const float gc = dot3(nx, cx, ny, cy, nz, cz);
+            const float upc = fmaf(up1, dot3(e1x, cx, e1y, cy, e1z, cz), up2 * dot3(e2x, cx, e2y, cy, e2z, cz));
+            float xcam = fmaf(upar, gc - 1.0f, xc) + upc;
+            const float vc = dot3(cx, vxc, cy, vyc, cz, vzc);
+            xcam = kTemp ? fmaf(xcam, isc, vc) : xcam + vc;
+            const int ch = channel_of(xcam, cedges, P.emis_nch, P.ch_inv_w, P.ch_lo, P.ch_safe);
+            if ((unsigned)ch < (unsigned)P.emis_nch) {
+                int64_t wq = 0;
+                if constexpr (kDip) {
+                    // contributions below 2^32 (F <= 30) convert through 32 bits
+                    const float wf = 0.75f * fmaf(gc, gc, 1.0f) * P.frac_scale;
+                    wq = P.emis_w32 ? (int64_t)__float2uint_rn(wf) : (int64_t)__float2ll_rn(wf);
+                }
+                E.add(ch, wq, flush_emis);
+            } else {
+                ndrop += 1;
+            }
         }
-    };
-    auto commit = [&](const ScatPrep &q) {
-        if (P.emis_raw) {
-            if (q.kb >= 1 && q.kb <= P.emis_nch)
-                emis_add(E, q.kb - 1, q.wq, P.emis_raw + (int64_t)cell * P.emis_nch);
-            else
-                c_drop += 1;
-        }
-        nx = q.ox; ny = q.oy; nz = q.oz;
-        x = q.xo + nx * vxc + ny * vyc + nz * vzc;
+        nx = ox; ny = oy; nz = oz;
+        x = fmaf(vzc, nz, fmaf(vyc, ny, fmaf(vxc, nx, xo)));
         nscat_pkt += 1;
-        c_scat += 1;
     };
 
-    // a retired packet: flush the tallies of its last cell, log it
-    auto retire = [&]() {
-        if (P.jbar_raw && jacc != 0) { tally_add_i64(P.jbar_raw + cell, jacc); jacc = 0; }
-        if (P.emis_raw) emis_flush(E, P.emis_raw + (int64_t)cell * P.emis_nch);
-        if (P.plog) {
-            float *L = P.plog + 8 * (pid - P.packet_offset);
+    // a retired packet: write back the tallies of its last cell, count and log it
+    auto retire = [&]() __attribute__((always_inline)) {
+        flush_jbar();
+        flush_emis();
+        count(outcome - 1, 1);
+        count(kLcScat, nscat_pkt);
+        count(kLcCross, ncross_pkt);
+        if (ndrop) { count(kLcDrop, ndrop); ndrop = 0; }
+        const ColdParams C = cold_params();
+        if (C->plog) {
+            float *L = C->plog + 8 * (pid - C->packet_offset);
             L[0] = x; L[1] = (float)nscat_pkt; L[2] = (float)outcome;
             L[3] = nx; L[4] = ny; L[5] = nz;
             L[6] = (float)cell; L[7] = (float)ev;
@@ -652,7 +748,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     // as records (their cell's register tallies flushed first); one
     // wave-aggregated atomic takes the slots.  A parked lane is free for new
     // work, with no outcome.  The budget bounds a round by its slowest packet.
-    auto park = [&](bool want, bool &scat, float xc, uint32_t kind) {
+    auto park = [&](bool want, bool &scat, float xc, uint32_t kind) __attribute__((always_inline)) {
         const uint64_t pm = __ballot(want);
         if (pm == 0ull) return;
         const int leader = __ffsll((long long)pm) - 1;
@@ -660,8 +756,9 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         if (lane == leader) base = atomicAdd(P.park_count, (unsigned long long)__popcll(pm));
         base = __shfl(base, leader, 64);
         if (want) {
-            if (P.jbar_raw && jacc != 0) { tally_add_i64(P.jbar_raw + cell, jacc); jacc = 0; }
-            if (P.emis_raw) emis_flush(E, P.emis_raw + (int64_t)cell * P.emis_nch);
+            flush_jbar();
+            flush_emis();
+            if (ndrop) { count(kLcDrop, ndrop); ndrop = 0; }
             const uint64_t slot = base + (uint64_t)__popcll(pm & lanemask_lt);
             if (slot < P.park_cap) {
                 uint4 *r = P.park_out + kParkQuads * slot;
@@ -670,163 +767,158 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 r[2] = make_uint4(__float_as_uint(nx), __float_as_uint(ny), __float_as_uint(nz), nscat_pkt);
                 r[3] = make_uint4(ncross_pkt, __float_as_uint(xc), kind, 0u);
             } else {
-                atomicOr(status, (uint32_t)KRT_ST_STUCK_BIT);  // the host sizes the list; never expected
-                c_stuck += 1;
+                atomicOr(P.status, (uint32_t)KRT_ST_STUCK_BIT);  // the host sizes the list; never expected
+                count(kLcStuck, 1);
+                count(kLcScat, nscat_pkt);
+                count(kLcCross, ncross_pkt);
             }
             have = false;
             scat = false;
         }
     };
 
+    // the event of this lane is over (scattering walked, or a call): the next one's draws
+    auto next_event = [&](auto draw) __attribute__((always_inline)) {
+        ev += 1;
+        draw();
+        if (ev > max_events) give_up();
+    };
+
+    // Packets start spread over the waves: wave w (counted across the
+    // workgroups first, so that consecutive waves sit on different CUs) begins
+    // with the packets [w first_lanes, (w + 1) first_lanes); the pool beyond
+    // them is shared (empty where first_lanes < 64).
+    const uint64_t n_work = P.n_res + P.n_packets;
+    const uint64_t wave = (uint64_t)(threadIdx.x / 64) * gridDim.x + blockIdx.x;
+    const uint64_t n_first = (uint64_t)(blockDim.x / 64) * gridDim.x * (uint64_t)P.first_lanes;
+    bool first = true;
+    int ticks = 0;
     bool tail = false;
     for (;;) {
         // ---- refill retired lanes from the global queue -------------------
         bool need = !have && !done;
         uint64_t need_mask = __ballot(need);
         if (need_mask) {
-            int cnt = __popcll(need_mask);
-            int leader = __ffsll((long long)need_mask) - 1;
             unsigned long long base = 0;
-            if (lane == leader) base = atomicAdd(P.work_counter, (unsigned long long)cnt);
-            base = __shfl(base, leader, 64);
+            if (first) {
+                base = wave * (uint64_t)P.first_lanes;
+                first = false;
+                if (lane >= P.first_lanes) { done = true; need = false; }
+            } else {
+                const int leader = __ffsll((long long)need_mask) - 1;
+                if (lane == leader) base = n_first + atomicAdd(P.work_counter, (unsigned long long)__popcll(need_mask));
+                base = __shfl(base, leader, 64);
+            }
+            uint64_t idx = 0;
             if (need) {
-                uint64_t idx = base + (uint64_t)__popcll(need_mask & lanemask_lt);
-                if (idx < P.n_res) {
+                idx = base + (uint64_t)__popcll(need_mask & lanemask_lt);
+                if (idx >= n_work) { done = true; need = false; }
+            }
+            const bool fresh_pkt = need && idx >= P.n_res;
+            const uint64_t fm = __ballot(fresh_pkt);
+            if (fm && lane == __ffsll((long long)fm) - 1) count(kLcEmit, (uint64_t)__popcll(fm));
+            if (need) {
+                const ColdParams C = cold_params();
+                if (!fresh_pkt) {
                     // ---- a packet back from a network call: its next event ----
-                    const uint4 *r = P.res_in + kParkQuads * idx;
+                    const uint4 *r = C->res_in + kParkQuads * idx;
                     const uint4 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
                     pid = (uint64_t)r0.x | ((uint64_t)r0.y << 32);
                     ev = r0.z;
                     cell = (int)r0.w;
-                    ci = cell % P.n[0];
-                    cj = (cell / P.n[0]) % P.n[1];
-                    ck = cell / (P.n[0] * P.n[1]);
+                    locate();
                     fx = __uint_as_float(r1.x); fy = __uint_as_float(r1.y); fz = __uint_as_float(r1.z);
                     x = __uint_as_float(r1.w);
                     nx = __uint_as_float(r2.x); ny = __uint_as_float(r2.y); nz = __uint_as_float(r2.z);
                     nscat_pkt = r2.w;
                     ncross_pkt = r3.x;
-                    k0c = P.k0[cell];
-                    if (P.vx) { vxc = P.vx[cell]; vyc = P.vy[cell]; vzc = P.vz[cell]; }
-                    else { vxc = vyc = vzc = 0.0f; }
-                    epsc = P.eps ? P.eps[cell] : 0.0f;
-                    kabsc = P.kabs ? P.kabs[cell] : 0.0f;
                     enter_cell();
-                    jacc = 0;
-                    seg = 0;
-                    ev += 1;
-                    if ((uint64_t)ev > P.max_events) {
-                        c_stuck += 1;
-                        atomicOr(status, (uint32_t)KRT_ST_STUCK_BIT);
-                        outcome = 3;
-                        have = false;
-                    } else {
-                        const uint4 A = philox(make_uint4(ev, r0.x, r0.y, 0u), P.key0, P.key1);
-                        tau = -f_log(u01(A.x));
-                        wa1 = A.y; wa2 = A.z; wa3 = A.w;
-                        have = true;
-                    }
-                } else if (idx - P.n_res >= P.n_packets) {
-                    done = true;
                 } else {
                     // ---- emission (event 0) ----------------------------------
-                    pid = P.packet_offset + P.new_lo + (idx - P.n_res);
+                    pid = C->packet_offset + C->new_lo + (idx - C->n_res);
                     const uint32_t plo = (uint32_t)pid, phi = (uint32_t)(pid >> 32);
-                    uint4 e0 = philox(make_uint4(0u, plo, phi, 0u), P.key0, P.key1);
-                    if (P.source == KRT_SRC_BEAM_I) {
-                        nx = P.src_dir[0]; ny = P.src_dir[1]; nz = P.src_dir[2];
+                    uint4 e0 = philox(make_uint4(0u, plo, phi, 0u), C->key0, C->key1);
+                    if (C->source == KRT_SRC_BEAM_I) {
+                        nx = C->src_dir[0]; ny = C->src_dir[1]; nz = C->src_dir[2];
                     } else {
-                        float mu = 2.0f * u01(e0.x) - 1.0f;
-                        float st = f_sqrt(fmaxf(0.0f, 1.0f - mu * mu));
+                        float mu = fmaf(2.0f, u01(e0.x), -1.0f);
+                        float st = f_sqrt(fmaxf(0.0f, fmaf(-mu, mu, 1.0f)));
                         float ph = u01(e0.y);
                         nx = st * cos_rev(ph); ny = st * sin_rev(ph); nz = mu;
                     }
-                    if (P.source == KRT_SRC_VOLUME_I) {
-                        uint4 e1 = philox(make_uint4(0u, plo, phi, 1u), P.key0, P.key1);
-                        int col = (int)__umulhi(e0.z, (uint32_t)P.ncell);
-                        cell = (u01(e0.w) < P.alias_prob[col]) ? col : P.alias_idx[col];
-                        ci = cell % P.n[0];
-                        cj = (cell / P.n[0]) % P.n[1];
-                        ck = cell / (P.n[0] * P.n[1]);
+                    if (C->source == KRT_SRC_VOLUME_I) {
+                        uint4 e1 = philox(make_uint4(0u, plo, phi, 1u), C->key0, C->key1);
+                        int col = (int)__umulhi(e0.z, (uint32_t)C->ncell);
+                        cell = (u01(e0.w) < C->alias_prob[col]) ? col : C->alias_idx[col];
+                        locate();
                         fx = u01(e1.x); fy = u01(e1.y); fz = u01(e1.z);
                     } else {
                         int c3[3]; float f3[3];
                         float nd[3] = {nx, ny, nz};
                         double u2[2] = {0.0, 0.0};
-                        if (P.source == KRT_SRC_PLANE_I) {
-                            uint4 e1 = philox(make_uint4(0u, plo, phi, 1u), P.key0, P.key1);
+                        if (C->source == KRT_SRC_PLANE_I) {
+                            uint4 e1 = philox(make_uint4(0u, plo, phi, 1u), C->key0, C->key1);
                             u2[0] = (double)u01(e1.x); u2[1] = (double)u01(e1.y);
                         }
 #pragma unroll
                         for (int d = 0; d < 3; ++d) {
-                            double X = P.src_pos[d];
-                            if (P.source == KRT_SRC_PLANE_I && d < 2) X = P.lo[d] + u2[d] * (P.hi[d] - P.lo[d]);
-                            double f = (X - P.lo[d]) / P.dxd[d];
+                            double X = C->src_pos[d];
+                            if (C->source == KRT_SRC_PLANE_I && d < 2) X = fma(u2[d], C->hi[d] - C->lo[d], C->lo[d]);
+                            double f = (X - C->lo[d]) / C->dxd[d];
                             double fl = floor(f);
                             int c = (int)fl;
                             float fr = (float)(f - fl);
                             if (fl == f && nd[d] < 0.0f) { c -= 1; fr = 1.0f; }
                             if (c < 0) { c = 0; fr = 0.0f; }
-                            if (c >= P.n[d]) { c = P.n[d] - 1; fr = 1.0f; }
+                            if (c >= C->n[d]) { c = C->n[d] - 1; fr = 1.0f; }
                             c3[d] = c; f3[d] = fr;
                         }
                         ci = c3[0]; cj = c3[1]; ck = c3[2];
                         fx = f3[0]; fy = f3[1]; fz = f3[2];
-                        cell = (ck * P.n[1] + cj) * P.n[0] + ci;
+                        cell = (ck * C->n[1] + cj) * C->n[0] + ci;
                     }
-                    k0c = P.k0[cell];
-                    if (P.vx) { vxc = P.vx[cell]; vyc = P.vy[cell]; vzc = P.vz[cell]; }
-                    else { vxc = vyc = vzc = 0.0f; }
-                    epsc = P.eps ? P.eps[cell] : 0.0f;
-                kabsc = P.kabs ? P.kabs[cell] : 0.0f;
                     enter_cell();
-                    float xg = P.src_x0;
-                    if (P.src_profile != KRT_PROF_DELTA_I) {
-                        uint4 e2 = philox(make_uint4(0u, plo, phi, 2u), P.key0, P.key1);
+                    float xg = C->src_x0;
+                    if (C->src_profile != KRT_PROF_DELTA_I) {
+                        uint4 e2 = philox(make_uint4(0u, plo, phi, 2u), C->key0, C->key1);
                         float rr = f_sqrt(-f_log(u01(e2.x)));
                         float th = u01(e2.y);
                         xg = rr * cos_rev(th);
-                        if (P.src_profile == KRT_PROF_VOIGT_I) {
+                        if (C->src_profile == KRT_PROF_VOIGT_I) {
                             float c = u01(e2.z) - 0.5f;  // Cauchy(a): a tan(pi c)
-                            xg += (kTemp ? ac : a) * sin_rev(0.5f * c) * f_rcp(cos_rev(0.5f * c));
+                            xg = fmaf((kTemp ? ac : a) * sin_rev(0.5f * c), f_rcp(cos_rev(0.5f * c)), xg);
                         }
                         if constexpr (kTemp) xg *= isc;  // the emitting cell's units -> reference
                     }
-                    x = xg + nx * vxc + ny * vyc + nz * vzc;
-                    ev = 1;
-                    uint4 A = philox(make_uint4(1u, plo, phi, 0u), P.key0, P.key1);
-                    tau = -f_log(u01(A.x));
-                    wa1 = A.y; wa2 = A.z; wa3 = A.w;
+                    x = fmaf(nz, vzc, fmaf(ny, vyc, fmaf(nx, vxc, xg)));
+                    ev = 0;
                     nscat_pkt = 0;
                     ncross_pkt = 0;
-                    seg = 0;
-                    jacc = 0;
-                    have = true;
-                    c_emit += 1;
                 }
+                pk = philox_packet((uint32_t)pid, (uint32_t)(pid >> 32), P.key0, P.key1);
+                seg = 0;
+                jacc = 0;
+                have = true;
+                next_event(draw_event);
             }
         }
         const uint64_t live_mask = __ballot(have);
-        if (live_mask == 0ull) break;
+        // (a packet resumed past its last event is neither live nor done: it retires below)
+        if (live_mask == 0ull && __ballot(!done) == 0ull) break;
         // pool exhausted and few live lanes: continue in tail mode
         if (!kEsc && P.tail_lanes > 0 && __ballot(done) != 0ull && __popcll(live_mask) <= P.tail_lanes) {
             tail = true;
             break;
         }
+        if (++ticks == kEmisTicks) {
+            ticks = 0;
+            flush_emis();
+        }
 
         // ---- one flight segment (divergent) --------------------------------
         bool scat = false;
-        float xc = 0.0f;
-        ScatPrep q;
-        if (kEsc && pend) xc = x - (nx * vxc + ny * vyc + nz * vzc);  // held at its scattering
-        if (have && !pend) {
-            const float xg = (x - (nx * vxc + ny * vyc + nz * vzc)) * (kTemp ? sc : 1.0f);
-            SDraws b;
-            scatter_draws(philox(make_uint4(ev, (uint32_t)pid, (uint32_t)(pid >> 32), 1u), P.key0, P.key1),
-                          P.phase == KRT_PHASE_DIPOLE_I, b);
-            prepare(xg, u01(wa2), u01(wa3), b, q);
-            flight(u01(wa1), scat, xc);
-        }
+        const float xc = gas_freq();
+        if (have && !pend) flight(xc, [&]() __attribute__((always_inline)) { return u01(wa1); }, scat);
 
         // ---- learned whole-cell escape ---------------------------------------
         // At a scattering inside a thick cubic cell, at least esc_depth_min below
@@ -836,93 +928,83 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         // evaluates the network here, batched over the asking lanes of the wave
         // (wave-uniform); park mode writes the packet to the park list and frees
         // the lane, and escape_call_kernel applies the call.
-        bool mlp = false;
-        if (kEsc || kPark) {
+        bool mlp = false, go = false;
+        if (kPark) {
             CellFrame CF{};
             float ltc = 0.0f, ldep = 0.0f;
-            if (kPark && scat) mlp = call_eligible(P, k0c, fx, fy, fz, xc, CF, ltc, ldep);
-            if (kEsc && (scat || pend)) mlp = call_ok(P, k0c, fx, fy, fz, xc);
-            if (kPark) {
-                bool cont = false;
-                if (!mlp && scat) {
-                    commit(q);
-                    cont = ++seg >= P.park_budget;
+            if (scat) mlp = call_eligible(P, k0c, fx, fy, fz, xc, CF, ltc, ldep);
+        }
+        if (kEsc) {
+            if (scat || pend) mlp = call_ok(P, k0c, fx, fy, fz, xc);
+            // once the packet pool is exhausted (some lane of this wave is done) the
+            // wave lives only as long as its slowest packet: fewer asking lanes suffice.
+            // With waiting on (esc_wait > 0) a qualifying lane that finds too few
+            // others holds its scattering (pend) instead of walking it, for at most
+            // esc_wait iterations; the batch also goes when every live lane asks.
+            // While the pool lasts and nothing forces the batch, it takes whole
+            // 16-sample blocks only: the askers past them, in lane order, stay held.
+            const uint64_t wm = __ballot(mlp);
+            const bool tailw = __ballot(done) != 0ull;
+            const int need_lanes = tailw ? P.esc_tail_lanes : P.esc_min_lanes;
+            const bool forced = wm == __ballot(have) || __ballot(pend && pwait >= P.esc_wait) != 0ull;
+            go = wm != 0ull && (__popcll(wm) >= need_lanes || forced);  // wave-uniform
+            bool held = !go;
+            if (go && !tailw && !forced && P.esc_wait > 0 && mlp && __popcll(wm) >= 16)
+                held = __popcll(wm & lanemask_lt) >= (__popcll(wm) & ~15);
+            if (held) {
+                if (mlp && P.esc_wait > 0) {
+                    pwait = pend ? pwait + 1 : 1;
+                    pend = true;
                 }
-                park(mlp || cont, scat, xc, mlp ? 1u : 0u);
-            } else {
-                // once the packet pool is exhausted (some lane of this wave is done) the
-                // wave lives only as long as its slowest packet: fewer asking lanes suffice.
-                // With waiting on (esc_wait > 0) a qualifying lane that finds too few
-                // others holds its scattering (pend) instead of walking it, for at most
-                // esc_wait iterations; the batch also goes when every live lane asks.
-                // While the pool lasts and nothing forces the batch, it takes whole
-                // 16-sample blocks only: the askers past them, in lane order, stay held.
-                uint64_t wm = __ballot(mlp);
-                const bool tailw = __ballot(done) != 0ull;
-                const int need_lanes = tailw ? P.esc_tail_lanes : P.esc_min_lanes;
-                const bool forced = wm == __ballot(have) || __ballot(pend && pwait >= P.esc_wait) != 0ull;
-                const bool go = wm != 0ull && (__popcll(wm) >= need_lanes || forced);  // wave-uniform
-                bool held = !go;
-                if (go && !tailw && !forced && P.esc_wait > 0 && mlp && __popcll(wm) >= 16)
-                    held = __popcll(wm & lanemask_lt) >= (__popcll(wm) & ~15);
-                if (held) {
-                    if (mlp && P.esc_wait > 0) {
-                        pwait = pend ? pwait + 1 : 1;
-                        pend = true;
-                    }
-                    mlp = false;
-                }
-                wm = __ballot(mlp);  // the lanes this batch serves
-                // this event's plain scatterings first, so their prepared state is
-                // not live across the network evaluation
-                if (scat && !mlp && !pend) commit(q);
-                if (go) {
-                    {
-                        float tc, dep;
-                        call_frame(P, k0c, fx, fy, fz, CF, tc, dep);
-                        ltc = __log10f(tc);
-                        ldep = __log10f(dep);
-                    }
-                    const uint32_t plo = (uint32_t)pid, phi = (uint32_t)(pid >> 32);
-                    const uint4 C = philox(make_uint4(ev, plo, phi, 2u), P.key0, P.key1);
-                    const uint4 D = philox(make_uint4(ev, plo, phi, 3u), P.key0, P.key1);
-                    float cnd[10];
-                    call_condition(P, CF, ltc, ldep, xc, nx, ny, nz, cnd);
-                    int face;
-                    float xo, mo[kMlpOut];
-                    call_network(mimg, mbias, mnorm, lane, wm, cnd, C, D, face, xo, mo);
-                    if (mlp) {
-                        int64_t *ebase = P.emis_raw ? P.emis_raw + (int64_t)cell * P.emis_nch : nullptr;
-                        // the deposit spans consecutive channels, each once: direct atomics
-                        call_apply(P, mnorm, cedges, CF, mo, face, xo, C.z, ltc, ldep, xc, vxc, vyc, vzc, fx, fy,
-                                   fz, nx, ny, nz, x, c_skip, c_drop,
-                                   [&](int ch, int64_t w) __attribute__((always_inline)) { tally_add_i64(ebase + ch, w); });
-                        c_mlp += 1;
-                    }
-                }
-                // an event is consumed by a walked scattering or a call; a held one waits
-                const bool served = go && mlp;
-                if (served) pend = false;
-                scat = (scat && !pend) || served;
+                mlp = false;
             }
         }
 
         // ---- resonant scattering (event ev), divergent -----------------------
-        if (scat) {
-            const uint32_t plo = (uint32_t)pid, phi = (uint32_t)(pid >> 32);
-            if (!kEsc && !kPark) commit(q);  // the network modes committed above
-            // next event
-            ev += 1;
-            if ((uint64_t)ev > P.max_events) {
-                c_stuck += 1;
-                atomicOr(status, (uint32_t)KRT_ST_STUCK_BIT);
-                outcome = 3;
-                have = false;
-            } else {
-                uint4 A = philox(make_uint4(ev, plo, phi, 0u), P.key0, P.key1);
-                tau = -f_log(u01(A.x));
-                wa1 = A.y; wa2 = A.z; wa3 = A.w;
+        const bool walk = scat && !mlp && !pend;
+        if (walk) {
+            SDraws b;
+            scatter_draws(wb, kDip, b);
+            scatter(xc, u01(wa2), u01(wa3), b);
+            if constexpr (!kEsc && !kPark) next_event(draw_event);
+        }
+        if (kPark) {
+            const bool cont = walk && ++seg >= P.park_budget;
+            bool go_on = walk;
+            park(mlp || cont, go_on, xc, mlp ? 1u : 0u);
+            if (go_on) next_event(draw_event);
+        }
+        if (kEsc) {
+            if (go) {
+                const uint64_t wm = __ballot(mlp);  // the lanes this batch serves
+                CellFrame CF{};
+                float ltc, ldep;
+                {
+                    float tc, dep;
+                    call_frame(P, k0c, fx, fy, fz, CF, tc, dep);
+                    ltc = __log10f(tc);
+                    ldep = __log10f(dep);
+                }
+                const uint32_t plo = (uint32_t)pid, phi = (uint32_t)(pid >> 32);
+                const uint4 C = philox(make_uint4(ev, plo, phi, 2u), P.key0, P.key1);
+                const uint4 D = philox(make_uint4(ev, plo, phi, 3u), P.key0, P.key1);
+                float cnd[10];
+                call_condition(P, CF, ltc, ldep, xc, nx, ny, nz, cnd);
+                int face;
+                float xo, mo[kMlpOut];
+                call_network(mimg, mbias, mnorm, lane, wm, cnd, C, D, face, xo, mo);
+                if (mlp) {
+                    int64_t *ebase = P.emis_raw ? P.emis_raw + (int64_t)cell * P.emis_nch : nullptr;
+                    // the deposit spans consecutive channels, each once: direct atomics
+                    call_apply(P, mnorm, cedges, CF, mo, face, xo, C.z, ltc, ldep, xc, vxc, vyc, vzc, fx, fy,
+                               fz, nx, ny, nz, x, c_skip, c_drop,
+                               [&](int ch, int64_t w) __attribute__((always_inline)) { tally_add_i64(ebase + ch, w); });
+                    c_mlp += 1;
+                    pend = false;
+                }
             }
+            // an event is consumed by a walked scattering or a call; a held one waits
+            if (walk || mlp) next_event(draw_event);
         }
         if (!have && outcome != 0) retire();
     }
@@ -935,9 +1017,9 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     // the same words mapped by the same functions as in the loop above, so the
     // tallies do not depend on where a packet switches mode.
     if (!kEsc && tail) {
-        const bool dipole = P.phase == KRT_PHASE_DIPOLE_I;
         uint64_t bank_live = 0ull;
-        uint32_t ev0 = 0;
+        int k = 1, rank = 0;
+        uint32_t ev0 = 0, ev1 = 0;  // events the bank holds for this lane: [ev0, ev1)
         bool fresh = false;  // set after a scattering: tau of the new event comes from the draws
         float pt = 0.f, pue = 0.f, pr1 = 0.f, pr2 = 0.f;
         SDraws pb;
@@ -945,26 +1027,28 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         for (;;) {
             const uint64_t live = __ballot(have);
             if (live == 0ull) break;
-            const int k = __popcll(live);
-            const int rank = __popcll(live & lanemask_lt);
-            const int nslot = (63 - rank) / k + 1;
-            const bool out_of_draws = have && (int)(ev - ev0) >= nslot;
-            if (live != bank_live || __ballot(out_of_draws) != 0ull) {
+            if (live != bank_live || __ballot(have && ev == ev1) != 0ull) {
+                k = __popcll(live);
+                rank = __popcll(live & lanemask_lt);
                 if (have) ev0 = ev;
+                ev1 = ev0 + (uint32_t)((63 - rank) / k + 1);
                 const int r = lane % k, sl = lane / k;
                 const int owner = nth_set_lane(live, r);
-                const uint32_t olo = __shfl((uint32_t)pid, owner, 64);
-                const uint32_t ohi = __shfl((uint32_t)(pid >> 32), owner, 64);
+                PhiloxPacket op;
+                op.bk = __shfl(pk.bk, owner, 64);
+                op.hk = __shfl(pk.hk, owner, 64);
+                op.la = __shfl(pk.la, owner, 64);
                 const uint32_t e = __shfl(ev0, owner, 64) + (uint32_t)sl;
-                const uint4 A = philox(make_uint4(e, olo, ohi, 0u), P.key0, P.key1);
+                uint4 A, B;
+                philox_pair(op, e, P.key0, P.key1, A, B);
                 pt = -f_log(u01(A.x));
                 pue = u01(A.y);
                 pr1 = u01(A.z);
                 pr2 = u01(A.w);
-                scatter_draws(philox(make_uint4(e, olo, ohi, 1u), P.key0, P.key1), dipole, pb);
+                scatter_draws(B, kDip, pb);
                 bank_live = live;
             }
-            const int src = have ? (int)(ev - ev0) * k + rank : lane;
+            const int src = have ? (int)__umul24(ev - ev0, (unsigned)k) + rank : lane;
             const float dt = __shfl(pt, src, 64), due = __shfl(pue, src, 64);
             const float dr1 = __shfl(pr1, src, 64), dr2 = __shfl(pr2, src, 64);
             SDraws db;
@@ -972,51 +1056,43 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             db.g = __shfl(pb.g, src, 64); db.sg = __shfl(pb.sg, src, 64);
             db.cp = __shfl(pb.cp, src, 64); db.sp = __shfl(pb.sp, src, 64);
             if (have && fresh) { tau = dt; fresh = false; }
-            bool scat = false;
-            float xc = 0.0f;
-            ScatPrep q;
-            if (have) {
-                prepare((x - (nx * vxc + ny * vyc + nz * vzc)) * (kTemp ? sc : 1.0f), dr1, dr2, db, q);
-                flight(due, scat, xc);
+            if (++ticks == kEmisTicks) {
+                ticks = 0;
+                flush_emis();
             }
+            bool scat = false;
+            const float xc = gas_freq();
+            if (have) flight(xc, [&]() __attribute__((always_inline)) { return due; }, scat);
             bool called = false;
             if (kPark) {
                 CellFrame CF{};
                 float ltc = 0.0f, ldep = 0.0f;
                 called = scat && call_eligible(P, k0c, fx, fy, fz, xc, CF, ltc, ldep);
-                bool cont = false;
-                if (scat && !called) {
-                    commit(q);
-                    cont = ++seg >= P.park_budget;
-                }
-                park(called || cont, scat, xc, called ? 1u : 0u);
             }
-            if (scat) {
-                if (!kPark) commit(q);
-                ev += 1;
-                if ((uint64_t)ev > P.max_events) {
-                    c_stuck += 1;
-                    atomicOr(status, (uint32_t)KRT_ST_STUCK_BIT);
-                    outcome = 3;
-                    have = false;
-                } else {
-                    fresh = true;
-                }
+            bool walk = scat && !called;
+            if (walk) scatter(xc, dr1, dr2, db);
+            if (kPark) {
+                const bool cont = walk && ++seg >= P.park_budget;
+                park(called || cont, walk, xc, called ? 1u : 0u);
             }
+            if (walk) next_event([&]() __attribute__((always_inline)) { fresh = true; });
             if (!have && outcome != 0) retire();
         }
     }
 
-    wave_add_counter(P.counters + KRT_C_EMITTED, c_emit);
-    wave_add_counter(P.counters + KRT_C_ESCAPED, c_esc);
-    wave_add_counter(P.counters + KRT_C_DESTROYED, c_des);
-    wave_add_counter(P.counters + KRT_C_SCATTER, c_scat);
-    wave_add_counter(P.counters + KRT_C_CROSS, c_cross);
-    wave_add_counter(P.counters + KRT_C_STUCK, c_stuck);
-    wave_add_counter(P.counters + KRT_C_EMIS_DROP, c_drop);
     if (kEsc) {
+        wave_add_counter(P.counters + KRT_C_EMIS_DROP, c_drop);
         wave_add_counter(P.counters + KRT_C_MLP_I, c_mlp);
         wave_add_counter(P.counters + KRT_C_SKIPPED_I, c_skip);
+    }
+    __syncthreads();
+    if (threadIdx.x < kNLdsCounters && lcnt[threadIdx.x] != 0ull) {
+        constexpr int slot[kNLdsCounters] = {KRT_C_ESCAPED, KRT_C_DESTROYED, KRT_C_STUCK, KRT_C_EMITTED,
+                                             KRT_C_SCATTER, KRT_C_CROSS, KRT_C_EMIS_DROP};
+        int to = slot[0];
+#pragma unroll
+        for (int i = 1; i < kNLdsCounters; ++i) to = (int)threadIdx.x == i ? slot[i] : to;
+        atomicAdd(reinterpret_cast<unsigned long long *>(P.counters + to), lcnt[threadIdx.x]);
     }
 }
 
@@ -1100,49 +1176,70 @@ __global__ void debug_upar_kernel(const float *tab, float a, float thd, float x,
 }
 
 // ---------------------------------------------------------------- launch ---
-hipError_t launch_transport(const RunParams &P, int mode, int grid, int block, hipStream_t s) {
-    const bool fused = mode == kModeFused;
-    // plain and park: tables and both edge sets; fused: tables, channel edges, image
-    static_assert(sizeof(float) * (kTabFloats + kChanEdgeFloats) + kMlpFwdBytes <= 160 * 1024,
-                  "the network variant's LDS fits one CU (160 KiB)");
-    const size_t lds = fused ? sizeof(float) * (kTabFloats + kChanEdgeFloats) + (size_t)kMlpFwdBytes
-                             : sizeof(float) * (kTabFloats + kEdgeFloats);
-    // the fused variant is compiled for the block size: up to 512 lanes 256
-    // VGPRs (no spills, 2 waves per SIMD; the default), up to 768 lanes 168
-    // VGPRs (spills, 3 waves), above that 128 (4 waves, heavy spills).
-    // Profile modes 1 and 2 exist for the plain walk only; park mode has the
-    // plain walk's register budget (1024 lanes).
-    const int variant = fused ? (block <= 512 ? 2 : (block <= 768 ? 5 : 1))
-                              : (mode == kModePark ? 7
-                                                   : (P.bratio ? 8 : (P.tclass ? 6 : (P.profile_mode == 1 ? 3
-                                                                      : (P.profile_mode == 2 ? 4 : 0)))));
-    static bool attr_set[9] = {false, false, false, false, false, false, false, false, false};
-    const void *fns[9] = {reinterpret_cast<const void *>(mc_transport_kernel<kModePlain, 1024>),
-                          reinterpret_cast<const void *>(mc_transport_kernel<kModeFused, 1024>),
-                          reinterpret_cast<const void *>(mc_transport_kernel<kModeFused, 512>),
-                          reinterpret_cast<const void *>(mc_transport_kernel<kModePlain, 1024, 1>),
-                          reinterpret_cast<const void *>(mc_transport_kernel<kModePlain, 1024, 2>),
-                          reinterpret_cast<const void *>(mc_transport_kernel<kModeFused, 768>),
-                          reinterpret_cast<const void *>(mc_transport_kernel<kModePlain, 1024, 3>),
-                          reinterpret_cast<const void *>(mc_transport_kernel<kModePark, 1024>),
-                          reinterpret_cast<const void *>(mc_transport_kernel<kModePlain, 1024, 4>)};
-    if (!attr_set[variant]) {
-        hipError_t e = hipFuncSetAttribute(fns[variant], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+// dynamic LDS of a transport launch: at most the tables, the edges and the
+// dipole windows of 1024 threads, or the tables and the network image
+constexpr int kPlainLds = sizeof(float) * (kTabFloats + kEdgeFloats) + sizeof(int64_t) * kNLdsCounters;
+constexpr int kFusedLds =
+    (int)sizeof(float) * (kTabFloats + kChanEdgeFloats) + kMlpFwdBytes + (int)sizeof(int64_t) * kNLdsCounters;
+constexpr int kMaxTransportLds = std::max(kPlainLds + (int)sizeof(int64_t) * kEmisSlots * 1024, kFusedLds);
+static_assert(kMaxTransportLds <= 160 * 1024, "a workgroup's LDS fits one CU (160 KiB)");
+static_assert((kTabFloats + kEdgeFloats) % 4 == 0 && (kTabFloats + kChanEdgeFloats + kMlpFwdBytes / 4) % 4 == 0,
+              "the counters are aligned");
+
+// Packets a wave starts with, so that few packets use many SIMDs: up to two
+// waves per SIMD (eight of a workgroup's) share them evenly, more packets fill
+// those waves' lanes first and then further waves.  A lone wave leaves issue
+// slots idle that a second one takes, a third and fourth only slow the first
+// two (10,000 packets on a tau0 = 300 slab: 15.1 ms with one wave per SIMD,
+// 14.9 with two, 15.0 with three, 15.5 with four; 130,000 on a 32^3 dipole
+// sphere of tau0 = 1e3: 30.9, 30.2, 32.6, 33.5).
+static int first_lanes(uint64_t n, uint64_t waves, uint64_t grid) {
+    const uint64_t w = std::min(waves, 8 * grid);
+    return (int)std::min<uint64_t>(64, (n + w - 1) / w);
+}
+
+template <int kMode, int kMaxThreads, int kProf, bool kDip>
+static hipError_t launch_transport_t(const RunParams &P, int grid, int block, size_t lds, hipStream_t s) {
+    auto fn = mc_transport_kernel<kMode, kMaxThreads, kProf, kDip>;
+    static std::atomic<bool> attr_set{false};  // the most any launch of this variant asks for
+    if (!attr_set.load()) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kMaxTransportLds);
         if (e != hipSuccess) return e;
-        attr_set[variant] = true;
+        attr_set.store(true);
     }
-    switch (variant) {
-        case 0: hipLaunchKernelGGL((mc_transport_kernel<kModePlain, 1024>), dim3(grid), dim3(block), lds, s, P); break;
-        case 1: hipLaunchKernelGGL((mc_transport_kernel<kModeFused, 1024>), dim3(grid), dim3(block), lds, s, P); break;
-        case 2: hipLaunchKernelGGL((mc_transport_kernel<kModeFused, 512>), dim3(grid), dim3(block), lds, s, P); break;
-        case 3: hipLaunchKernelGGL((mc_transport_kernel<kModePlain, 1024, 1>), dim3(grid), dim3(block), lds, s, P); break;
-        case 5: hipLaunchKernelGGL((mc_transport_kernel<kModeFused, 768>), dim3(grid), dim3(block), lds, s, P); break;
-        case 6: hipLaunchKernelGGL((mc_transport_kernel<kModePlain, 1024, 3>), dim3(grid), dim3(block), lds, s, P); break;
-        case 7: hipLaunchKernelGGL((mc_transport_kernel<kModePark, 1024>), dim3(grid), dim3(block), lds, s, P); break;
-        case 8: hipLaunchKernelGGL((mc_transport_kernel<kModePlain, 1024, 4>), dim3(grid), dim3(block), lds, s, P); break;
-        default: hipLaunchKernelGGL((mc_transport_kernel<kModePlain, 1024, 2>), dim3(grid), dim3(block), lds, s, P); break;
-    }
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, s, P);
     return hipGetLastError();
+}
+
+template <int kProf>
+static hipError_t launch_plain(const RunParams &P, int grid, int block, hipStream_t s) {
+    // tables and both edge sets; with dipole phase the emissivity windows' sums
+    if (P.phase == KRT_PHASE_DIPOLE_I)
+        return launch_transport_t<kModePlain, 1024, kProf, true>(
+            P, grid, block, kPlainLds + (P.emis_raw ? sizeof(int64_t) * kEmisSlots * (size_t)block : 0), s);
+    return launch_transport_t<kModePlain, 1024, kProf, false>(P, grid, block, kPlainLds, s);
+}
+
+hipError_t launch_transport(const RunParams &P0, int mode, int grid, int block, hipStream_t s) {
+    RunParams P = P0;
+    P.first_lanes = first_lanes(P.n_res + P.n_packets, (uint64_t)grid * (uint64_t)(block / 64), (uint64_t)grid);
+    if (mode == kModeFused) {
+        // compiled for the block size: up to 512 lanes 256 VGPRs (2 waves per SIMD;
+        // the default), up to 768 lanes 168 VGPRs (spills, 3 waves), above that
+        // 128 (4 waves, heavy spills)
+        if (block <= 512) return launch_transport_t<kModeFused, 512, 0, false>(P, grid, block, kFusedLds, s);
+        if (block <= 768) return launch_transport_t<kModeFused, 768, 0, false>(P, grid, block, kFusedLds, s);
+        return launch_transport_t<kModeFused, 1024, 0, false>(P, grid, block, kFusedLds, s);
+    }
+    if (mode == kModePark)
+        return launch_transport_t<kModePark, 1024, 0, false>(P, grid, block, kPlainLds, s);
+    // temperature and the profile modes exist for the plain walk only
+    if (P.bratio) return launch_plain<4>(P, grid, block, s);
+    if (P.tclass) return launch_plain<3>(P, grid, block, s);
+    if (P.profile_mode == 1) return launch_plain<1>(P, grid, block, s);
+    if (P.profile_mode == 2) return launch_plain<2>(P, grid, block, s);
+    return launch_plain<0>(P, grid, block, s);
 }
 
 // ------------------------------------------------------------ call kernel ---

@@ -1,0 +1,81 @@
+"""The transport's tally windows and start of packets at the sizes where they
+can go wrong, against the same walk tallied or split differently: integer
+tallies are exact sums, so the comparisons are exact."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2608_09340_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("phase", [0, 1])
+@pytest.mark.parametrize("nch", [1, 3, 7, 16, 64])
+def test_channel_windows_match_fine_channels(gpu_ctx, phase, nch):
+    """A window moves rarely with wide channels and at nearly every scattering
+    with 256 narrow ones; the fine channels' sums over each wide channel are
+    the wide run's tallies (the edges of the wide channels are edges of the
+    fine ones)."""
+    from paper_2608_09340_amd import krt
+    lo, hi, n = -6.0, 6.0, 20000
+    fine = 256 // nch * nch
+    T = krt.Transport(W.sphere(7, 200.0, 1e-2, phase=phase, emis=(nch, lo, hi), vmax=2.0), ctx=gpu_ctx)
+    a = T.run(n, seed=11)
+    F = krt.Transport(W.sphere(7, 200.0, 1e-2, phase=phase, emis=(fine, lo, hi), vmax=2.0), ctx=gpu_ctx)
+    b = F.run(n, seed=11)
+    assert np.array_equal(a["emis_raw"], b["emis_raw"].reshape(-1, nch, fine // nch).sum(axis=2))
+    assert a["counters"] == b["counters"]
+    assert a["counters"]["emis_dropped"] > 0
+    if phase == 0:  # every scattering tallied once, 2^20 each
+        c = a["counters"]
+        assert int(a["emis_raw"].sum()) == (c["scatterings"] - c["emis_dropped"]) << 20
+
+
+def test_windows_hold_long_visits(gpu_ctx):
+    """One thick cell and few packets: a lane adds far more scatterings to one
+    window than an 8-bit count holds."""
+    from paper_2608_09340_amd import krt
+    p = W._problem((1, 1, 1), (-1.0,) * 3, (1.0,) * 3, (0, 0, 0), np.array([3000.0]), 1e-2,
+                   source={"kind": W.SRC_POINT, "pos": (0.0, 0.0, 0.0), "profile": W.PROF_DELTA, "x0": 0.0},
+                   tally={"spec_nbins": 16, "spec_lo": -16.0, "spec_hi": 16.0, "emis_nch": 2, "ch_lo": -64.0,
+                          "ch_hi": 64.0, "n_cam": (1.0, 0.0, 0.0)})
+    r = krt.Transport(p, ctx=gpu_ctx).run(100, seed=1)
+    c = r["counters"]
+    assert c["scatterings"] > 100 * 1000 and c["emis_dropped"] == 0
+    assert int(r["emis_raw"].sum()) == c["scatterings"] << 20
+
+
+@pytest.mark.parametrize("ch", [(1e6, 1e6 + 1.0, 64), (-1e-6, 1e-6, 256), (-40.0, 40.0, 1)])
+def test_channels_at_the_rounding_of_their_edges(gpu_ctx, ch):
+    """Channels narrower than the rounding of their edges, far from zero, or a
+    single one: totals and drops still account for every scattering, and the
+    beam's own frequency offset puts scatterings inside the first set."""
+    from paper_2608_09340_amd import krt
+    p = W.thin_moving_slab(tau=5.0, a=1e-2)
+    p["tally"].update({"ch_lo": ch[0], "ch_hi": ch[1], "emis_nch": ch[2]})
+    if ch[0] > 1e5:
+        p["grid"]["vel"][:] = 0.0
+        p["grid"]["vel"][2, :] = 1e6
+    r = krt.Transport(p, ctx=gpu_ctx).run(5000, seed=3)
+    c = r["counters"]
+    assert c["scatterings"] > 1000
+    assert int(r["emis_raw"].sum()) == (c["scatterings"] - c["emis_dropped"]) << 20
+    if ch[0] != -1e-6:
+        assert c["emis_dropped"] < c["scatterings"]
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 4095, 4097, 70001])
+def test_spread_packets_match_split_range(gpu_ctx, n):
+    """Few packets start spread over the waves; the same packets as two calls
+    start in other lanes and give the same sums."""
+    from paper_2608_09340_amd import krt
+    T = krt.Transport(W.sphere(5, 30.0, 1e-2, phase=1, emis=(16, -12.0, 12.0)), ctx=gpu_ctx)
+    a = T.run(n, seed=3)
+    assert a["counters"]["emitted"] == n == a["counters"]["escaped"]
+    k = (n + 1) // 3
+    parts = [T.run(m, seed=3, packet_offset=o) for m, o in ((k, 0), (n - k, k)) if m]
+    for key in ("spec_raw", "emis_raw"):
+        assert np.array_equal(a[key], sum(r[key] for r in parts))
+    assert a["counters"]["scatterings"] == sum(r["counters"]["scatterings"] for r in parts)
