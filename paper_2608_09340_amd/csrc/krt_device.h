@@ -156,20 +156,31 @@ __device__ __forceinline__ float voigt_analytic(float a, float u0, float ua) {
 // Atom parallel velocity for gas-frame frequency x (Sec. 2.1.1): piece by r1
 // against the cumulative piece probabilities, quantile by r2, bilinear in
 // (row of |x|, quantile node).
-__device__ __forceinline__ float upar_lds(const float *T, float x, float a, float thd,
-                                          float r1, float r2) {
+// The piece probabilities (cumulative, first three) depend on |x| alone and can
+// be read ahead of the draw.
+struct UparMass {
+    float4 m0, m1;
+    float fm;
+};
+__device__ __forceinline__ UparMass upar_mass(const float *T, float xa) {
+#pragma clang fp contract(off)
+    const float pm = xa * (float)(kMassN / 8);
+    const int im = max(0, min((int)pm, kMassN - 1));
+    UparMass q;
+    q.fm = pm - (float)im;
+    q.m0 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im);
+    q.m1 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im + 4);
+    return q;
+}
+__device__ __forceinline__ float upar_from(const float *T, const UparMass &q, float x, float a, float thd, float r1,
+                                           float r2) {
 #pragma clang fp contract(off)
     const float xa = fabsf(x);
     const bool lin = xa < 8.0f;
-    // cumulative piece probabilities; beyond the table every draw is the bump's
-    const float pm = xa * (float)(kMassN / 8);
-    const int im = max(0, min((int)pm, kMassN - 1));
-    const float fm = pm - (float)im;
-    const float4 m0 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im);
-    const float4 m1 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im + 4);
-    const float c1 = lin ? fmaf(fm, m1.x - m0.x, m0.x) : 0.0f;
-    const float c2 = lin ? fmaf(fm, m1.y - m0.y, m0.y) : 0.0f;
-    const float c3 = lin ? fmaf(fm, m1.z - m0.z, m0.z) : 1.0f;
+    // beyond the table every draw is the bump's
+    const float c1 = lin ? fmaf(q.fm, q.m1.x - q.m0.x, q.m0.x) : 0.0f;
+    const float c2 = lin ? fmaf(q.fm, q.m1.y - q.m0.y, q.m0.y) : 0.0f;
+    const float c3 = lin ? fmaf(q.fm, q.m1.z - q.m0.z, q.m0.z) : 1.0f;
     const float p = __builtin_unpredictable(lin) ? xa * 6.0f : fminf(fmaf(f_log(xa * 0.125f), kRowInvLog, 48.0f), 63.0f);
     const int j = max(0, min((int)p, kRows - 2));
     const float fr = p - (float)j;
@@ -194,6 +205,10 @@ __device__ __forceinline__ float upar_lds(const float *T, float x, float a, floa
     const float uw = xa + (l1 ? -s : s);
     const float u = spike ? us : ((l2 && !l1) ? v : uw);
     return (x < 0.0f) ? -u : u;  // p(u | -x) = p(-u | x)
+}
+
+__device__ __forceinline__ float upar_lds(const float *T, float x, float a, float thd, float r1, float r2) {
+    return upar_from(T, upar_mass(T, fabsf(x)), x, a, thd, r1, r2);
 }
 
 // Dipole phase (3/8)(1 + g^2): g = 2 sinh(asinh(4u - 2)/3).

@@ -69,21 +69,23 @@ struct EmisWindow {
             }
         }
     }
-    // one scattering of weight v (kSum; 2^frac_bits otherwise) into channel ch;
-    // write_back flushes this window
+    // one scattering of weight v (kSum; 2^frac_bits otherwise) into channel ch if
+    // `in`; write_back flushes this window
     template <class F>
-    __device__ __forceinline__ void add(int ch, int64_t v, F write_back) {
+    __device__ __forceinline__ void add(bool in, int ch, int64_t v, F write_back) {
         int d = ch - w;
-        if ((unsigned)d >= (unsigned)kEmisSlots) {
+        if (in && (unsigned)d >= (unsigned)kEmisSlots) {
             write_back();
             w = ch - (kEmisSlots / 2 - 1);
             d = kEmisSlots / 2 - 1;
         }
         if constexpr (kSum) {
-            __hip_atomic_fetch_add(acc + d * stride, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            cnt |= 1ull << d;
+            if (in) {
+                __hip_atomic_fetch_add(acc + d * stride, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                cnt |= 1ull << d;
+            }
         } else {
-            cnt += 1ull << (8 * d);
+            cnt += (uint64_t)(in ? 1 : 0) << ((8 * d) & 63);
         }
     }
 };
@@ -524,13 +526,25 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
 
     const int lane = __lane_id();
     const uint64_t lanemask_lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const float a = P.a, thd = P.thd;
+    float a = P.a, thd = P.thd;
+    // what every iteration reads stays in vector registers: as scalars these
+    // values are too many, and would be loaded again, with a wait, in each
+    float dx0 = P.dx[0], dx1 = P.dx[1], dx2 = P.dx[2], idx0 = P.inv_dx[0], idx1 = P.inv_dx[1], idx2 = P.inv_dx[2];
+    float cx = P.n_cam[0], cy = P.n_cam[1], cz = P.n_cam[2];
+    float ch_lo = P.ch_lo, ch_inv_w = P.ch_inv_w, ch_safe = P.ch_safe;
+    if constexpr (!kEsc) {
+        asm volatile("" : "+v"(a), "+v"(thd), "+v"(dx0), "+v"(dx1), "+v"(dx2), "+v"(idx0), "+v"(idx1), "+v"(idx2));
+        asm volatile("" : "+v"(cx), "+v"(cy), "+v"(cz), "+v"(ch_lo), "+v"(ch_inv_w), "+v"(ch_safe));
+    }
 
     // lane state
     float sc = 1.0f, isc = 1.0f, ac = a, thdc = thd;  // cell temperature (kProf 3, 4)
     float sac = a, tv = 0.0f;  // continuum (kProf 4): the sampler node's damping, upper Voigt weight
     int toff = 0, voff = 0;
-    bool have = false, done = false;
+    // kLive, kNeed (a packet), kDone (the pool is empty), or above kLive: retiring
+    // with outcome state - kLive (1 escaped, 2 destroyed, 3 stuck)
+    constexpr int kDone = -1, kNeed = 0, kLive = 1;
+    int state = kNeed;
     uint64_t pid = 0;
     PhiloxPacket pk{};
     int ci = 0, cj = 0, ck = 0, cell = 0;
@@ -545,25 +559,31 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     uint32_t seg = 0;  // plain scatterings of the packet in this launch (park mode)
     bool pend = false;   // fused mode: a qualifying scattering waits for its wave's next call batch
     uint32_t pwait = 0;  // ... for this many loop iterations so far
-    int outcome = 0;  // 1 escaped, 2 destroyed, 3 stuck
     int64_t jacc = 0;
     int64_t c_mlp = 0, c_skip = 0, c_drop = 0;  // network calls
     const float jscale = P.jbar_scale * kInvSqrtPiF;
+    const bool emis_on = P.emis_raw != nullptr, jbar_on = P.jbar_raw != nullptr;
     const bool destroys = P.eps != nullptr || P.kabs != nullptr;  // uniform
     const uint32_t max_events = (uint32_t)P.max_events;
     auto count = [&](int slot, uint64_t v) __attribute__((always_inline)) { atomicAdd(&lcnt[slot], (unsigned long long)v); };
 
     // entering a cell: its fields, and with temperature classes or a continuum
     // of widths its frequency scale, damping, sampler threshold and table set
-    auto enter_cell = [&]() __attribute__((always_inline)) {
-        const ColdParams C = cold_params();
-        k0c = C->k0[cell];
-        if (C->vx) { vxc = C->vx[cell]; vyc = C->vy[cell]; vzc = C->vz[cell]; }
-        if (C->eps) epsc = C->eps[cell];
-        if (C->kabs) kabsc = C->kabs[cell];
+    struct CellFields {
+        const float *k0, *vx, *vy, *vz, *eps, *kabs;
+        __device__ __forceinline__ void load(ColdParams C) {
+            k0 = C->k0; vx = C->vx; vy = C->vy; vz = C->vz; eps = C->eps; kabs = C->kabs;
+            asm volatile("" : "+s"(k0), "+s"(vx), "+s"(vy), "+s"(vz), "+s"(eps), "+s"(kabs));
+        }
+    };
+    auto enter_cell = [&](const CellFields &F) __attribute__((always_inline)) {
+        k0c = F.k0[cell];
+        if (F.vx) { vxc = F.vx[cell]; vyc = F.vy[cell]; vzc = F.vz[cell]; }
+        if (F.eps) epsc = F.eps[cell];
+        if (F.kabs) kabsc = F.kabs[cell];
         if constexpr (kProf == 3) {
-            const int k = C->tclass[cell];
-            const float4 cp = C->cls_par[k];
+            const int k = P.tclass[cell];
+            const float4 cp = P.cls_par[k];
             sc = cp.x; ac = cp.y; thdc = cp.z; isc = cp.w;
             sac = ac;
             toff = k * kTabFloats;
@@ -596,67 +616,69 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     };
     auto flush_emis = [&]() __attribute__((always_inline)) {
         const ColdParams C = cold_params();
-        if (C->emis_raw) E.flush(C->emis_raw + (int64_t)cell * C->emis_nch, C->emis_frac_bits);
+        E.flush(C->emis_raw + (int64_t)cell * C->emis_nch, C->emis_frac_bits);
     };
     auto flush_jbar = [&]() __attribute__((always_inline)) {
         if (jacc != 0) { tally_add_i64(cold_params()->jbar_raw + cell, jacc); jacc = 0; }
     };
     auto give_up = [&]() __attribute__((always_inline)) {
         atomicOr(cold_params()->status, (uint32_t)KRT_ST_STUCK_BIT);
-        outcome = 3;
-        have = false;
+        state = kLive + 3;
     };
 
-    // one flight segment of a live lane: to the next interaction (scat = true,
-    // or destruction) or across one cell face (escape / periodic wrap / next cell)
-    auto flight = [&](float xc, auto ue, bool &scat) __attribute__((always_inline)) {
-#pragma clang fp contract(off)
+    // the table entries a lane's gas-frame frequency selects, read together: the
+    // sampler's wait for the flight's opacity costs it nothing then
+    struct Lookup {
         float H;
-        if constexpr (kProf == 2) H = voigt_analytic(a, P.voigt_u0, fabsf(xc));
-        else if constexpr (kProf == 4) H = cont_voigt(P, voff, tv, fabsf(xc));
-        else H = voigt_lds((kProf == 3) ? P.cls_tab + toff : T, fabsf(xc));
+        UparMass m;
+    };
+    auto look_up = [&](float xc) __attribute__((always_inline)) {
+        Lookup q;
+        q.m = upar_mass(kTemp ? ((kProf == 4) ? P.cs_tab : P.cls_tab) + toff : T, fabsf(xc));
+        if constexpr (kProf == 2) q.H = voigt_analytic(a, P.voigt_u0, fabsf(xc));
+        else if constexpr (kProf == 4) q.H = cont_voigt(P, voff, tv, fabsf(xc));
+        else q.H = voigt_lds((kProf == 3) ? P.cls_tab + toff : T, fabsf(xc));
+        return q;
+    };
+
+    // one flight segment of a live lane: to the next interaction (returns true
+    // if it scatters) or across one cell face (escape / periodic wrap / next cell)
+    auto flight = [&](float H, auto ue) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
         H = (k0c > 0.0f) ? H : 0.0f;
         // line opacity plus the cell's grey absorption (exactly k0 H without one)
         const float kap = fmaf(k0c, H, kabsc);
-        const float tx = face_dist(nx, fx, P.dx[0]), ty = face_dist(ny, fy, P.dx[1]), tz = face_dist(nz, fz, P.dx[2]);
+        const float tx = face_dist(nx, fx, dx0), ty = face_dist(ny, fy, dx1), tz = face_dist(nz, fz, dx2);
         const float tm = fminf(fminf(tx, ty), tz);
-        const bool ax0 = tx == tm, ax1 = !ax0 && ty == tm;  // ties go to the lower axis
         const float dmin = fmaxf(tm, 0.0f);
         const float dtau = kap * dmin;
         const bool hit = kap > 0.0f && dtau >= tau;  // interaction inside the cell
         const float l = hit ? tau * f_rcp(kap) : dmin;
-        fx = fminf(fmaxf(fmaf(l * nx, P.inv_dx[0], fx), 0.0f), 1.0f);
-        fy = fminf(fmaxf(fmaf(l * ny, P.inv_dx[1], fy), 0.0f), 1.0f);
-        fz = fminf(fmaxf(fmaf(l * nz, P.inv_dx[2], fz), 0.0f), 1.0f);
-        if (P.jbar_raw) {
+        fx = fminf(fmaxf(fmaf(l * nx, idx0, fx), 0.0f), 1.0f);
+        fy = fminf(fmaxf(fmaf(l * ny, idx1, fy), 0.0f), 1.0f);
+        fz = fminf(fmaxf(fmaf(l * nz, idx2, fz), 0.0f), 1.0f);
+        if (jbar_on) {
             asm volatile("");  // a branch: not computed and dropped by every run without the tally
             jacc += (int64_t)__float2ll_rn(l * H * jscale);
         }
-        scat = hit;
-        if (hit) {
-            // an absorption with probability p_d = kabs / kap, else a line scattering
-            // destroyed with probability eps: one uniform decides both
-            if (destroys) {
-                const float pd = (kabsc > 0.0f) ? kabsc * f_rcp(kap) : 0.0f;
-                if (ue() < fmaf(1.0f - pd, epsc, pd)) {
-                    scat = false;
-                    outcome = 2;
-                    have = false;
-                }
-            }
-        } else {
+        bool scat = hit;
+        if (!hit) {
+            // every parameter of the crossing at once: one wait instead of one at each use
+            const ColdParams C = cold_params();
+            const int gn0 = C->n[0], gn1 = C->n[1], gn2 = C->n[2], b0 = C->bc[0], b1 = C->bc[1], b2 = C->bc[2];
+            CellFields F;
+            F.load(C);
             tau -= dtau;
             ncross_pkt += 1;
             // leaving the cell: flush its tallies
-            flush_jbar();
-            flush_emis();
-            const ColdParams C = cold_params();
-            const int gn0 = C->n[0], gn1 = C->n[1], gn2 = C->n[2];
+            if (jbar_on) flush_jbar();
+            if (emis_on) flush_emis();
+            const bool ax0 = tx == tm, ax1 = !ax0 && ty == tm;  // ties go to the lower axis
             const float na = by_axis(ax0, ax1, nx, ny, nz);
             const int st = na > 0.0f ? 1 : -1;
             const float fn = na > 0.0f ? 0.0f : 1.0f;
             const int na_n = by_axis(ax0, ax1, gn0, gn1, gn2);
-            const bool periodic = by_axis(ax0, ax1, C->bc[0], C->bc[1], C->bc[2]) != 0;
+            const bool periodic = by_axis(ax0, ax1, b0, b1, b2) != 0;
             int c = by_axis(ax0, ax1, ci, cj, ck) + st;
             const bool out = (unsigned)c >= (unsigned)na_n;
             c = out ? (st > 0 ? 0 : na_n - 1) : c;  // the wrapped cell of a periodic axis
@@ -667,8 +689,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 const int b = bin_index(x, sedges, C->spec_nb, C->spec_inv_w);
                 if (b < 0) atomicOr(C->status, (uint32_t)KRT_ST_NAN_BIT);
                 else atomicAdd(reinterpret_cast<unsigned long long *>(C->spec_raw + b), 1ull);
-                outcome = 1;
-                have = false;
+                state = kLive + 1;
             } else if (ncross_pkt > kMaxCrossings) {
                 give_up();
             } else {
@@ -676,18 +697,27 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 cj = ax1 ? c : cj;
                 ck = (ax0 || ax1) ? ck : c;
                 cell = (ck * gn1 + cj) * gn0 + ci;
-                enter_cell();
+                enter_cell(F);
+            }
+        } else if (destroys) {
+            // an absorption with probability p_d = kabs / kap, else a line scattering
+            // destroyed with probability eps: one uniform decides both
+            const float pd = (kabsc > 0.0f) ? kabsc * f_rcp(kap) : 0.0f;
+            if (ue() < fmaf(1.0f - pd, epsc, pd)) {
+                scat = false;
+                state = kLive + 2;
             }
         }
+        return scat;
     };
 
     // the resonant scattering of a live lane at gas-frame frequency xc with its
     // event's draws (eq. riia-scatter), and its emissivity tally
-    auto scatter = [&](float xc, float r1, float r2, const SDraws &b) __attribute__((always_inline)) {
+    auto scatter = [&](float xc, const UparMass &m, float r1, float r2, const SDraws &b) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
         const float up1 = b.up1, up2 = b.up2, g = b.g, sg = b.sg, cp = b.cp, sp = b.sp;
-        const float upar = kTemp ? upar_lds(((kProf == 4) ? P.cs_tab : P.cls_tab) + toff, xc, sac, thdc, r1, r2)
-                                 : upar_lds(T, xc, a, thd, r1, r2);
+        const float upar = kTemp ? upar_from(((kProf == 4) ? P.cs_tab : P.cls_tab) + toff, m, xc, sac, thdc, r1, r2)
+                                 : upar_from(T, m, xc, a, thd, r1, r2);
         // orthonormal basis about n (Duff et al. 2017)
         const float sgn = copysignf(1.0f, nz);
         const float A_ = -f_rcp(sgn + nz);
@@ -700,25 +730,22 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         ox *= rn; oy *= rn; oz *= rn;
         float xo = fmaf(sg, fmaf(up1, cp, up2 * sp), fmaf(upar, g - 1.0f, xc));
         if constexpr (kTemp) xo *= isc;  // back to reference units
-        if (P.emis_raw) {
-            const float cx = P.n_cam[0], cy = P.n_cam[1], cz = P.n_cam[2];
+        if (emis_on) {
             const float gc = dot3(nx, cx, ny, cy, nz, cz);
             const float upc = fmaf(up1, dot3(e1x, cx, e1y, cy, e1z, cz), up2 * dot3(e2x, cx, e2y, cy, e2z, cz));
             float xcam = fmaf(upar, gc - 1.0f, xc) + upc;
             const float vc = dot3(cx, vxc, cy, vyc, cz, vzc);
             xcam = kTemp ? fmaf(xcam, isc, vc) : xcam + vc;
-            const int ch = channel_of(xcam, cedges, P.emis_nch, P.ch_inv_w, P.ch_lo, P.ch_safe);
-            if ((unsigned)ch < (unsigned)P.emis_nch) {
-                int64_t wq = 0;
-                if constexpr (kDip) {
-                    // contributions below 2^32 (F <= 30) convert through 32 bits
-                    const float wf = 0.75f * fmaf(gc, gc, 1.0f) * P.frac_scale;
-                    wq = P.emis_w32 ? (int64_t)__float2uint_rn(wf) : (int64_t)__float2ll_rn(wf);
-                }
-                E.add(ch, wq, flush_emis);
-            } else {
-                ndrop += 1;
+            const int ch = channel_of(xcam, cedges, P.emis_nch, ch_inv_w, ch_lo, ch_safe);
+            const bool in = (unsigned)ch < (unsigned)P.emis_nch;
+            int64_t wq = 0;
+            if constexpr (kDip) {
+                // contributions below 2^32 (F <= 30) convert through 32 bits
+                const float wf = 0.75f * fmaf(gc, gc, 1.0f) * P.frac_scale;
+                wq = P.emis_w32 ? (int64_t)__float2uint_rn(wf) : (int64_t)__float2ll_rn(wf);
             }
+            E.add(in, ch, wq, flush_emis);
+            ndrop += in ? 0u : 1u;
         }
         nx = ox; ny = oy; nz = oz;
         x = fmaf(vzc, nz, fmaf(vyc, ny, fmaf(vxc, nx, xo)));
@@ -727,8 +754,9 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
 
     // a retired packet: write back the tallies of its last cell, count and log it
     auto retire = [&]() __attribute__((always_inline)) {
-        flush_jbar();
-        flush_emis();
+        const int outcome = state - kLive;
+        if (jbar_on) flush_jbar();
+        if (emis_on) flush_emis();
         count(outcome - 1, 1);
         count(kLcScat, nscat_pkt);
         count(kLcCross, ncross_pkt);
@@ -740,7 +768,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             L[3] = nx; L[4] = ny; L[5] = nz;
             L[6] = (float)cell; L[7] = (float)ev;
         }
-        outcome = 0;
+        state = kNeed;
     };
 
     // park mode: lanes with a qualifying scattering (kind 1), or past their
@@ -756,8 +784,8 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         if (lane == leader) base = atomicAdd(P.park_count, (unsigned long long)__popcll(pm));
         base = __shfl(base, leader, 64);
         if (want) {
-            flush_jbar();
-            flush_emis();
+            if (jbar_on) flush_jbar();
+            if (emis_on) flush_emis();
             if (ndrop) { count(kLcDrop, ndrop); ndrop = 0; }
             const uint64_t slot = base + (uint64_t)__popcll(pm & lanemask_lt);
             if (slot < P.park_cap) {
@@ -772,7 +800,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 count(kLcScat, nscat_pkt);
                 count(kLcCross, ncross_pkt);
             }
-            have = false;
+            state = kNeed;
             scat = false;
         }
     };
@@ -796,14 +824,14 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     bool tail = false;
     for (;;) {
         // ---- refill retired lanes from the global queue -------------------
-        bool need = !have && !done;
+        bool need = state == kNeed;
         uint64_t need_mask = __ballot(need);
         if (need_mask) {
             unsigned long long base = 0;
             if (first) {
                 base = wave * (uint64_t)P.first_lanes;
                 first = false;
-                if (lane >= P.first_lanes) { done = true; need = false; }
+                if (lane >= P.first_lanes) { state = kDone; need = false; }
             } else {
                 const int leader = __ffsll((long long)need_mask) - 1;
                 if (lane == leader) base = n_first + atomicAdd(P.work_counter, (unsigned long long)__popcll(need_mask));
@@ -812,13 +840,15 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             uint64_t idx = 0;
             if (need) {
                 idx = base + (uint64_t)__popcll(need_mask & lanemask_lt);
-                if (idx >= n_work) { done = true; need = false; }
+                if (idx >= n_work) { state = kDone; need = false; }
             }
             const bool fresh_pkt = need && idx >= P.n_res;
             const uint64_t fm = __ballot(fresh_pkt);
             if (fm && lane == __ffsll((long long)fm) - 1) count(kLcEmit, (uint64_t)__popcll(fm));
             if (need) {
                 const ColdParams C = cold_params();
+                CellFields F;
+                F.load(C);
                 if (!fresh_pkt) {
                     // ---- a packet back from a network call: its next event ----
                     const uint4 *r = C->res_in + kParkQuads * idx;
@@ -832,7 +862,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                     nx = __uint_as_float(r2.x); ny = __uint_as_float(r2.y); nz = __uint_as_float(r2.z);
                     nscat_pkt = r2.w;
                     ncross_pkt = r3.x;
-                    enter_cell();
+                    enter_cell(F);
                 } else {
                     // ---- emission (event 0) ----------------------------------
                     pid = C->packet_offset + C->new_lo + (idx - C->n_res);
@@ -877,7 +907,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                         fx = f3[0]; fy = f3[1]; fz = f3[2];
                         cell = (ck * C->n[1] + cj) * C->n[0] + ci;
                     }
-                    enter_cell();
+                    enter_cell(F);
                     float xg = C->src_x0;
                     if (C->src_profile != KRT_PROF_DELTA_I) {
                         uint4 e2 = philox(make_uint4(0u, plo, phi, 2u), C->key0, C->key1);
@@ -898,27 +928,28 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 pk = philox_packet((uint32_t)pid, (uint32_t)(pid >> 32), P.key0, P.key1);
                 seg = 0;
                 jacc = 0;
-                have = true;
+                state = kLive;
                 next_event(draw_event);
             }
         }
-        const uint64_t live_mask = __ballot(have);
         // (a packet resumed past its last event is neither live nor done: it retires below)
-        if (live_mask == 0ull && __ballot(!done) == 0ull) break;
+        if (__ballot(state != kDone) == 0ull) break;
         // pool exhausted and few live lanes: continue in tail mode
-        if (!kEsc && P.tail_lanes > 0 && __ballot(done) != 0ull && __popcll(live_mask) <= P.tail_lanes) {
+        if (!kEsc && P.tail_lanes > 0 && __ballot(state == kDone) != 0ull &&
+            __popcll(__ballot(state == kLive)) <= P.tail_lanes) {
             tail = true;
             break;
         }
         if (++ticks == kEmisTicks) {
             ticks = 0;
-            flush_emis();
+            if (emis_on) flush_emis();
         }
 
         // ---- one flight segment (divergent) --------------------------------
         bool scat = false;
         const float xc = gas_freq();
-        if (have && !pend) flight(xc, [&]() __attribute__((always_inline)) { return u01(wa1); }, scat);
+        const Lookup tl = look_up(xc);
+        if (state == kLive && !pend) scat = flight(tl.H, [&]() __attribute__((always_inline)) { return u01(wa1); });
 
         // ---- learned whole-cell escape ---------------------------------------
         // At a scattering inside a thick cubic cell, at least esc_depth_min below
@@ -944,9 +975,9 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             // While the pool lasts and nothing forces the batch, it takes whole
             // 16-sample blocks only: the askers past them, in lane order, stay held.
             const uint64_t wm = __ballot(mlp);
-            const bool tailw = __ballot(done) != 0ull;
+            const bool tailw = __ballot(state == kDone) != 0ull;
             const int need_lanes = tailw ? P.esc_tail_lanes : P.esc_min_lanes;
-            const bool forced = wm == __ballot(have) || __ballot(pend && pwait >= P.esc_wait) != 0ull;
+            const bool forced = wm == __ballot(state == kLive) || __ballot(pend && pwait >= P.esc_wait) != 0ull;
             go = wm != 0ull && (__popcll(wm) >= need_lanes || forced);  // wave-uniform
             bool held = !go;
             if (go && !tailw && !forced && P.esc_wait > 0 && mlp && __popcll(wm) >= 16)
@@ -965,7 +996,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         if (walk) {
             SDraws b;
             scatter_draws(wb, kDip, b);
-            scatter(xc, u01(wa2), u01(wa3), b);
+            scatter(xc, tl.m, u01(wa2), u01(wa3), b);
             if constexpr (!kEsc && !kPark) next_event(draw_event);
         }
         if (kPark) {
@@ -1006,7 +1037,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             // an event is consumed by a walked scattering or a call; a held one waits
             if (walk || mlp) next_event(draw_event);
         }
-        if (!have && outcome != 0) retire();
+        if (state > kLive) retire();
     }
     // ---- tail mode ------------------------------------------------------------
     // The packet pool is exhausted and at most tail_lanes lanes are live, so the
@@ -1025,6 +1056,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         SDraws pb;
         pb.up1 = pb.up2 = pb.g = pb.sg = pb.cp = pb.sp = 0.f;
         for (;;) {
+            const bool have = state == kLive;
             const uint64_t live = __ballot(have);
             if (live == 0ull) break;
             if (live != bank_live || __ballot(have && ev == ev1) != 0ull) {
@@ -1058,11 +1090,12 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             if (have && fresh) { tau = dt; fresh = false; }
             if (++ticks == kEmisTicks) {
                 ticks = 0;
-                flush_emis();
+                if (emis_on) flush_emis();
             }
             bool scat = false;
             const float xc = gas_freq();
-            if (have) flight(xc, [&]() __attribute__((always_inline)) { return due; }, scat);
+            const Lookup tl = look_up(xc);
+            if (have) scat = flight(tl.H, [&]() __attribute__((always_inline)) { return due; });
             bool called = false;
             if (kPark) {
                 CellFrame CF{};
@@ -1070,13 +1103,13 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 called = scat && call_eligible(P, k0c, fx, fy, fz, xc, CF, ltc, ldep);
             }
             bool walk = scat && !called;
-            if (walk) scatter(xc, dr1, dr2, db);
+            if (walk) scatter(xc, tl.m, dr1, dr2, db);
             if (kPark) {
                 const bool cont = walk && ++seg >= P.park_budget;
                 park(called || cont, walk, xc, called ? 1u : 0u);
             }
             if (walk) next_event([&]() __attribute__((always_inline)) { fresh = true; });
-            if (!have && outcome != 0) retire();
+            if (state > kLive) retire();
         }
     }
 
