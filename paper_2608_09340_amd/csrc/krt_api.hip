@@ -246,15 +246,15 @@ bool valid_bins(int nb, double lo, double hi) {
     return nb > 0 && nb < (1 << 24) && std::isfinite(lo) && std::isfinite(hi) && hi > lo;
 }
 
-// channel_of's margin: half a channel less a bound on how far, in channels, the
-// guess (x - lo) inv_w in binary32 and the rounded edges can be from the exact
-// position: one rounding each of the edges, of lo and of x - lo (units of
-// 2^-24 of the largest of them), and two of the product, doubled.  Channels so
-// narrow that the margin vanishes always go by their edges.
+// channel_guess's margin: half a channel less a bound on how far, in channels, its
+// guess fma(x, 1 / w, -lo / w) in binary32 and the rounded edges can be from the
+// exact position.  Inside the channels |x| is at most the larger end, `big`;
+// rounding adds at most 2^-24 each of big / w for 1 / w, of it for lo / w, of nb
+// for the sum, and of big / w for an edge; doubled.  Channels so narrow that the
+// margin vanishes always go by their edges.
 float channel_safe(int nb, double lo, double hi) {
     const double inv_w = nb / (hi - lo), big = std::max(std::fabs(lo), std::fabs(hi));
-    const double tol = 2.0 * std::ldexp(1.0, -24) * (inv_w * (3.0 * big + (hi - lo)) + 3.0 * nb);
-    return (float)std::max(0.0, 0.5 - tol);
+    return (float)std::max(0.0, 0.5 - 2.0 * std::ldexp(1.0, -24) * (4.0 * inv_w * big + 2.0 * nb));
 }
 
 // binary32 bin edges lo + (hi - lo) k / nb, k = 0..nb, evaluated in FP64
@@ -677,7 +677,7 @@ static int mc_run_impl(krt_ctx *c, uint64_t n_packets, uint64_t seed, const krt_
     P.phase = c->lines[l].phase;
     P.source = o->source;
     P.src_profile = o->src_profile;
-    P.src_x0 = (float)o->src_x0;
+    P.src_x0 = (float)o->src_x0 + 0.0f;  // -0 as 0: the sampler takes the sign of the frequency
     if (noalloc) {
         // the pinned block is reused only after this call's stream synchronisation
         float *e = c->host_edges;
@@ -698,7 +698,7 @@ static int mc_run_impl(krt_ctx *c, uint64_t n_packets, uint64_t seed, const krt_
     P.ch_inv_w = o->emis_nch > 0 ? (float)(o->emis_nch / (o->ch_hi - o->ch_lo)) : 0.0f;
     P.ch_edges = edges + kMaxSpecBins + 1;
     if (o->emis_nch > 0) {
-        P.ch_lo = (float)o->ch_lo;
+        P.ch_off = (float)(-o->ch_lo * (o->emis_nch / (o->ch_hi - o->ch_lo)));
         P.ch_safe = channel_safe(o->emis_nch, o->ch_lo, o->ch_hi);
     }
     P.frac_scale = std::ldexp(1.0f, fb);

@@ -95,6 +95,12 @@ __device__ __forceinline__ float f_rsq(float x) { return __builtin_amdgcn_rsqf(x
 __device__ __forceinline__ float sin_rev(float r) { return __builtin_amdgcn_sinf(r); }
 __device__ __forceinline__ float cos_rev(float r) { return __builtin_amdgcn_cosf(r); }
 
+// a or b, both evaluated: where lanes differ a branch costs more than either
+template <class V>
+__device__ __forceinline__ V sel(bool c, V a, V b) {
+    return __builtin_unpredictable(c) ? a : b;
+}
+
 // ------------------------------------------------------------------- bins ---
 // Index rule shared by every tally: edges[k] (k = 0..nb) are the binary32 values
 // of lo + (hi - lo) * k / nb computed in FP64 on the host; the bin is 1 + the
@@ -113,32 +119,47 @@ __device__ __forceinline__ int bin_index(float x, const float *edges, int nb, fl
     return k + 1;
 }
 
-// The channel k (0 <= k < nb) that bin_index puts x in, or a number outside
-// [0, nb).  The guess floor((x - lo) / width) is the answer unless x is within
-// rounding of an edge: `safe` is one half less the bound on that rounding in
-// widths (channel_safe), so a guess whose fraction is nearer than that to one half
-// needs no look at the edges.
-__device__ __forceinline__ int channel_of(float x, const float *edges, int nb, float inv_w, float lo, float safe) {
-    const float t = (x - lo) * inv_w;
+// The channel k (0 <= k < nb) that bin_index puts x in is floor(x / width - lo /
+// width) unless x is within rounding of an edge.  Returns that guess and sets
+// `sure` if its fraction is nearer to one half than `safe`, one half less the
+// bound on the rounding in widths; else the edges decide (bin_index, less one).
+// off: -lo / width.
+__device__ __forceinline__ int channel_guess(float x, float inv_w, float off, float safe, bool &sure) {
+    const float t = fmaf(x, inv_w, off);
     const float fl = floorf(t);
-    int k = (int)fl;
-    if (!(fabsf((t - fl) - 0.5f) < safe)) k = bin_index(x, edges, nb, inv_w) - 1;
-    return k;
+    sure = fabsf((t - fl) - 0.5f) < safe;
+    return (int)fl;
 }
 
 // ----------------------------------------------------------- LDS lookups ---
-// H(a, |x|): the core and wing pieces share one address and one read
-__device__ __forceinline__ float voigt_lds(const float *T, float xa) {
+// The entry of |x| in the Voigt table: its core and wing pieces share one address
+// and one read.  (int) of a float that may be NaN is 0 here, and none of the
+// indices below can be negative, so only the upper ends are clamped.
+struct VoigtEntry {
+    float4 c;
+    float f, w;   // position in the interval, 8 / |x|
+    int row;      // of 4 floats: core 0 .. 511, wing 512 .. 639
+};
+__device__ __forceinline__ VoigtEntry voigt_entry(const float *T, float xa) {
 #pragma clang fp contract(off)
+    static_assert(kOffVoigtCore == 0 && kOffVoigtWing == 4 * kVoigtCoreN, "the wing follows the core");
     const bool core = xa < 8.0f;
-    const float w = 8.0f * f_rcp(xa);
-    const float t = core ? xa * 64.0f : w * (float)kVoigtWingN;
-    const int i = max(0, min((int)t, core ? kVoigtCoreN - 1 : kVoigtWingN - 1));
-    const float f = t - (float)i;
-    const float4 c = *reinterpret_cast<const float4 *>(T + (core ? kOffVoigtCore : kOffVoigtWing) + 4 * i);
-    const float G = fmaf(f, fmaf(f, fmaf(f, c.w, c.z), c.y), c.x);
-    return core ? G : G * w * w * (1.0f / 64.0f);
+    VoigtEntry e;
+    e.w = 8.0f * f_rcp(xa);
+    const float t = sel(core, xa * 64.0f, e.w * (float)kVoigtWingN);
+    const int i = min((int)t, sel(core, kVoigtCoreN - 1, kVoigtWingN - 1));
+    e.row = i + sel(core, 0, kVoigtCoreN);
+    e.f = t - (float)i;
+    e.c = *reinterpret_cast<const float4 *>(T + 4 * e.row);
+    return e;
 }
+__device__ __forceinline__ float voigt_value(const VoigtEntry &e, float xa) {
+#pragma clang fp contract(off)
+    const float G = fmaf(e.f, fmaf(e.f, fmaf(e.f, e.c.w, e.c.z), e.c.y), e.c.x);
+    return sel(xa < 8.0f, G, G * e.w * e.w * (1.0f / 64.0f));
+}
+// H(a, |x|)
+__device__ __forceinline__ float voigt_lds(const float *T, float xa) { return voigt_value(voigt_entry(T, xa), xa); }
 
 // Analytic approximation of H(a, u) that blends the Doppler core exp(-u^2) and
 // the damping wing a / (sqrt(pi) (u^2 + a^2)) with the switch
@@ -162,39 +183,48 @@ struct UparMass {
     float4 m0, m1;
     float fm;
 };
-__device__ __forceinline__ UparMass upar_mass(const float *T, float xa) {
-#pragma clang fp contract(off)
-    const float pm = xa * (float)(kMassN / 8);
-    const int im = max(0, min((int)pm, kMassN - 1));
+// Its grid is the Voigt core's, so the Voigt entry gives row and position
+// (beyond |x| = 8 what is read is not used).
+__device__ __forceinline__ UparMass upar_mass(const float *T, const VoigtEntry &e) {
+    static_assert(kMassN == kVoigtCoreN && kOffMass + 4 * (kVoigtCoreN + kVoigtWingN) + 4 <= kTabFloats,
+                  "one grid, and the wing's rows stay inside the table block");
     UparMass q;
-    q.fm = pm - (float)im;
-    q.m0 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im);
-    q.m1 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * im + 4);
+    q.fm = e.f;
+    q.m0 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * e.row);
+    q.m1 = *reinterpret_cast<const float4 *>(T + kOffMass + 4 * e.row + 4);
     return q;
 }
+// the wing pieces' quantile coordinate: nodes at q = 4 xi^3 (xi < 1/2),
+// 1 - 4 (1 - xi)^3 (xi >= 1/2)
+__device__ __forceinline__ float wing_level(float r2) {
+#pragma clang fp contract(off)
+    const bool lo = r2 < 0.5f;
+    const float cb = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(0.25f * sel(lo, r2, 1.0f - r2)) * (1.0f / 3.0f));
+    return sel(lo, cb, 1.0f - cb);
+}
+// xw: wing_level(r2)
 __device__ __forceinline__ float upar_from(const float *T, const UparMass &q, float x, float a, float thd, float r1,
-                                           float r2) {
+                                           float r2, float xw) {
 #pragma clang fp contract(off)
     const float xa = fabsf(x);
     const bool lin = xa < 8.0f;
-    // beyond the table every draw is the bump's
-    const float c1 = lin ? fmaf(q.fm, q.m1.x - q.m0.x, q.m0.x) : 0.0f;
-    const float c2 = lin ? fmaf(q.fm, q.m1.y - q.m0.y, q.m0.y) : 0.0f;
-    const float c3 = lin ? fmaf(q.fm, q.m1.z - q.m0.z, q.m0.z) : 1.0f;
-    const float p = __builtin_unpredictable(lin) ? xa * 6.0f : fminf(fmaf(f_log(xa * 0.125f), kRowInvLog, 48.0f), 63.0f);
-    const int j = max(0, min((int)p, kRows - 2));
+    const float c1 = fmaf(q.fm, q.m1.x - q.m0.x, q.m0.x);
+    const float c2 = fmaf(q.fm, q.m1.y - q.m0.y, q.m0.y);
+    const float c3 = fmaf(q.fm, q.m1.z - q.m0.z, q.m0.z);
+    // the first that holds names the piece; beyond the table every draw is the bump's
+    const bool spike = lin & (r1 < c1), l1 = lin & (r1 < c2), l2 = !lin | (r1 < c3);
+    const float p = sel(lin, xa * 6.0f, fminf(fmaf(f_log(xa * 0.125f), kRowInvLog, 48.0f), 63.0f));
+    const int j = min((int)p, kRows - 2);
     const float fr = p - (float)j;
-    const bool spike = r1 < c1, l1 = r1 < c2, l2 = r1 < c3;  // the first that holds names the piece
-    const int off = spike ? kOffSpike : (l1 ? kOffL1 : (l2 ? kOffL2 : kOffRight));
-    // wing pieces: nodes at q = 4 xi^3 (xi < 1/2), 1 - 4 (1 - xi)^3 (xi >= 1/2)
-    const bool lo = r2 < 0.5f;
-    const float cb = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(0.25f * (lo ? r2 : 1.0f - r2)) * (1.0f / 3.0f));
-    const float xi = __builtin_unpredictable(spike) ? r2 : (lo ? cb : 1.0f - cb);
-    const float nq1 = spike ? (float)(kQS - 1) : (float)(kQL1 - 1);  // kQL1 == kQL2 == kQR
-    const int k = max(0, min((int)(xi * nq1), spike ? kQS - 2 : kQL1 - 2));
+    const int off = sel(spike, kOffSpike, sel(l1, kOffL1, sel(l2, kOffL2, kOffRight)));
+    const float xi = sel(spike, r2, xw);
+    int nq = sel(spike, kQS, kQL1);  // kQL1 == kQL2 == kQR
+    asm("" : "+v"(nq));              // one multiply-add below, not the shifts of a known power of two
+    const float nq1 = sel(spike, (float)(kQS - 1), (float)(kQL1 - 1));
+    const int k = min((int)(xi * nq1), nq - 2);
     const float fq = fmaf(xi, nq1, -(float)k);
-    const float *r0 = T + off + (spike ? j * kQS : j * kQL1) + k;
-    const float *rn = r0 + (spike ? kQS : kQL1);
+    const float *r0 = T + ((int)__umul24((unsigned)j, (unsigned)nq) + off + k);
+    const float *rn = r0 + nq;
     const float v0 = fmaf(fq, r0[1] - r0[0], r0[0]);
     const float v1 = fmaf(fq, rn[1] - rn[0], rn[0]);
     const float v = fmaf(fr, v1 - v0, v0);
@@ -202,13 +232,14 @@ __device__ __forceinline__ float upar_from(const float *T, const UparMass &q, fl
     const float th = v * thd * (1.0f / (2.0f * kPiF));
     const float us = fmaf(a * sin_rev(th), f_rcp(cos_rev(th)), xa);
     const float s = (float)kDelta * f_exp(v);
-    const float uw = xa + (l1 ? -s : s);
-    const float u = spike ? us : ((l2 && !l1) ? v : uw);
-    return (x < 0.0f) ? -u : u;  // p(u | -x) = p(-u | x)
+    const float uw = xa + sel(l1, -s, s);
+    const float u = sel(spike, us, sel(l2 & !l1, v, uw));
+    // p(u | -x) = p(-u | x): u takes the sign of x
+    return __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(u), __float_as_uint(x), 0x80000000u, 0x78));
 }
 
 __device__ __forceinline__ float upar_lds(const float *T, float x, float a, float thd, float r1, float r2) {
-    return upar_from(T, upar_mass(T, fabsf(x)), x, a, thd, r1, r2);
+    return upar_from(T, upar_mass(T, voigt_entry(T, fabsf(x))), x, a, thd, r1, r2, wing_level(r2));
 }
 
 // Dipole phase (3/8)(1 + g^2): g = 2 sinh(asinh(4u - 2)/3).

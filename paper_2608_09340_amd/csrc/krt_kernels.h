@@ -77,7 +77,7 @@ struct RunParams {
     float ch_inv_w;
     const float *ch_edges;    // [emis_nch + 1]
     float n_cam[3];
-    float ch_lo, ch_safe;  // channel_of: the first edge, half less the rounding of a guess in widths
+    float ch_off, ch_safe;  // channel_guess: -lo / width, half less the rounding of a guess in widths
     float frac_scale;  // 2^F, emissivity
     int emis_frac_bits;  // F
     float jbar_scale;  // 2^Fj, mean intensity

@@ -50,6 +50,7 @@ template <bool kSum>
 struct EmisWindow {
     int w = 0;            // first channel of the window
     uint64_t cnt = 0;     // 8-bit counts of channels w .. w + 7 (kSum: bit s = slot s in use)
+    int size;             // channels it spans: kEmisSlots, or all where there are fewer
     int64_t *acc;         // kSum: this thread's LDS sums
     int stride;           // ... and the distance between its slots
 
@@ -69,25 +70,22 @@ struct EmisWindow {
             }
         }
     }
-    // one scattering of weight v (kSum; 2^frac_bits otherwise) into channel ch if
-    // `in`; write_back flushes this window
-    template <class F>
-    __device__ __forceinline__ void add(bool in, int ch, int64_t v, F write_back) {
-        int d = ch - w;
-        if (in && (unsigned)d >= (unsigned)kEmisSlots) {
-            write_back();
-            w = ch - (kEmisSlots / 2 - 1);
-            d = kEmisSlots / 2 - 1;
-        }
+    // One scattering of weight v (kSum; 2^frac_bits otherwise) into channel ch,
+    // `unit` = 1, or nothing, `unit` = 0 (a lane without a packet; v is 0 too).
+    // The caller has seen that the window holds the channel (or the lane adds
+    // nothing).
+    __device__ __forceinline__ void add(int ch, uint32_t unit, int64_t v) {
+        const uint32_t d = (uint32_t)(ch - w);
         if constexpr (kSum) {
-            if (in) {
-                __hip_atomic_fetch_add(acc + d * stride, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                cnt |= 1ull << d;
-            }
+            const uint32_t s = min(d, (uint32_t)(kEmisSlots - 1));
+            __hip_atomic_fetch_add(acc + s * stride, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            cnt |= (uint64_t)(unit << s);
         } else {
-            cnt += (uint64_t)(in ? 1 : 0) << ((8 * d) & 63);
+            cnt += (uint64_t)unit << ((8 * d) & 63);
         }
     }
+    // moves the (written back) window to hold channel ch of nch
+    __device__ __forceinline__ void move(int ch, int nch) { w = max(0, min(ch - (size / 2 - 1), nch - size)); }
 };
 
 // Counters a workgroup keeps in LDS until it ends: the outcomes 1..3 of retired
@@ -408,24 +406,30 @@ __device__ __forceinline__ float cont_voigt(const RunParams &P, int voff, float 
 }
 
 // --------------------------------------------------------------- kernel ---
-// Draws of an event: the destruction uniform ue, the sampler's uniforms r1, r2,
-// the two u_perp components (Box-Muller, N(0, 1/2) each), the cosine g of the
-// scattering angle (isotropic or dipole) with sqrt(1 - g^2), and cos, sin of
-// the azimuth psi.
+// Draws of a scattering: the sampler's uniforms r1, r2 with the latter's
+// wing_level, the two u_perp components (Box-Muller, N(0, 1/2) each), the cosine
+// g of the scattering angle (isotropic or dipole) with sqrt(1 - g^2), cos, sin
+// of the azimuth psi, and the u_perp component along the outgoing direction's
+// transverse part.
 struct SDraws {
-    float up1, up2, g, sg, cp, sp;
+    float r1, r2, xw, up1, up2, g, sg, cp, sp, kick;
 };
 
-__device__ __forceinline__ void scatter_draws(uint4 B, bool dipole, SDraws &d) {
+__device__ __forceinline__ void scatter_draws(uint32_t w1, uint32_t w2, uint4 B, bool dipole, SDraws &d) {
+#pragma clang fp contract(off)
+    d.r1 = u01(w1);
+    d.r2 = u01(w2);
+    d.xw = wing_level(d.r2);
     const float rr = f_sqrt(-f_log(u01(B.x)));
     const float th = u01(B.y);
     d.up1 = rr * cos_rev(th);
     d.up2 = rr * sin_rev(th);
-    d.g = dipole ? dipole_g(u01(B.z)) : 2.0f * u01(B.z) - 1.0f;
-    d.sg = f_sqrt(fmaxf(0.0f, 1.0f - d.g * d.g));
+    d.g = dipole ? dipole_g(u01(B.z)) : fmaf(2.0f, u01(B.z), -1.0f);
+    d.sg = f_sqrt(fmaxf(0.0f, fmaf(-d.g, d.g, 1.0f)));
     const float psi = u01(B.w);
     d.cp = cos_rev(psi);
     d.sp = sin_rev(psi);
+    d.kick = fmaf(d.up1, d.cp, d.up2 * d.sp);
 }
 
 // ax bx + ay by + az bz in the one order every variant uses
@@ -438,8 +442,7 @@ __device__ __forceinline__ float dot3(float ax, float bx, float ay, float by, fl
 // lane's state in memory
 template <class V>
 __device__ __forceinline__ V by_axis(bool ax0, bool ax1, V x, V y, V z) {
-    const V yz = ax1 ? y : z;
-    return ax0 ? x : yz;
+    return sel(ax0, x, sel(ax1, y, z));
 }
 
 // Distance along one axis to the face ahead: n the direction's component, f the
@@ -447,7 +450,8 @@ __device__ __forceinline__ V by_axis(bool ax0, bool ax1, V x, V y, V z) {
 // times inf) for a packet exactly on the face; the minimum over the axes
 // ignores a NaN as it ignores +inf, and the direction has another component.
 __device__ __forceinline__ float face_dist(float n, float f, float dx) {
-    return (n > 0.0f ? 1.0f - f : f) * dx * f_rcp(fabsf(n));
+    const float up = fminf(fmaxf(n * 0x1p126f, 0.0f), 1.0f);  // 1 toward the upper face, 0 toward the lower
+    return fabsf(f - up) * dx * f_rcp(fabsf(n));
 }
 
 // kProf: 0 tables in LDS (production); 1 the same tables read from global
@@ -500,6 +504,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     unsigned long long *lcnt =
         reinterpret_cast<unsigned long long *>(lds4 + (kEsc ? kLdsMlp + kMlpFwdBytes / 4 : kTabFloats + kEdgeFloats) / 4);
     EmisWindow<kDip> E;
+    E.size = min(kEmisSlots, P.emis_nch);
     {
         const float4 *src = reinterpret_cast<const float4 *>(P.tab);
         for (int i = threadIdx.x; i < kTabFloats / 4; i += blockDim.x) lds4[i] = src[i];
@@ -531,10 +536,10 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     // values are too many, and would be loaded again, with a wait, in each
     float dx0 = P.dx[0], dx1 = P.dx[1], dx2 = P.dx[2], idx0 = P.inv_dx[0], idx1 = P.inv_dx[1], idx2 = P.inv_dx[2];
     float cx = P.n_cam[0], cy = P.n_cam[1], cz = P.n_cam[2];
-    float ch_lo = P.ch_lo, ch_inv_w = P.ch_inv_w, ch_safe = P.ch_safe;
+    float ch_off = P.ch_off, ch_inv_w = P.ch_inv_w, ch_safe = P.ch_safe;
     if constexpr (!kEsc) {
         asm volatile("" : "+v"(a), "+v"(thd), "+v"(dx0), "+v"(dx1), "+v"(dx2), "+v"(idx0), "+v"(idx1), "+v"(idx2));
-        asm volatile("" : "+v"(cx), "+v"(cy), "+v"(cz), "+v"(ch_lo), "+v"(ch_inv_w), "+v"(ch_safe));
+        asm volatile("" : "+v"(cx), "+v"(cy), "+v"(cz), "+v"(ch_off), "+v"(ch_inv_w), "+v"(ch_safe));
     }
 
     // lane state
@@ -634,26 +639,34 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     };
     auto look_up = [&](float xc) __attribute__((always_inline)) {
         Lookup q;
-        q.m = upar_mass(kTemp ? ((kProf == 4) ? P.cs_tab : P.cls_tab) + toff : T, fabsf(xc));
-        if constexpr (kProf == 2) q.H = voigt_analytic(a, P.voigt_u0, fabsf(xc));
-        else if constexpr (kProf == 4) q.H = cont_voigt(P, voff, tv, fabsf(xc));
-        else q.H = voigt_lds((kProf == 3) ? P.cls_tab + toff : T, fabsf(xc));
+        const float xa = fabsf(xc);
+        const float *TL = kTemp ? ((kProf == 4) ? P.cs_tab : P.cls_tab) + toff : T;
+        const VoigtEntry e = voigt_entry(TL, xa);
+        q.m = upar_mass(TL, e);
+        if constexpr (kProf == 2) q.H = voigt_analytic(a, P.voigt_u0, xa);
+        else if constexpr (kProf == 4) q.H = cont_voigt(P, voff, tv, xa);
+        else q.H = voigt_value(e, xa);
         return q;
     };
 
-    // one flight segment of a live lane: to the next interaction (returns true
-    // if it scatters) or across one cell face (escape / periodic wrap / next cell)
-    auto flight = [&](float H, auto ue) __attribute__((always_inline)) {
+    // one flight segment: to the next interaction, or to the face of the cell
+    struct Segment {
+        float kap, dtau, tx, ty, tm;
+        bool hit;  // an interaction inside the cell
+    };
+    auto segment = [&](float H) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
+        Segment q;
         H = (k0c > 0.0f) ? H : 0.0f;
         // line opacity plus the cell's grey absorption (exactly k0 H without one)
-        const float kap = fmaf(k0c, H, kabsc);
-        const float tx = face_dist(nx, fx, dx0), ty = face_dist(ny, fy, dx1), tz = face_dist(nz, fz, dx2);
-        const float tm = fminf(fminf(tx, ty), tz);
-        const float dmin = fmaxf(tm, 0.0f);
-        const float dtau = kap * dmin;
-        const bool hit = kap > 0.0f && dtau >= tau;  // interaction inside the cell
-        const float l = hit ? tau * f_rcp(kap) : dmin;
+        q.kap = fmaf(k0c, H, kabsc);
+        q.tx = face_dist(nx, fx, dx0);
+        q.ty = face_dist(ny, fy, dx1);
+        q.tm = fminf(fminf(q.tx, q.ty), face_dist(nz, fz, dx2));
+        const float dmin = fmaxf(q.tm, 0.0f);
+        q.dtau = q.kap * dmin;
+        q.hit = (q.kap > 0.0f) & (q.dtau >= tau);
+        const float l = sel(q.hit, tau * f_rcp(q.kap), dmin);
         fx = fminf(fmaxf(fmaf(l * nx, idx0, fx), 0.0f), 1.0f);
         fy = fminf(fmaxf(fmaf(l * ny, idx1, fy), 0.0f), 1.0f);
         fz = fminf(fmaxf(fmaf(l * nz, idx2, fz), 0.0f), 1.0f);
@@ -661,63 +674,64 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             asm volatile("");  // a branch: not computed and dropped by every run without the tally
             jacc += (int64_t)__float2ll_rn(l * H * jscale);
         }
-        bool scat = hit;
-        if (!hit) {
-            // every parameter of the crossing at once: one wait instead of one at each use
-            const ColdParams C = cold_params();
-            const int gn0 = C->n[0], gn1 = C->n[1], gn2 = C->n[2], b0 = C->bc[0], b1 = C->bc[1], b2 = C->bc[2];
-            CellFields F;
-            F.load(C);
-            tau -= dtau;
-            ncross_pkt += 1;
-            // leaving the cell: flush its tallies
-            if (jbar_on) flush_jbar();
-            if (emis_on) flush_emis();
-            const bool ax0 = tx == tm, ax1 = !ax0 && ty == tm;  // ties go to the lower axis
-            const float na = by_axis(ax0, ax1, nx, ny, nz);
-            const int st = na > 0.0f ? 1 : -1;
-            const float fn = na > 0.0f ? 0.0f : 1.0f;
-            const int na_n = by_axis(ax0, ax1, gn0, gn1, gn2);
-            const bool periodic = by_axis(ax0, ax1, b0, b1, b2) != 0;
-            int c = by_axis(ax0, ax1, ci, cj, ck) + st;
-            const bool out = (unsigned)c >= (unsigned)na_n;
-            c = out ? (st > 0 ? 0 : na_n - 1) : c;  // the wrapped cell of a periodic axis
-            fx = ax0 ? fn : fx;
-            fy = ax1 ? fn : fy;
-            fz = (ax0 || ax1) ? fz : fn;
-            if (out && !periodic) {
-                const int b = bin_index(x, sedges, C->spec_nb, C->spec_inv_w);
-                if (b < 0) atomicOr(C->status, (uint32_t)KRT_ST_NAN_BIT);
-                else atomicAdd(reinterpret_cast<unsigned long long *>(C->spec_raw + b), 1ull);
-                state = kLive + 1;
-            } else if (ncross_pkt > kMaxCrossings) {
-                give_up();
-            } else {
-                ci = ax0 ? c : ci;
-                cj = ax1 ? c : cj;
-                ck = (ax0 || ax1) ? ck : c;
-                cell = (ck * gn1 + cj) * gn0 + ci;
-                enter_cell(F);
-            }
-        } else if (destroys) {
-            // an absorption with probability p_d = kabs / kap, else a line scattering
-            // destroyed with probability eps: one uniform decides both
-            const float pd = (kabsc > 0.0f) ? kabsc * f_rcp(kap) : 0.0f;
-            if (ue() < fmaf(1.0f - pd, epsc, pd)) {
-                scat = false;
-                state = kLive + 2;
-            }
+        return q;
+    };
+    // ... which the packet crosses: escape, periodic wrap or the next cell
+    auto cross = [&](const Segment &q) __attribute__((always_inline)) {
+        // every parameter of the crossing at once: one wait instead of one at each use
+        const ColdParams C = cold_params();
+        const int gn0 = C->n[0], gn1 = C->n[1], gn2 = C->n[2], b0 = C->bc[0], b1 = C->bc[1], b2 = C->bc[2];
+        CellFields F;
+        F.load(C);
+        tau -= q.dtau;
+        ncross_pkt += 1;
+        // leaving the cell: flush its tallies
+        if (jbar_on) flush_jbar();
+        if (emis_on) flush_emis();
+        const bool ax0 = q.tx == q.tm, ax1 = !ax0 && q.ty == q.tm;  // ties go to the lower axis
+        const float na = by_axis(ax0, ax1, nx, ny, nz);
+        const int st = na > 0.0f ? 1 : -1;
+        const float fn = na > 0.0f ? 0.0f : 1.0f;
+        const int na_n = by_axis(ax0, ax1, gn0, gn1, gn2);
+        const bool periodic = by_axis(ax0, ax1, b0, b1, b2) != 0;
+        int c = by_axis(ax0, ax1, ci, cj, ck) + st;
+        const bool out = (unsigned)c >= (unsigned)na_n;
+        c = out ? (st > 0 ? 0 : na_n - 1) : c;  // the wrapped cell of a periodic axis
+        fx = ax0 ? fn : fx;
+        fy = ax1 ? fn : fy;
+        fz = (ax0 || ax1) ? fz : fn;
+        if (out && !periodic) {
+            const int b = bin_index(x, sedges, C->spec_nb, C->spec_inv_w);
+            if (b < 0) atomicOr(C->status, (uint32_t)KRT_ST_NAN_BIT);
+            else atomicAdd(reinterpret_cast<unsigned long long *>(C->spec_raw + b), 1ull);
+            state = kLive + 1;
+        } else if (ncross_pkt > kMaxCrossings) {
+            give_up();
+        } else {
+            ci = ax0 ? c : ci;
+            cj = ax1 ? c : cj;
+            ck = (ax0 || ax1) ? ck : c;
+            cell = (ck * gn1 + cj) * gn0 + ci;
+            enter_cell(F);
         }
-        return scat;
+    };
+    // an interaction is an absorption with probability p_d = kabs / kap, else a
+    // line scattering destroyed with probability eps: one uniform decides both
+    auto destroyed = [&](const Segment &q, float ue) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+        const float pd = (kabsc > 0.0f) ? kabsc * f_rcp(q.kap) : 0.0f;
+        return ue < fmaf(1.0f - pd, epsc, pd);
     };
 
     // the resonant scattering of a live lane at gas-frame frequency xc with its
     // event's draws (eq. riia-scatter), and its emissivity tally
-    auto scatter = [&](float xc, const UparMass &m, float r1, float r2, const SDraws &b) __attribute__((always_inline)) {
+    // (unit = 1; a lane without a packet may pass through with unit = 0, tallying
+    // nothing)
+    auto scatter = [&](float xc, const UparMass &m, const SDraws &b, uint32_t unit) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
         const float up1 = b.up1, up2 = b.up2, g = b.g, sg = b.sg, cp = b.cp, sp = b.sp;
-        const float upar = kTemp ? upar_from(((kProf == 4) ? P.cs_tab : P.cls_tab) + toff, m, xc, sac, thdc, r1, r2)
-                                 : upar_from(T, m, xc, a, thd, r1, r2);
+        const float upar = kTemp ? upar_from(((kProf == 4) ? P.cs_tab : P.cls_tab) + toff, m, xc, sac, thdc, b.r1, b.r2, b.xw)
+                                 : upar_from(T, m, xc, a, thd, b.r1, b.r2, b.xw);
         // orthonormal basis about n (Duff et al. 2017)
         const float sgn = copysignf(1.0f, nz);
         const float A_ = -f_rcp(sgn + nz);
@@ -728,7 +742,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         float oz = fmaf(g, nz, sg * fmaf(cp, e1z, sp * e2z));
         const float rn = f_rsq(fmaf(oz, oz, fmaf(ox, ox, oy * oy)));
         ox *= rn; oy *= rn; oz *= rn;
-        float xo = fmaf(sg, fmaf(up1, cp, up2 * sp), fmaf(upar, g - 1.0f, xc));
+        float xo = fmaf(sg, b.kick, fmaf(upar, g - 1.0f, xc));
         if constexpr (kTemp) xo *= isc;  // back to reference units
         if (emis_on) {
             const float gc = dot3(nx, cx, ny, cy, nz, cz);
@@ -736,16 +750,29 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             float xcam = fmaf(upar, gc - 1.0f, xc) + upc;
             const float vc = dot3(cx, vxc, cy, vyc, cz, vzc);
             xcam = kTemp ? fmaf(xcam, isc, vc) : xcam + vc;
-            const int ch = channel_of(xcam, cedges, P.emis_nch, ch_inv_w, ch_lo, ch_safe);
-            const bool in = (unsigned)ch < (unsigned)P.emis_nch;
+            bool sure;
+            int ch = channel_guess(xcam, ch_inv_w, ch_off, ch_safe, sure);
+            const bool other = (unit != 0) & (!sure | ((unsigned)(ch - E.w) >= (unsigned)E.size));
+            if (__ballot(other) != 0ull) {  // wave-uniform: rare
+                if (other) {
+                    const int nch = P.emis_nch;
+                    if (!sure) ch = bin_index(xcam, cedges, nch, ch_inv_w) - 1;
+                    if ((unsigned)ch >= (unsigned)nch) {
+                        ndrop += 1;
+                        unit = 0;
+                    } else if ((unsigned)(ch - E.w) >= (unsigned)E.size) {
+                        flush_emis();
+                        E.move(ch, nch);
+                    }
+                }
+            }
             int64_t wq = 0;
             if constexpr (kDip) {
                 // contributions below 2^32 (F <= 30) convert through 32 bits
-                const float wf = 0.75f * fmaf(gc, gc, 1.0f) * P.frac_scale;
+                const float wf = unit ? 0.75f * fmaf(gc, gc, 1.0f) * P.frac_scale : 0.0f;
                 wq = P.emis_w32 ? (int64_t)__float2uint_rn(wf) : (int64_t)__float2ll_rn(wf);
             }
-            E.add(in, ch, wq, flush_emis);
-            ndrop += in ? 0u : 1u;
+            E.add(ch, unit, wq);
         }
         nx = ox; ny = oy; nz = oz;
         x = fmaf(vzc, nz, fmaf(vyc, ny, fmaf(vxc, nx, xo)));
@@ -809,7 +836,14 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     auto next_event = [&](auto draw) __attribute__((always_inline)) {
         ev += 1;
         draw();
-        if (ev > max_events) give_up();
+    };
+    // packets past their last event, and those that ended
+    auto settle = [&]() __attribute__((always_inline)) {
+        const bool over = ev > max_events;
+        if (over || state > kLive) {
+            if (over && state == kLive) give_up();
+            if (state > kLive) retire();
+        }
     };
 
     // Packets start spread over the waves: wave w (counted across the
@@ -820,7 +854,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     const uint64_t wave = (uint64_t)(threadIdx.x / 64) * gridDim.x + blockIdx.x;
     const uint64_t n_first = (uint64_t)(blockDim.x / 64) * gridDim.x * (uint64_t)P.first_lanes;
     bool first = true;
-    int ticks = 0;
+    int ticks = kEmisTicks;
     bool tail = false;
     for (;;) {
         // ---- refill retired lanes from the global queue -------------------
@@ -930,26 +964,40 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 jacc = 0;
                 state = kLive;
                 next_event(draw_event);
+                if (ev > max_events) give_up();
+            }
+            // (a packet resumed past its last event is neither live nor done: it
+            // retires below)
+            if (__ballot(state != kDone) == 0ull) break;
+            // pool exhausted and few live lanes: continue in tail mode
+            if (!kEsc && P.tail_lanes > 0 && __ballot(state == kDone) != 0ull &&
+                __popcll(__ballot(state == kLive)) <= P.tail_lanes) {
+                tail = true;
+                break;
             }
         }
-        // (a packet resumed past its last event is neither live nor done: it retires below)
-        if (__ballot(state != kDone) == 0ull) break;
-        // pool exhausted and few live lanes: continue in tail mode
-        if (!kEsc && P.tail_lanes > 0 && __ballot(state == kDone) != 0ull &&
-            __popcll(__ballot(state == kLive)) <= P.tail_lanes) {
-            tail = true;
-            break;
-        }
-        if (++ticks == kEmisTicks) {
-            ticks = 0;
+        if (--ticks == 0) {
+            asm volatile("");
+            ticks = kEmisTicks;
             if (emis_on) flush_emis();
         }
 
         // ---- one flight segment (divergent) --------------------------------
-        bool scat = false;
         const float xc = gas_freq();
         const Lookup tl = look_up(xc);
-        if (state == kLive && !pend) scat = flight(tl.H, [&]() __attribute__((always_inline)) { return u01(wa1); });
+        const bool fly = (state == kLive) & !pend;
+        Segment sg{};
+        // (the position of a lane without a packet is of no use to anyone)
+        if (!kEsc || fly) sg = segment(tl.H);
+        bool scat = fly & sg.hit;
+        if (fly & !sg.hit) cross(sg);
+        if (!kEsc && destroys) {
+            asm volatile("");
+            if (scat && destroyed(sg, u01(wa1))) {
+                state = kLive + 2;
+                scat = false;
+            }
+        }
 
         // ---- learned whole-cell escape ---------------------------------------
         // At a scattering inside a thick cubic cell, at least esc_depth_min below
@@ -995,8 +1043,8 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         const bool walk = scat && !mlp && !pend;
         if (walk) {
             SDraws b;
-            scatter_draws(wb, kDip, b);
-            scatter(xc, tl.m, u01(wa2), u01(wa3), b);
+            scatter_draws(wa2, wa3, wb, kDip, b);
+            scatter(xc, tl.m, b, 1);
             if constexpr (!kEsc && !kPark) next_event(draw_event);
         }
         if (kPark) {
@@ -1037,7 +1085,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
             // an event is consumed by a walked scattering or a call; a held one waits
             if (walk || mlp) next_event(draw_event);
         }
-        if (state > kLive) retire();
+        settle();
     }
     // ---- tail mode ------------------------------------------------------------
     // The packet pool is exhausted and at most tail_lanes lanes are live, so the
@@ -1047,69 +1095,95 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     // live lane fetches its event's draws by a cross-lane read.  The draws are
     // the same words mapped by the same functions as in the loop above, so the
     // tallies do not depend on where a packet switches mode.
+    // Such a wave is bound by the latency of one packet's chain and issues an
+    // instruction only every few cycles, a branch with its change of the lane
+    // mask every ten or so.  What need not be looked at for each event (draws
+    // used up, window counts, the event limit) is counted down together in a
+    // scalar, and the lanes without a packet go along, so that while no lane
+    // crosses a face an event is one straight piece of code.
     if (!kEsc && tail) {
-        uint64_t bank_live = 0ull;
-        int k = 1, rank = 0;
-        uint32_t ev0 = 0, ev1 = 0;  // events the bank holds for this lane: [ev0, ev1)
-        bool fresh = false;  // set after a scattering: tau of the new event comes from the draws
-        float pt = 0.f, pue = 0.f, pr1 = 0.f, pr2 = 0.f;
-        SDraws pb;
-        pb.up1 = pb.up2 = pb.g = pb.sg = pb.cp = pb.sp = 0.f;
+        int left = 0;         // events until the next look
+        int k = 1;            // live lanes when the bank was filled
+        int at = 0;           // 4 x the lane that holds this lane's draws (bpermute's address)
+        bool fresh = false;   // set after a scattering: tau of the new event comes from the draws
+        uint32_t unit = 0;    // 1 for a live lane
+        float pt = 0.f, pue = 0.f;
+        SDraws pb{};
         for (;;) {
-            const bool have = state == kLive;
-            const uint64_t live = __ballot(have);
-            if (live == 0ull) break;
-            if (live != bank_live || __ballot(have && ev == ev1) != 0ull) {
+            if (left == 0) {
+                settle();
+                const uint64_t live = __ballot(state == kLive);
+                if (live == 0ull) break;
+                if (ticks <= 64) {
+                    ticks = kEmisTicks;
+                    if (emis_on) flush_emis();
+                }
                 k = __popcll(live);
-                rank = __popcll(live & lanemask_lt);
-                if (have) ev0 = ev;
-                ev1 = ev0 + (uint32_t)((63 - rank) / k + 1);
-                const int r = lane % k, sl = lane / k;
-                const int owner = nth_set_lane(live, r);
+                left = 64 / k;  // each lane's share of the bank
+                ticks -= left;
+                if (__ballot(state == kLive && max_events - ev < 64u) != 0ull) left = 1;
+                unit = state == kLive ? 1u : 0u;
+                const int owner = nth_set_lane(live, lane % k);
                 PhiloxPacket op;
                 op.bk = __shfl(pk.bk, owner, 64);
                 op.hk = __shfl(pk.hk, owner, 64);
                 op.la = __shfl(pk.la, owner, 64);
-                const uint32_t e = __shfl(ev0, owner, 64) + (uint32_t)sl;
+                const uint32_t e = __shfl(ev, owner, 64) + (uint32_t)(lane / k);
                 uint4 A, B;
                 philox_pair(op, e, P.key0, P.key1, A, B);
                 pt = -f_log(u01(A.x));
                 pue = u01(A.y);
-                pr1 = u01(A.z);
-                pr2 = u01(A.w);
-                scatter_draws(B, kDip, pb);
-                bank_live = live;
+                scatter_draws(A.z, A.w, B, kDip, pb);
+                at = 4 * __popcll(live & lanemask_lt);
             }
-            const int src = have ? (int)__umul24(ev - ev0, (unsigned)k) + rank : lane;
-            const float dt = __shfl(pt, src, 64), due = __shfl(pue, src, 64);
-            const float dr1 = __shfl(pr1, src, 64), dr2 = __shfl(pr2, src, 64);
+            --left;
+            auto fetch = [&](float v) __attribute__((always_inline)) {
+                return __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(v)));
+            };
+            const float dt = fetch(pt);
             SDraws db;
-            db.up1 = __shfl(pb.up1, src, 64); db.up2 = __shfl(pb.up2, src, 64);
-            db.g = __shfl(pb.g, src, 64); db.sg = __shfl(pb.sg, src, 64);
-            db.cp = __shfl(pb.cp, src, 64); db.sp = __shfl(pb.sp, src, 64);
-            if (have && fresh) { tau = dt; fresh = false; }
-            if (++ticks == kEmisTicks) {
-                ticks = 0;
-                if (emis_on) flush_emis();
-            }
-            bool scat = false;
+            db.r1 = fetch(pb.r1); db.r2 = fetch(pb.r2); db.xw = fetch(pb.xw);
+            db.g = fetch(pb.g); db.sg = fetch(pb.sg);
+            db.cp = fetch(pb.cp); db.sp = fetch(pb.sp);
+            db.kick = fetch(pb.kick);
+            db.up1 = fetch(pb.up1); db.up2 = fetch(pb.up2);
+            tau = sel(fresh, dt, tau);
+            fresh = false;
             const float xc = gas_freq();
             const Lookup tl = look_up(xc);
-            if (have) scat = flight(tl.H, [&]() __attribute__((always_inline)) { return due; });
+            const bool have = state == kLive;
+            const Segment sg = segment(tl.H);
+            if (!kPark && !destroys && __ballot(have & !sg.hit) == 0ull) {
+                scatter(xc, tl.m, db, unit);
+                next_event([&]() __attribute__((always_inline)) { fresh = true; at += 4 * k; });
+                continue;
+            }
+            float due = 0.0f;
+            if (destroys) due = fetch(pue);
+            bool walk = have & sg.hit;
+            if (have & !sg.hit) cross(sg);
+            if (destroys && walk && destroyed(sg, due)) {
+                state = kLive + 2;
+                walk = false;
+            }
             bool called = false;
             if (kPark) {
                 CellFrame CF{};
                 float ltc = 0.0f, ldep = 0.0f;
-                called = scat && call_eligible(P, k0c, fx, fy, fz, xc, CF, ltc, ldep);
+                called = walk && call_eligible(P, k0c, fx, fy, fz, xc, CF, ltc, ldep);
+                walk = walk && !called;
             }
-            bool walk = scat && !called;
-            if (walk) scatter(xc, tl.m, dr1, dr2, db);
+            if (walk) scatter(xc, tl.m, db, 1);
             if (kPark) {
                 const bool cont = walk && ++seg >= P.park_budget;
                 park(called || cont, walk, xc, called ? 1u : 0u);
             }
-            if (walk) next_event([&]() __attribute__((always_inline)) { fresh = true; });
-            if (state > kLive) retire();
+            if (walk) next_event([&]() __attribute__((always_inline)) { fresh = true; at += 4 * k; });
+            if (__ballot(have & (state != kLive)) != 0ull) {
+                settle();
+                unit = state == kLive ? 1u : 0u;
+                if (__ballot(state == kLive) == 0ull) break;
+            }
         }
     }
 
