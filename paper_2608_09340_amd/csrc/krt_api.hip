@@ -1251,7 +1251,7 @@ extern "C" int krt_escape_record(krt_ctx *c, int32_t line, uint64_t n, uint64_t 
     R.counter = c->work_counter;
     R.out = samples_dev;
     HIPCHK(c, launch_zero_i64(reinterpret_cast<int64_t *>(c->work_counter), 1, c->stream));
-    HIPCHK(c, launch_cell_record(R, 4 * c->cus, c->stream));
+    HIPCHK(c, launch_cell_record(R, c->cus, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return KRT_OK;
 }

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "krt_internal.h"
 #include "krt_kernels.h"
 
@@ -250,6 +252,105 @@ __device__ __forceinline__ float dipole_g(float u) {
     float e = f_exp(t);
     float g = e - f_rcp(e);
     return copysignf(g, q);
+}
+
+// ------------------------------------------------------------- scattering ---
+// Draws of a scattering: the sampler's uniforms r1, r2 with the latter's
+// wing_level, the two u_perp components (Box-Muller, N(0, 1/2) each), the cosine
+// g of the scattering angle (isotropic or dipole) with sqrt(1 - g^2), cos, sin
+// of the azimuth psi, and the u_perp component along the outgoing direction's
+// transverse part.
+struct SDraws {
+    float r1, r2, xw, up1, up2, g, sg, cp, sp, kick;
+};
+
+__device__ __forceinline__ void scatter_draws(uint32_t w1, uint32_t w2, uint4 B, bool dipole, SDraws &d) {
+#pragma clang fp contract(off)
+    d.r1 = u01(w1);
+    d.r2 = u01(w2);
+    d.xw = wing_level(d.r2);
+    const float rr = f_sqrt(-f_log(u01(B.x)));
+    const float th = u01(B.y);
+    d.up1 = rr * cos_rev(th);
+    d.up2 = rr * sin_rev(th);
+    d.g = dipole ? dipole_g(u01(B.z)) : fmaf(2.0f, u01(B.z), -1.0f);
+    d.sg = f_sqrt(fmaxf(0.0f, fmaf(-d.g, d.g, 1.0f)));
+    const float psi = u01(B.w);
+    d.cp = cos_rev(psi);
+    d.sp = sin_rev(psi);
+    d.kick = fmaf(d.up1, d.cp, d.up2 * d.sp);
+}
+
+// ax bx + ay by + az bz in the one order every variant uses
+__device__ __forceinline__ float dot3(float ax, float bx, float ay, float by, float az, float bz) {
+    return fmaf(az, bz, fmaf(ax, bx, ay * by));
+}
+
+// Orthonormal basis (e1, e2) about n (Duff et al. 2017)
+struct Basis {
+    float e1x, e1y, e1z, e2x, e2y, e2z;
+};
+__device__ __forceinline__ Basis scatter_basis(float nx, float ny, float nz) {
+#pragma clang fp contract(off)
+    const float sgn = copysignf(1.0f, nz);
+    const float A = -f_rcp(sgn + nz);
+    Basis e;
+    e.e2x = nx * ny * A;
+    e.e2y = fmaf(ny * ny, A, sgn);
+    e.e2z = -ny;
+    e.e1x = fmaf(A, nx * (nx * sgn), 1.0f);
+    e.e1y = sgn * e.e2x;
+    e.e1z = -sgn * nx;
+    return e;
+}
+// the outgoing direction
+__device__ __forceinline__ void scatter_turn(float nx, float ny, float nz, const Basis &e, const SDraws &b, float &ox,
+                                             float &oy, float &oz) {
+#pragma clang fp contract(off)
+    ox = fmaf(b.g, nx, b.sg * fmaf(b.cp, e.e1x, b.sp * e.e2x));
+    oy = fmaf(b.g, ny, b.sg * fmaf(b.cp, e.e1y, b.sp * e.e2y));
+    oz = fmaf(b.g, nz, b.sg * fmaf(b.cp, e.e1z, b.sp * e.e2z));
+    const float rn = f_rsq(fmaf(oz, oz, fmaf(ox, ox, oy * oy)));
+    ox *= rn; oy *= rn; oz *= rn;
+}
+// the outgoing gas-frame frequency (eq. riia-scatter)
+__device__ __forceinline__ float scatter_shift(float x, float upar, const SDraws &b) {
+#pragma clang fp contract(off)
+    return fmaf(b.sg, b.kick, fmaf(upar, b.g - 1.0f, x));
+}
+
+// ----------------------------------------------------------------- waves ---
+// Lane index of the k-th set bit (k counted from 0) of m; k < popcount(m).
+__device__ __forceinline__ int nth_set_lane(uint64_t m, int k) {
+    int pos = 0;
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) {
+        const uint64_t low = (w == 64) ? m : (m & ((1ull << w) - 1ull));
+        const int c = __popcll(low);
+        if (k >= c) { k -= c; m >>= w; pos += w; }
+        else m = low;
+    }
+    return pos;
+}
+
+// x, y or z of the axis a crossing goes along; by value, since a conditional
+// between captured variables would select between their addresses and hold the
+// lane's state in memory
+template <class V>
+__device__ __forceinline__ V by_axis(bool ax0, bool ax1, V x, V y, V z) {
+    return sel(ax0, x, sel(ax1, y, z));
+}
+
+// Packets a wave starts with, so that few packets use many SIMDs: up to two
+// waves per SIMD (eight of a workgroup's) share them evenly, more packets fill
+// those waves' lanes first and then further waves.  A lone wave leaves issue
+// slots idle that a second one takes, a third and fourth only slow the first
+// two (10,000 packets on a tau0 = 300 slab: 15.1 ms with one wave per SIMD,
+// 14.9 with two, 15.0 with three, 15.5 with four; 130,000 on a 32^3 dipole
+// sphere of tau0 = 1e3: 30.9, 30.2, 32.6, 33.5).
+inline int first_lanes(uint64_t n, uint64_t waves, uint64_t grid) {
+    const uint64_t w = std::min(waves, 8 * grid);
+    return (int)std::min<uint64_t>(64, (n + w - 1) / w);
 }
 
 }  // namespace krt

@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "krt_internal.h"
 #include "krt_kernels.h"
 #include "krt_mlp.h"
@@ -21,10 +23,18 @@
 namespace krt {
 
 // ------------------------------------------------------------- recording ---
-// Persistent pool: each lane takes record indices from one wave-aggregated
-// atomic on `counter` (zeroed by the caller) and walks one event per loop
-// iteration, so records of very different lengths share waves without idling.
-__global__ void __launch_bounds__(256) cell_record_kernel(RecordParams R) {
+// Persistent pool as in the transport: records spread over the waves first,
+// then each lane takes an index from one wave-aggregated atomic on `counter`
+// (zeroed by the caller); one event per loop iteration, so records of very
+// different lengths share waves without idling; once the pool is empty a wave
+// with few walks left draws their coming events ahead with its idle lanes and
+// runs an event as one straight piece of code while no walk leaves the cell.
+// A launch lasts as long as its longest walk, so the chain of one event bounds
+// it, and the bulk the instruction issue.
+constexpr int kRecThreads = 1024;
+constexpr int kRecTailLanes = 32;
+__global__ void __launch_bounds__(kRecThreads) cell_record_kernel(RecordParams R) {
+#pragma clang fp contract(off)
     extern __shared__ float4 lds4[];
     float *T = reinterpret_cast<float *>(lds4);
     const float4 *src = reinterpret_cast<const float4 *>(R.tab);
@@ -32,32 +42,120 @@ __global__ void __launch_bounds__(256) cell_record_kernel(RecordParams R) {
     __syncthreads();
     const int lane = __lane_id();
     const uint64_t lanemask_lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const float la = __log10f(R.a);
-    bool have = false, done = false;
-    uint64_t idx = 0, pid = 0;
+    constexpr int kDone = -1, kNeed = 0, kLive = 1;
+    int state = kNeed;
+    uint64_t idx = 0;
+    PhiloxPacket pk{};
+    uint4 wb = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t w1 = 0, w2 = 0;
     float lt = 0.f, tauc = 0.f, xin = 0.f, q0 = 0.f, q1 = 0.f, q2 = 0.f;
     float m0 = 0.f, m1 = 0.f, m2 = 1.f;
-    float px = 0.f, py = 0.f, pz = 0.f, nx = 0.f, ny = 0.f, nz = 1.f, x = 0.f, sx2 = 0.f;
-    uint32_t ev = 0, ns = 0;
+    float px = 0.f, py = 0.f, pz = 0.f, nx = 0.f, ny = 0.f, nz = 1.f, x = 0.f, sx2 = 0.f, tau = 0.f;
+    uint32_t ns = 0;  // scatterings so far; the next event is ns + 1
+    auto draw_event = [&]() __attribute__((always_inline)) {
+        uint4 A;
+        philox_pair(pk, ns + 1, R.k0, R.k1, A, wb);
+        tau = -f_log(u01(A.x));
+        w1 = A.z; w2 = A.w;
+    };
+    // one event of a walk: the flight from the last interaction point (none
+    // before the first event), then the scattering unless it left the cell
+    struct Flight {
+        float tx, ty, tm;
+        bool inside;
+        UparMass m;
+    };
+    auto fly = [&]() __attribute__((always_inline)) {
+        Flight f;
+        const float xa = fabsf(x);
+        const VoigtEntry e = voigt_entry(T, xa);
+        f.m = upar_mass(T, e);
+        const float kap = tauc * voigt_value(e, xa);
+        // a zero component gives +inf or NaN, which the minimum ignores
+        f.tx = fabsf(px - copysignf(1.0f, nx)) * f_rcp(fabsf(nx));
+        f.ty = fabsf(py - copysignf(1.0f, ny)) * f_rcp(fabsf(ny));
+        f.tm = fminf(fminf(f.tx, f.ty), fabsf(pz - copysignf(1.0f, nz)) * f_rcp(fabsf(nz)));
+        const float dm = fmaxf(f.tm, 0.0f);
+        const bool first = ns == 0;
+        f.inside = first | !(kap * dm < tau);
+        const float l = sel(f.inside, sel(first, 0.0f, tau * f_rcp(kap)), dm);
+        px = fminf(fmaxf(fmaf(l, nx, px), -1.f), 1.f);
+        py = fminf(fmaxf(fmaf(l, ny, py), -1.f), 1.f);
+        pz = fminf(fmaxf(fmaf(l, nz, pz), -1.f), 1.f);
+        return f;
+    };
+    auto scatter = [&](const UparMass &m, const SDraws &b) __attribute__((always_inline)) {
+        const float upar = upar_from(T, m, x, R.a, R.thd, b.r1, b.r2, b.xw);
+        const Basis e = scatter_basis(nx, ny, nz);
+        float ox, oy, oz;
+        scatter_turn(nx, ny, nz, e, b, ox, oy, oz);
+        sx2 = fmaf(x, x, sx2);
+        x = scatter_shift(x, upar, b);
+        nx = ox; ny = oy; nz = oz;
+        ns += 1;
+    };
+    // a walk that left the cell (or passed max_scat: stored invalid)
+    auto store = [&](const Flight &f, bool exited) __attribute__((always_inline)) {
+        float *o = R.out + (int64_t)kRec * idx;
+        o[kRecLT] = lt;
+        o[kRecLA] = __log10f(R.a);
+        o[kRecX] = xin;
+        o[kRecQ0] = q0; o[kRecQ0 + 1] = q1; o[kRecQ0 + 2] = q2;
+        o[kRecLD] = lt + __log10f(fmaxf(1.0f - q2, 1e-30f));
+        o[kRecN0] = m0; o[kRecN0 + 1] = m1; o[kRecN0 + 2] = m2;
+        if (exited) {
+            const bool ax0 = f.tx == f.tm, ax1 = !ax0 && f.ty == f.tm;  // ties go to the lower axis
+            // the face's axis, and the two that follow it cyclically
+            const float nn = by_axis(ax0, ax1, nx, ny, nz), n1 = by_axis(ax0, ax1, ny, nz, nx),
+                        n2 = by_axis(ax0, ax1, nz, nx, ny);
+            const float qk = by_axis(ax0, ax1, q0, q1, q2), qa = by_axis(ax0, ax1, q1, q2, q0),
+                        qb = by_axis(ax0, ax1, q2, q0, q1);
+            const float side = nn > 0.f ? 1.f : -1.f;
+            const float dpl = fmaf(-side, qk, 1.f);
+            const float ds = by_axis(ax0, ax1, py, pz, px) - qa, dt = by_axis(ax0, ax1, pz, px, py) - qb;
+            o[kRecFace] = (float)(2 * by_axis(ax0, ax1, 0, 1, 2) + (side > 0.f ? 1 : 0));
+            o[kRecYS] = ds / dpl;
+            o[kRecYT] = dt / dpl;
+            o[kRecMu] = fabsf(nn);
+            o[kRecAlpha] = atan2f(fabsf(fmaf(ds, n2, -(dt * n1))), fmaf(ds, n1, dt * n2));
+            o[kRecXOut] = x;
+            o[kRecLogN] = logf((float)ns);
+            o[kRecLogX2] = logf(fmaxf(sx2 / (float)ns, 1e-6f));
+            o[kRecValid] = 1.0f;
+        } else {
+            for (int k = kRecFace; k <= kRecValid; ++k) o[k] = 0.0f;
+        }
+        o[kRec - 1] = 0.0f;
+        state = kNeed;
+    };
+    const uint64_t wave = (uint64_t)(threadIdx.x / 64) * gridDim.x + blockIdx.x;
+    const uint64_t n_first = (uint64_t)(blockDim.x / 64) * gridDim.x * (uint64_t)R.first_lanes;
+    bool start = true;
     for (;;) {
-        const bool need = !have && !done;
-        const uint64_t need_mask = __ballot(need);
+        const uint64_t need_mask = __ballot(state == kNeed);
         if (need_mask) {
-            const int leader = __ffsll((long long)need_mask) - 1;
-            unsigned long long base = 0;
-            if (lane == leader) base = atomicAdd(R.counter, (unsigned long long)__popcll(need_mask));
-            base = __shfl(base, leader, 64);
-            if (need) {
+            uint64_t base = 0;
+            if (start) {
+                base = wave * (uint64_t)R.first_lanes;
+                start = false;
+                if (lane >= R.first_lanes) state = kDone;
+            } else {
+                const int leader = __ffsll((long long)need_mask) - 1;
+                unsigned long long b = 0;
+                if (lane == leader) b = n_first + atomicAdd(R.counter, (unsigned long long)__popcll(need_mask));
+                base = __shfl(b, leader, 64);
+            }
+            if (state == kNeed) {
                 idx = base + (uint64_t)__popcll(need_mask & lanemask_lt);
                 if (idx >= R.n) {
-                    done = true;
+                    state = kDone;
                 } else {
-                    pid = R.offset + idx;
+                    const uint64_t pid = R.offset + idx;
                     const uint32_t plo = (uint32_t)pid, phi = (uint32_t)(pid >> 32);
                     const uint4 c = philox(make_uint4(0u, plo, phi, 3u), R.k0, R.k1);
                     const uint4 d = philox(make_uint4(0u, plo, phi, 4u), R.k0, R.k1);
                     const uint4 e = philox(make_uint4(0u, plo, phi, 5u), R.k0, R.k1);
-                    lt = R.lt_lo + (R.lt_hi - R.lt_lo) * u01(c.x);
+                    lt = fmaf(R.lt_hi - R.lt_lo, u01(c.x), R.lt_lo);
                     tauc = f_exp(lt * 2.302585093f);
                     if (R.fixed) {
                         xin = R.x_in;
@@ -67,16 +165,17 @@ __global__ void __launch_bounds__(256) cell_record_kernel(RecordParams R) {
                         if (u01(c.y) < 0.5f) xin = fabsf(f_sqrt(-f_log(u01(c.z))) * cos_rev(u01(c.w)));
                         else xin = kRecXMax * u01(c.z);
                         // depth to the nearest face log-uniform in [depth_lo, tau_c]
-                        const float ld = fminf(R.ld_lo, lt) + (lt - fminf(R.ld_lo, lt)) * u01(e.x);
+                        const float l0 = fminf(R.ld_lo, lt);
+                        const float ld = fmaf(lt - l0, u01(e.x), l0);
                         q2 = fminf(fmaxf(1.0f - f_exp((ld - lt) * 2.302585093f), 0.0f), 0.99999f);
-                        float a0 = q2 * u01(e.y), a1 = q2 * u01(e.z);
+                        const float a0 = q2 * u01(e.y), a1 = q2 * u01(e.z);
                         q0 = fminf(a0, a1);
                         q1 = fmaxf(a0, a1);
                     }
                     if (R.fixed && !R.iso_dir) {
                         m0 = R.n_in[0]; m1 = R.n_in[1]; m2 = R.n_in[2];
                     } else {
-                        const float mu0 = 2.0f * u01(d.x) - 1.0f, st0 = f_sqrt(fmaxf(0.0f, 1.0f - mu0 * mu0));
+                        const float mu0 = fmaf(2.0f, u01(d.x), -1.0f), st0 = f_sqrt(fmaxf(0.0f, fmaf(-mu0, mu0, 1.0f)));
                         const float ph0 = u01(d.y);
                         m0 = st0 * cos_rev(ph0); m1 = st0 * sin_rev(ph0); m2 = mu0;
                     }
@@ -85,101 +184,81 @@ __global__ void __launch_bounds__(256) cell_record_kernel(RecordParams R) {
                     x = xin;
                     sx2 = 0.0f;
                     ns = 0;
-                    ev = 1;
-                    have = true;
+                    state = kLive;
+                    pk = philox_packet(plo, phi, R.k0, R.k1);
+                    draw_event();
                 }
             }
+            const uint64_t live = __ballot(state == kLive);
+            if (live == 0ull) break;  // the pool is empty: every lane is done
+            if (__ballot(state == kDone) != 0ull && __popcll(live) <= kRecTailLanes) break;
         }
-        if (__ballot(have) == 0ull) break;
-        if (!have) continue;
-        const uint32_t plo = (uint32_t)pid, phi = (uint32_t)(pid >> 32);
-        const uint4 A = philox(make_uint4(ev, plo, phi, 0u), R.k0, R.k1);
-        bool exited = false;
-        int ax = 0;
-        if (ev > 1) {
-            // flight from the last interaction point
-            const float tau = -f_log(u01(A.x));
-            const float kap = tauc * voigt_lds(T, fabsf(x));
-            const float tx = (nx > 0.f) ? (1.f - px) * f_rcp(nx) : ((nx < 0.f) ? (-1.f - px) * f_rcp(nx) : INFINITY);
-            const float ty = (ny > 0.f) ? (1.f - py) * f_rcp(ny) : ((ny < 0.f) ? (-1.f - py) * f_rcp(ny) : INFINITY);
-            const float tz = (nz > 0.f) ? (1.f - pz) * f_rcp(nz) : ((nz < 0.f) ? (-1.f - pz) * f_rcp(nz) : INFINITY);
-            float dm = tx;
-            if (ty < dm) { dm = ty; ax = 1; }
-            if (tz < dm) { dm = tz; ax = 2; }
-            dm = fmaxf(dm, 0.0f);
-            if (kap * dm < tau) {
-                px += dm * nx; py += dm * ny; pz += dm * nz;
-                exited = true;
-            } else {
-                const float l = tau * f_rcp(kap);
-                px = fminf(fmaxf(px + l * nx, -1.f), 1.f);
-                py = fminf(fmaxf(py + l * ny, -1.f), 1.f);
-                pz = fminf(fmaxf(pz + l * nz, -1.f), 1.f);
-            }
+        const Flight f = fly();  // (a done lane's position is of no use to anyone)
+        const bool live = state == kLive;
+        bool over = false;
+        if (live & f.inside) {
+            SDraws b;
+            scatter_draws(w1, w2, wb, false, b);
+            scatter(f.m, b);
+            draw_event();
+            over = ns > R.max_scat;
         }
-        if (!exited) {
-            // resonant scattering (isotropic phase), event ev's words
-            const uint4 B = philox(make_uint4(ev, plo, phi, 1u), R.k0, R.k1);
-            const float upar = upar_lds(T, x, R.a, R.thd, u01(A.z), u01(A.w));
-            const float rr = f_sqrt(-f_log(u01(B.x)));
-            const float th = u01(B.y);
-            const float up1 = rr * cos_rev(th), up2 = rr * sin_rev(th);
-            const float g = 2.0f * u01(B.z) - 1.0f;
-            const float psi = u01(B.w);
-            const float sg = f_sqrt(fmaxf(0.0f, 1.0f - g * g));
-            const float sgn = copysignf(1.0f, nz);
-            const float A_ = -f_rcp(sgn + nz);
-            const float B_ = nx * ny * A_;
-            const float e1x = 1.0f + sgn * nx * nx * A_, e1y = sgn * B_, e1z = -sgn * nx;
-            const float e2x = B_, e2y = sgn + ny * ny * A_, e2z = -ny;
-            const float cp = cos_rev(psi), sp = sin_rev(psi);
-            const float ox = g * nx + sg * (cp * e1x + sp * e2x);
-            const float oy = g * ny + sg * (cp * e1y + sp * e2y);
-            const float oz = g * nz + sg * (cp * e1z + sp * e2z);
-            const float rn = f_rsq(ox * ox + oy * oy + oz * oz);
-            sx2 += x * x;
-            x = x + upar * (g - 1.0f) + sg * (up1 * cp + up2 * sp);
-            nx = ox * rn; ny = oy * rn; nz = oz * rn;
-            ns += 1;
-            ev += 1;
+        if (live & (!f.inside | over)) store(f, !f.inside);
+    }
+    // ---- tail (none left: the first look ends it)
+    int left = 0;        // events until the next look
+    int k = 1;           // live lanes when the bank was filled
+    int at = 0;          // 4 x the lane that holds this lane's draws
+    bool fresh = false;  // tau of the event comes from the draws
+    float pt = 0.f;
+    SDraws pb{};
+    for (;;) {
+        if (left == 0) {
+            const uint64_t live = __ballot(state == kLive);
+            if (live == 0ull) break;
+            k = __popcll(live);
+            left = 64 / k;
+            if (__ballot(state == kLive && R.max_scat - ns < 64u) != 0ull) left = 1;
+            const int owner = nth_set_lane(live, lane % k);
+            PhiloxPacket op;
+            op.bk = __shfl(pk.bk, owner, 64);
+            op.hk = __shfl(pk.hk, owner, 64);
+            op.la = __shfl(pk.la, owner, 64);
+            const uint32_t e = __shfl(ns, owner, 64) + 1u + (uint32_t)(lane / k);
+            uint4 A, B;
+            philox_pair(op, e, R.k0, R.k1, A, B);
+            pt = -f_log(u01(A.x));
+            scatter_draws(A.z, A.w, B, false, pb);
+            at = 4 * __popcll(live & lanemask_lt);
         }
-        const bool capped = !exited && ns > R.max_scat;
-        if (exited || capped) {
-            float *o = R.out + (int64_t)kRec * idx;
-            o[kRecLT] = lt;
-            o[kRecLA] = la;
-            o[kRecX] = xin;
-            o[kRecQ0] = q0; o[kRecQ0 + 1] = q1; o[kRecQ0 + 2] = q2;
-            o[kRecLD] = lt + __log10f(fmaxf(1.0f - q2, 1e-30f));
-            o[kRecN0] = m0; o[kRecN0 + 1] = m1; o[kRecN0 + 2] = m2;
-            if (exited) {
-                const float qq[3] = {q0, q1, q2}, P[3] = {px, py, pz}, N[3] = {nx, ny, nz};
-                float side = 0.f, dpl = 1.f, ds = 0.f, dt = 0.f, n1 = 0.f, n2 = 0.f, nn = 0.f;
-#pragma unroll
-                for (int k = 0; k < 3; ++k)
-                    if (k == ax) {
-                        const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
-                        side = N[k] > 0.f ? 1.f : -1.f;
-                        dpl = 1.f - side * qq[k];
-                        ds = fminf(fmaxf(P[k1], -1.f), 1.f) - qq[k1];
-                        dt = fminf(fmaxf(P[k2], -1.f), 1.f) - qq[k2];
-                        n1 = N[k1]; n2 = N[k2]; nn = N[k];
-                    }
-                o[kRecFace] = (float)(2 * ax + (side > 0.f ? 1 : 0));
-                o[kRecYS] = ds / dpl;
-                o[kRecYT] = dt / dpl;
-                o[kRecMu] = fabsf(nn);
-                o[kRecAlpha] = atan2f(fabsf(ds * n2 - dt * n1), ds * n1 + dt * n2);
-                o[kRecXOut] = x;
-                o[kRecLogN] = logf((float)ns);
-                o[kRecLogX2] = logf(fmaxf(sx2 / (float)ns, 1e-6f));
-                o[kRecValid] = 1.0f;
-            } else {
-                for (int k = kRecFace; k <= kRecValid; ++k) o[k] = 0.0f;
-            }
-            o[kRec - 1] = 0.0f;
-            have = false;
+        --left;
+        auto fetch = [&](float v) __attribute__((always_inline)) {
+            return __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(v)));
+        };
+        const float dt = fetch(pt);
+        SDraws db;
+        db.up1 = db.up2 = 0.0f;
+        db.r1 = fetch(pb.r1); db.r2 = fetch(pb.r2); db.xw = fetch(pb.xw);
+        db.g = fetch(pb.g); db.sg = fetch(pb.sg);
+        db.cp = fetch(pb.cp); db.sp = fetch(pb.sp);
+        db.kick = fetch(pb.kick);
+        tau = sel(fresh, dt, tau);
+        const Flight f = fly();
+        const bool live = state == kLive;
+        if (__ballot(live & !f.inside) == 0ull && left != 0) {
+            scatter(f.m, db);
+            fresh = true;
+            at += 4 * k;
+            continue;
         }
+        bool over = false;
+        if (live & f.inside) {
+            scatter(f.m, db);
+            at += 4 * k;
+            over = ns > R.max_scat;
+        }
+        fresh = true;
+        if (live & (!f.inside | over)) store(f, !f.inside);
     }
 }
 
@@ -716,16 +795,18 @@ __global__ void mlp_calib_finish_kernel(const double *sums, float *norm) {
 }
 
 // --------------------------------------------------------------- launch ---
-hipError_t launch_cell_record(const RecordParams &R, int grid, hipStream_t s) {
-    size_t lds = sizeof(float) * kTabFloats;
-    static bool attr = false;
-    if (!attr) {
+hipError_t launch_cell_record(const RecordParams &R0, int cus, hipStream_t s) {
+    const size_t lds = sizeof(float) * kTabFloats;
+    static std::atomic<bool> attr{false};
+    if (!attr.load()) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(cell_record_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        attr = true;
+        attr.store(true);
     }
-    hipLaunchKernelGGL(cell_record_kernel, dim3(grid), dim3(256), lds, s, R);
+    RecordParams R = R0;
+    R.first_lanes = first_lanes(R.n, (uint64_t)cus * (kRecThreads / 64), (uint64_t)cus);
+    hipLaunchKernelGGL(cell_record_kernel, dim3(cus), dim3(kRecThreads), lds, s, R);
     return hipGetLastError();
 }
 

@@ -173,10 +173,11 @@ struct RecordParams {
     uint32_t max_scat;            // records past this many scatterings are invalid
     int fixed, iso_dir;           // fixed start (x_in, q, n_in) / isotropic n_in with it
     float x_in, q[3], n_in[3];
-    unsigned long long *counter;  // record pool, zeroed before the launch
+    unsigned long long *counter;  // record pool beyond the first records, zeroed before the launch
+    int first_lanes;              // records a wave starts with (1..64)
     float *out;                   // [n][kRec]
 };
-hipError_t launch_cell_record(const RecordParams &R, int grid, hipStream_t s);
+hipError_t launch_cell_record(const RecordParams &R, int cus, hipStream_t s);
 hipError_t launch_mlp_init(float *p, uint32_t k0, uint32_t k1, hipStream_t s);
 hipError_t launch_mlp_pack(const float *p, const float *norm, unsigned char *blob, unsigned char *img,
                            hipStream_t s);

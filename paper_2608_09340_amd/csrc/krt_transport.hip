@@ -100,19 +100,6 @@ __device__ __forceinline__ void wave_add_counter(int64_t *dst, int64_t v) {
 }
 
 // ------------------------------------------------------ learned escape ---
-// Lane index of the k-th set bit (k counted from 0) of m; k < popcount(m).
-__device__ __forceinline__ int nth_set_lane(uint64_t m, int k) {
-    int pos = 0;
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) {
-        const uint64_t low = (w == 64) ? m : (m & ((1ull << w) - 1ull));
-        const int c = __popcll(low);
-        if (k >= c) { k -= c; m >>= w; pos += w; }
-        else m = low;
-    }
-    return pos;
-}
-
 // Batched evaluation of the escape network for the lanes of the wave set in
 // `ask` (wave-uniform control flow: every lane executes the MFMA).  The asking
 // lanes are packed in rank order into blocks of 16 samples, so a call costs
@@ -406,45 +393,6 @@ __device__ __forceinline__ float cont_voigt(const RunParams &P, int voff, float 
 }
 
 // --------------------------------------------------------------- kernel ---
-// Draws of a scattering: the sampler's uniforms r1, r2 with the latter's
-// wing_level, the two u_perp components (Box-Muller, N(0, 1/2) each), the cosine
-// g of the scattering angle (isotropic or dipole) with sqrt(1 - g^2), cos, sin
-// of the azimuth psi, and the u_perp component along the outgoing direction's
-// transverse part.
-struct SDraws {
-    float r1, r2, xw, up1, up2, g, sg, cp, sp, kick;
-};
-
-__device__ __forceinline__ void scatter_draws(uint32_t w1, uint32_t w2, uint4 B, bool dipole, SDraws &d) {
-#pragma clang fp contract(off)
-    d.r1 = u01(w1);
-    d.r2 = u01(w2);
-    d.xw = wing_level(d.r2);
-    const float rr = f_sqrt(-f_log(u01(B.x)));
-    const float th = u01(B.y);
-    d.up1 = rr * cos_rev(th);
-    d.up2 = rr * sin_rev(th);
-    d.g = dipole ? dipole_g(u01(B.z)) : fmaf(2.0f, u01(B.z), -1.0f);
-    d.sg = f_sqrt(fmaxf(0.0f, fmaf(-d.g, d.g, 1.0f)));
-    const float psi = u01(B.w);
-    d.cp = cos_rev(psi);
-    d.sp = sin_rev(psi);
-    d.kick = fmaf(d.up1, d.cp, d.up2 * d.sp);
-}
-
-// ax bx + ay by + az bz in the one order every variant uses
-__device__ __forceinline__ float dot3(float ax, float bx, float ay, float by, float az, float bz) {
-    return fmaf(az, bz, fmaf(ax, bx, ay * by));
-}
-
-// x, y or z of the axis a crossing goes along; by value, since a conditional
-// between captured variables would select between their addresses and hold the
-// lane's state in memory
-template <class V>
-__device__ __forceinline__ V by_axis(bool ax0, bool ax1, V x, V y, V z) {
-    return sel(ax0, x, sel(ax1, y, z));
-}
-
 // Distance along one axis to the face ahead: n the direction's component, f the
 // position in the cell, dx its width.  A zero component gives +inf, or NaN (0
 // times inf) for a packet exactly on the face; the minimum over the axes
@@ -729,24 +677,17 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     // nothing)
     auto scatter = [&](float xc, const UparMass &m, const SDraws &b, uint32_t unit) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
-        const float up1 = b.up1, up2 = b.up2, g = b.g, sg = b.sg, cp = b.cp, sp = b.sp;
         const float upar = kTemp ? upar_from(((kProf == 4) ? P.cs_tab : P.cls_tab) + toff, m, xc, sac, thdc, b.r1, b.r2, b.xw)
                                  : upar_from(T, m, xc, a, thd, b.r1, b.r2, b.xw);
-        // orthonormal basis about n (Duff et al. 2017)
-        const float sgn = copysignf(1.0f, nz);
-        const float A_ = -f_rcp(sgn + nz);
-        const float e2x = nx * ny * A_, e2y = fmaf(ny * ny, A_, sgn), e2z = -ny;
-        const float e1x = fmaf(A_, nx * (nx * sgn), 1.0f), e1y = sgn * e2x, e1z = -sgn * nx;
-        float ox = fmaf(g, nx, sg * fmaf(cp, e1x, sp * e2x));
-        float oy = fmaf(g, ny, sg * fmaf(cp, e1y, sp * e2y));
-        float oz = fmaf(g, nz, sg * fmaf(cp, e1z, sp * e2z));
-        const float rn = f_rsq(fmaf(oz, oz, fmaf(ox, ox, oy * oy)));
-        ox *= rn; oy *= rn; oz *= rn;
-        float xo = fmaf(sg, b.kick, fmaf(upar, g - 1.0f, xc));
+        const Basis e = scatter_basis(nx, ny, nz);
+        float ox, oy, oz;
+        scatter_turn(nx, ny, nz, e, b, ox, oy, oz);
+        float xo = scatter_shift(xc, upar, b);
         if constexpr (kTemp) xo *= isc;  // back to reference units
         if (emis_on) {
             const float gc = dot3(nx, cx, ny, cy, nz, cz);
-            const float upc = fmaf(up1, dot3(e1x, cx, e1y, cy, e1z, cz), up2 * dot3(e2x, cx, e2y, cy, e2z, cz));
+            const float upc = fmaf(b.up1, dot3(e.e1x, cx, e.e1y, cy, e.e1z, cz),
+                                   b.up2 * dot3(e.e2x, cx, e.e2y, cy, e.e2z, cz));
             float xcam = fmaf(upar, gc - 1.0f, xc) + upc;
             const float vc = dot3(cx, vxc, cy, vyc, cz, vzc);
             xcam = kTemp ? fmaf(xcam, isc, vc) : xcam + vc;
@@ -1292,18 +1233,6 @@ constexpr int kMaxTransportLds = std::max(kPlainLds + (int)sizeof(int64_t) * kEm
 static_assert(kMaxTransportLds <= 160 * 1024, "a workgroup's LDS fits one CU (160 KiB)");
 static_assert((kTabFloats + kEdgeFloats) % 4 == 0 && (kTabFloats + kChanEdgeFloats + kMlpFwdBytes / 4) % 4 == 0,
               "the counters are aligned");
-
-// Packets a wave starts with, so that few packets use many SIMDs: up to two
-// waves per SIMD (eight of a workgroup's) share them evenly, more packets fill
-// those waves' lanes first and then further waves.  A lone wave leaves issue
-// slots idle that a second one takes, a third and fourth only slow the first
-// two (10,000 packets on a tau0 = 300 slab: 15.1 ms with one wave per SIMD,
-// 14.9 with two, 15.0 with three, 15.5 with four; 130,000 on a 32^3 dipole
-// sphere of tau0 = 1e3: 30.9, 30.2, 32.6, 33.5).
-static int first_lanes(uint64_t n, uint64_t waves, uint64_t grid) {
-    const uint64_t w = std::min(waves, 8 * grid);
-    return (int)std::min<uint64_t>(64, (n + w - 1) / w);
-}
 
 template <int kMode, int kMaxThreads, int kProf, bool kDip>
 static hipError_t launch_transport_t(const RunParams &P, int grid, int block, size_t lds, hipStream_t s) {

@@ -79,3 +79,23 @@ def test_spread_packets_match_split_range(gpu_ctx, n):
     for key in ("spec_raw", "emis_raw"):
         assert np.array_equal(a[key], sum(r[key] for r in parts))
     assert a["counters"]["scatterings"] == sum(r["counters"]["scatterings"] for r in parts)
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 5000])
+def test_records_do_not_depend_on_their_lanes(gpu_ctx, n):
+    """Whole-cell walks started together or in two calls, in other lanes and
+    with other neighbours, are the same records bit for bit."""
+    import torch
+    from paper_2608_09340_amd import krt
+    krt.Transport(W.sphere(2, 1.0, 1e-2, phase=0, emis=None), ctx=gpu_ctx)
+    dev = torch.device("cuda", 0)
+
+    def rec(m, off):
+        out = torch.full((m, krt.ESC_NREC), -7.0, device=dev)
+        gpu_ctx.krt_escape_record(0, m, 5, off, 1.5, 3.0, out)
+        return out.cpu().numpy()
+
+    a, k = rec(n, 40), (n + 1) // 3
+    b = np.concatenate([rec(m, 40 + o) for m, o in ((k, 0), (n - k, k)) if m])
+    assert np.array_equal(a, b)
+    assert np.all(a[:, 18] == 1.0) and np.all(a[:, 19] == 0.0)
