@@ -353,4 +353,78 @@ inline int first_lanes(uint64_t n, uint64_t waves, uint64_t grid) {
     return (int)std::min<uint64_t>(64, (n + w - 1) / w);
 }
 
+// A wave's share of a launch's work items [0, n): the first `lanes` of them
+// fixed by its place, the rest from the launch's counter (zeroed by the caller).
+// The counter is one address for the whole chip and serves about one request in
+// 4.6 ns, so short items taken one refill at a time wait for it: in a Lambda
+// cycle's transport 4096 waves asked once per iteration, 19 us apart.  A wave
+// that comes back within kPoolSoon iterations therefore takes twice as many as
+// the last time (at most kPoolChunk, and at most half its even share of what is
+// left), and one that comes back later takes what it needs: long items are
+// never held in stock while another wave is idle.
+constexpr uint32_t kPoolChunk = 256;
+constexpr int kPoolSoon = 32;
+// Idle lanes are refilled together: at kRefillLanes of them, or kRefillWait
+// iterations after the first, or when no lane is live.  Starting a packet costs
+// the wave more than an iteration, however many lanes start.
+constexpr int kRefillLanes = 16, kRefillWait = 8;
+struct WorkPool {
+    uint64_t next;            // the stock's first item
+    uint32_t left, chunk;     // items in stock; taken the last time
+    bool dry;                 // the counter has passed n
+    int waited, since;        // iterations since the first idle lane, since the last request
+
+    __device__ __forceinline__ void init(int lanes) {
+        // waves counted across the workgroups first, so that consecutive ones sit on different CUs
+        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)) * gridDim.x + blockIdx.x;
+        next = (uint64_t)wave * (uint64_t)lanes;
+        left = (uint32_t)lanes;
+        chunk = 0;
+        dry = lanes < 64;
+        waited = 0;
+        since = 0;
+    }
+    // whether the idle lanes (a wave-uniform mask) are refilled in this iteration
+    __device__ __forceinline__ bool due(uint64_t idle, bool any_live) {
+        ++since;
+        if (idle == 0ull) return false;
+        if (__popcll(idle) >= kRefillLanes || ++waited >= kRefillWait || !any_live || dry) {
+            waited = 0;
+            return true;
+        }
+        return false;
+    }
+    // the work item of this lane (n or more: none), for the lanes of `idle`
+    __device__ __forceinline__ uint64_t take(uint64_t idle, int lane, uint64_t lanemask_lt, unsigned long long *counter,
+                                             uint64_t n, int lanes) {
+        const uint32_t cnt = (uint32_t)__popcll(idle), rank = (uint32_t)__popcll(idle & lanemask_lt);
+        uint64_t mine = rank < left ? next + rank : ~0ull;
+        if (cnt <= left) {
+            next += cnt;
+            left -= cnt;
+        } else if (dry) {
+            left = 0;
+        } else {
+            const uint32_t more = cnt - left, waves = (blockDim.x / 64) * gridDim.x;
+            const uint64_t first = (uint64_t)waves * (uint64_t)lanes;  // those given out by place
+            const uint64_t seen = max(next + left, first), rest = n > seen ? n - seen : 0;
+            // rest >> share is between half and the whole of the even share
+            const int share = 32 - __clz((int)waves);
+            chunk = since < kPoolSoon ? min(2 * max(chunk, more), kPoolChunk) : 0u;
+            chunk = max(more, (uint32_t)min(rest >> share, (uint64_t)chunk));
+            since = 0;
+            const int leader = __ffsll((long long)idle) - 1;
+            uint64_t nb = 0;
+            if (lane == leader) nb = first + atomicAdd(counter, (unsigned long long)chunk);
+            nb = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(nb >> 32), leader) << 32) |
+                 (uint32_t)__builtin_amdgcn_readlane((int)nb, leader);
+            if (rank >= left) mine = nb + (rank - left);
+            next = nb + more;
+            left = chunk - more;
+            dry = nb >= n;
+        }
+        return mine;
+    }
+};
+
 }  // namespace krt

@@ -128,25 +128,14 @@ __global__ void __launch_bounds__(kRecThreads) cell_record_kernel(RecordParams R
         o[kRec - 1] = 0.0f;
         state = kNeed;
     };
-    const uint64_t wave = (uint64_t)(threadIdx.x / 64) * gridDim.x + blockIdx.x;
-    const uint64_t n_first = (uint64_t)(blockDim.x / 64) * gridDim.x * (uint64_t)R.first_lanes;
-    bool start = true;
+    WorkPool pool;
+    pool.init(R.first_lanes);
     for (;;) {
         const uint64_t need_mask = __ballot(state == kNeed);
-        if (need_mask) {
-            uint64_t base = 0;
-            if (start) {
-                base = wave * (uint64_t)R.first_lanes;
-                start = false;
-                if (lane >= R.first_lanes) state = kDone;
-            } else {
-                const int leader = __ffsll((long long)need_mask) - 1;
-                unsigned long long b = 0;
-                if (lane == leader) b = n_first + atomicAdd(R.counter, (unsigned long long)__popcll(need_mask));
-                base = __shfl(b, leader, 64);
-            }
+        if (pool.due(need_mask, __ballot(state == kLive) != 0ull)) {
+            const uint64_t mine = pool.take(need_mask, lane, lanemask_lt, R.counter, R.n, R.first_lanes);
             if (state == kNeed) {
-                idx = base + (uint64_t)__popcll(need_mask & lanemask_lt);
+                idx = mine;
                 if (idx >= R.n) {
                     state = kDone;
                 } else {

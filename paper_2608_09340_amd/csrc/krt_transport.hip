@@ -787,41 +787,23 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
         }
     };
 
-    // Packets start spread over the waves: wave w (counted across the
-    // workgroups first, so that consecutive waves sit on different CUs) begins
-    // with the packets [w first_lanes, (w + 1) first_lanes); the pool beyond
-    // them is shared (empty where first_lanes < 64).
-    const uint64_t n_work = P.n_res + P.n_packets;
-    const uint64_t wave = (uint64_t)(threadIdx.x / 64) * gridDim.x + blockIdx.x;
-    const uint64_t n_first = (uint64_t)(blockDim.x / 64) * gridDim.x * (uint64_t)P.first_lanes;
-    bool first = true;
+    WorkPool pool;
+    pool.init(P.first_lanes);
     int ticks = kEmisTicks;
     bool tail = false;
     for (;;) {
-        // ---- refill retired lanes from the global queue -------------------
-        bool need = state == kNeed;
-        uint64_t need_mask = __ballot(need);
-        if (need_mask) {
-            unsigned long long base = 0;
-            if (first) {
-                base = wave * (uint64_t)P.first_lanes;
-                first = false;
-                if (lane >= P.first_lanes) { state = kDone; need = false; }
-            } else {
-                const int leader = __ffsll((long long)need_mask) - 1;
-                if (lane == leader) base = n_first + atomicAdd(P.work_counter, (unsigned long long)__popcll(need_mask));
-                base = __shfl(base, leader, 64);
-            }
-            uint64_t idx = 0;
-            if (need) {
-                idx = base + (uint64_t)__popcll(need_mask & lanemask_lt);
-                if (idx >= n_work) { state = kDone; need = false; }
-            }
-            const bool fresh_pkt = need && idx >= P.n_res;
+        // ---- refill idle lanes from the global queue -----------------------
+        const uint64_t need_mask = __ballot(state == kNeed);
+        if (pool.due(need_mask, __ballot(state == kLive) != 0ull)) {
+            bool need = state == kNeed;
+            const ColdParams C = cold_params();
+            const uint64_t n_res = C->n_res, n_work = n_res + C->n_packets;
+            const uint64_t idx = pool.take(need_mask, lane, lanemask_lt, C->work_counter, n_work, C->first_lanes);
+            if (need && idx >= n_work) { state = kDone; need = false; }
+            const bool fresh_pkt = need && idx >= n_res;
             const uint64_t fm = __ballot(fresh_pkt);
             if (fm && lane == __ffsll((long long)fm) - 1) count(kLcEmit, (uint64_t)__popcll(fm));
             if (need) {
-                const ColdParams C = cold_params();
                 CellFields F;
                 F.load(C);
                 if (!fresh_pkt) {
@@ -840,7 +822,7 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                     enter_cell(F);
                 } else {
                     // ---- emission (event 0) ----------------------------------
-                    pid = C->packet_offset + C->new_lo + (idx - C->n_res);
+                    pid = C->packet_offset + C->new_lo + (idx - n_res);
                     const uint32_t plo = (uint32_t)pid, phi = (uint32_t)(pid >> 32);
                     uint4 e0 = philox(make_uint4(0u, plo, phi, 0u), C->key0, C->key1);
                     if (C->source == KRT_SRC_BEAM_I) {

@@ -66,10 +66,11 @@ def test_channels_at_the_rounding_of_their_edges(gpu_ctx, ch):
         assert c["emis_dropped"] < c["scatterings"]
 
 
-@pytest.mark.parametrize("n", [1, 63, 65, 4095, 4097, 70001])
+@pytest.mark.parametrize("n", [1, 63, 65, 4095, 4097, 70001, 900001])
 def test_spread_packets_match_split_range(gpu_ctx, n):
-    """Few packets start spread over the waves; the same packets as two calls
-    start in other lanes and give the same sums."""
+    """Few packets start spread over the waves, more than the lanes come from the
+    shared pool in chunks; the same packets as two calls start in other lanes
+    and give the same sums."""
     from paper_2608_09340_amd import krt
     T = krt.Transport(W.sphere(5, 30.0, 1e-2, phase=1, emis=(16, -12.0, 12.0)), ctx=gpu_ctx)
     a = T.run(n, seed=3)
