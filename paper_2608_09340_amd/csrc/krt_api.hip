@@ -51,6 +51,8 @@ struct krt_ctx {
     double cont_key[3] = {-1.0, 0.0, 0.0};
     std::vector<krt_line_desc> lines;
     // scratch
+    float4 *rec = nullptr;           // cell records, filled at each run that uses them
+    int64_t rec_cap = 0;             // ... float4 allocated
     unsigned long long *work_counter = nullptr;
     double *level_consts = nullptr;
     double *level_power = nullptr;   // per-line partial and total powers of krt_levels_update
@@ -319,6 +321,7 @@ extern "C" void krt_destroy(krt_ctx *c) {
     if (c->cv_tab) (void)hipFree(c->cv_tab);
     if (c->cs_tab) (void)hipFree(c->cs_tab);
     if (c->cs_par) (void)hipFree(c->cs_par);
+    if (c->rec) (void)hipFree(c->rec);
     if (c->work_counter) (void)hipFree(c->work_counter);
     if (c->level_consts) (void)hipFree(c->level_consts);
     if (c->level_power) (void)hipFree(c->level_power);
@@ -545,6 +548,37 @@ static int run_parked(krt_ctx *c, const RunParams &P0, uint64_t n_packets, uint6
     return KRT_OK;
 }
 
+// Cell records (one line of memory per cell entered instead of one per field)
+// for a run of n packets, in quads of floats, or 0: read the fields where they
+// are.  Random cells miss the caches for every field, so where packets mostly
+// cross cells the walk is bound by the lines it fetches; the records are made
+// anew at each run (the fields are the caller's and may have changed), which
+// costs about 25 us for 128^3 cells, so they pay from some packets per cell on.
+// Used by the plain walk of profile mode 0 where a destruction or absorption
+// field makes short walks, and by the learned walk of the default geometry.
+constexpr int64_t kMaxRecordCells = int64_t(1) << 27;
+static int cell_record_quads(const RunParams &P, bool fused, bool other, uint64_t n) {
+    if (P.ncell > kMaxRecordCells || n < (uint64_t)P.ncell / 8) return 0;
+    if (fused) return P.vx ? 1 : 0;
+    if (other || P.profile_mode != 0 || P.tclass || P.bratio) return 0;
+    return (P.eps || P.kabs) ? 2 : 0;
+}
+// room for n float4 of records, kept by the context; false (and none) if the
+// device has no memory for them
+static bool reserve_records(krt_ctx *c, int64_t n) {
+    if (c->rec_cap >= n) return true;
+    if (c->rec) (void)hipFree(c->rec);
+    c->rec = nullptr;
+    c->rec_cap = 0;
+    if (hipMalloc(&c->rec, sizeof(float4) * (size_t)n) != hipSuccess) {
+        (void)hipGetLastError();
+        c->rec = nullptr;
+        return false;
+    }
+    c->rec_cap = n;
+    return true;
+}
+
 // krt_mc_run and krt_mc_run_noalloc: with noalloc the packet-pool counter and
 // the bin edges live in the per-device scratch array and the edges are staged
 // through a pinned block allocated at context creation, so the call allocates
@@ -755,6 +789,12 @@ static int mc_run_impl(krt_ctx *c, uint64_t n_packets, uint64_t seed, const krt_
     P.n_res = 0;
     P.new_lo = 0;
     P.park_budget = park_budget;
+    P.rec = nullptr;
+    const int quads = cell_record_quads(P, esc && !park && !noalloc && block <= 512, esc || noalloc, n_packets);
+    if (quads > 0 && reserve_records(c, nc * quads)) {
+        HIPCHK(c, launch_pack_fields(P, c->rec, quads, c->stream));
+        P.rec = c->rec;
+    }
     int grid = c->cus * per_cu;
     c->last_net_ms = 0.0f;
     c->last_rounds = 1;

@@ -58,6 +58,8 @@ struct RunParams {
     int bc[3];
     const float *k0, *vx, *vy, *vz, *eps;
     const float *kabs;  // [ncell] grey absorption coefficient, or null
+    const float4 *rec;  // the fields as one record per cell, or null: plain walk (profile mode 0, no
+                        // temperature) 2 quads (k0, v), (eps, kabs, 0, 0); fused walk 1 quad
     const float *alias_prob;
     const int *alias_idx;
     // line
@@ -150,6 +152,8 @@ constexpr int kParkQuads = 4;
 hipError_t launch_transport(const RunParams &P, int mode, int grid, int block, hipStream_t s);
 // the network call of each of n parked records, in place (learned escape)
 hipError_t launch_escape_call(const RunParams &P, uint4 *rec, uint64_t n, int grid, hipStream_t s);
+// fills rec, `quads` float4 a cell, from P's fields
+hipError_t launch_pack_fields(const RunParams &P, float4 *rec, int quads, hipStream_t s);
 hipError_t launch_finalize(const int64_t *raw, float *out, int64_t n, double scale, hipStream_t s);
 hipError_t launch_zero_i64(int64_t *p, int64_t n, hipStream_t s);
 hipError_t launch_saturation_check(const int64_t *p, int64_t n, uint32_t *status, hipStream_t s);

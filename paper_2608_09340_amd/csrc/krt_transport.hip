@@ -411,6 +411,8 @@ __device__ __forceinline__ float face_dist(float n, float f, float dx) {
 // opacity and the redistribution; frequencies return to reference units on
 // leaving the cell's frame.
 // kDip: dipole phase (plain walk; the learned escape is isotropic).
+// kRec: quads of the cell records (P.rec) that the fields are read from, 0 for
+// the fields' own arrays.
 //
 // A lane's iteration has three parts: the flight of every live lane (opacity,
 // distance to the face, position), then the cell change of the lanes that
@@ -433,7 +435,7 @@ __device__ __forceinline__ ColdParams cold_params() {
     return p;
 }
 
-template <int kMode, int kMaxThreads, int kProf = 0, bool kDip = false>
+template <int kMode, int kMaxThreads, int kProf = 0, bool kDip = false, int kRec = 0>
 __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) {
 #pragma clang fp contract(off)
     constexpr bool kEsc = kMode == kModeFused, kPark = kMode == kModePark;
@@ -524,16 +526,31 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
     // of widths its frequency scale, damping, sampler threshold and table set
     struct CellFields {
         const float *k0, *vx, *vy, *vz, *eps, *kabs;
+        const float4 *rec;
         __device__ __forceinline__ void load(ColdParams C) {
+            if constexpr (kRec > 0) {
+                rec = C->rec;
+                return;
+            }
             k0 = C->k0; vx = C->vx; vy = C->vy; vz = C->vz; eps = C->eps; kabs = C->kabs;
             asm volatile("" : "+s"(k0), "+s"(vx), "+s"(vy), "+s"(vz), "+s"(eps), "+s"(kabs));
         }
     };
     auto enter_cell = [&](const CellFields &F) __attribute__((always_inline)) {
-        k0c = F.k0[cell];
-        if (F.vx) { vxc = F.vx[cell]; vyc = F.vy[cell]; vzc = F.vz[cell]; }
-        if (F.eps) epsc = F.eps[cell];
-        if (F.kabs) kabsc = F.kabs[cell];
+        if constexpr (kRec > 0) {
+            const float4 *r = F.rec + (int64_t)cell * kRec;
+            const float4 q = r[0];
+            k0c = q.x; vxc = q.y; vyc = q.z; vzc = q.w;
+            if constexpr (kRec == 2) {
+                const float2 e = *reinterpret_cast<const float2 *>(r + 1);
+                epsc = e.x; kabsc = e.y;
+            }
+        } else {
+            k0c = F.k0[cell];
+            if (F.vx) { vxc = F.vx[cell]; vyc = F.vy[cell]; vzc = F.vz[cell]; }
+            if (F.eps) epsc = F.eps[cell];
+            if (F.kabs) kabsc = F.kabs[cell];
+        }
         if constexpr (kProf == 3) {
             const int k = P.tclass[cell];
             const float4 cp = P.cls_par[k];
@@ -1142,6 +1159,18 @@ __global__ void saturation_check_kernel(const int64_t *p, int64_t n, uint32_t *s
     if (__ballot(bad) != 0ull && __lane_id() == 0) atomicOr(status, (uint32_t)KRT_ST_SATURATE_BIT);
 }
 
+// One record per cell of the fields a packet needs on entering it: (k0, v) and,
+// with quads = 2, (eps, kabs, 0, 0).
+__global__ void pack_fields_kernel(const float *k0, const float *vx, const float *vy, const float *vz, const float *eps,
+                                   const float *kabs, float4 *rec, int quads, int64_t n) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (; i < n; i += stride) {
+        rec[i * quads] = make_float4(k0[i], vx ? vx[i] : 0.0f, vx ? vy[i] : 0.0f, vx ? vz[i] : 0.0f);
+        if (quads == 2) rec[2 * i + 1] = make_float4(eps ? eps[i] : 0.0f, kabs ? kabs[i] : 0.0f, 0.0f, 0.0f);
+    }
+}
+
 __global__ void zero_i64_kernel(int64_t *p, int64_t n) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -1216,9 +1245,9 @@ static_assert(kMaxTransportLds <= 160 * 1024, "a workgroup's LDS fits one CU (16
 static_assert((kTabFloats + kEdgeFloats) % 4 == 0 && (kTabFloats + kChanEdgeFloats + kMlpFwdBytes / 4) % 4 == 0,
               "the counters are aligned");
 
-template <int kMode, int kMaxThreads, int kProf, bool kDip>
+template <int kMode, int kMaxThreads, int kProf, bool kDip, int kRec = 0>
 static hipError_t launch_transport_t(const RunParams &P, int grid, int block, size_t lds, hipStream_t s) {
-    auto fn = mc_transport_kernel<kMode, kMaxThreads, kProf, kDip>;
+    auto fn = mc_transport_kernel<kMode, kMaxThreads, kProf, kDip, kRec>;
     static std::atomic<bool> attr_set{false};  // the most any launch of this variant asks for
     if (!attr_set.load()) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
@@ -1230,13 +1259,13 @@ static hipError_t launch_transport_t(const RunParams &P, int grid, int block, si
     return hipGetLastError();
 }
 
-template <int kProf>
+template <int kProf, int kRec = 0>
 static hipError_t launch_plain(const RunParams &P, int grid, int block, hipStream_t s) {
     // tables and both edge sets; with dipole phase the emissivity windows' sums
     if (P.phase == KRT_PHASE_DIPOLE_I)
-        return launch_transport_t<kModePlain, 1024, kProf, true>(
+        return launch_transport_t<kModePlain, 1024, kProf, true, kRec>(
             P, grid, block, kPlainLds + (P.emis_raw ? sizeof(int64_t) * kEmisSlots * (size_t)block : 0), s);
-    return launch_transport_t<kModePlain, 1024, kProf, false>(P, grid, block, kPlainLds, s);
+    return launch_transport_t<kModePlain, 1024, kProf, false, kRec>(P, grid, block, kPlainLds, s);
 }
 
 hipError_t launch_transport(const RunParams &P0, int mode, int grid, int block, hipStream_t s) {
@@ -1246,6 +1275,7 @@ hipError_t launch_transport(const RunParams &P0, int mode, int grid, int block, 
         // compiled for the block size: up to 512 lanes 256 VGPRs (2 waves per SIMD;
         // the default), up to 768 lanes 168 VGPRs (spills, 3 waves), above that
         // 128 (4 waves, heavy spills)
+        if (block <= 512 && P.rec) return launch_transport_t<kModeFused, 512, 0, false, 1>(P, grid, block, kFusedLds, s);
         if (block <= 512) return launch_transport_t<kModeFused, 512, 0, false>(P, grid, block, kFusedLds, s);
         if (block <= 768) return launch_transport_t<kModeFused, 768, 0, false>(P, grid, block, kFusedLds, s);
         return launch_transport_t<kModeFused, 1024, 0, false>(P, grid, block, kFusedLds, s);
@@ -1257,7 +1287,7 @@ hipError_t launch_transport(const RunParams &P0, int mode, int grid, int block, 
     if (P.tclass) return launch_plain<3>(P, grid, block, s);
     if (P.profile_mode == 1) return launch_plain<1>(P, grid, block, s);
     if (P.profile_mode == 2) return launch_plain<2>(P, grid, block, s);
-    return launch_plain<0>(P, grid, block, s);
+    return P.rec ? launch_plain<0, 2>(P, grid, block, s) : launch_plain<0>(P, grid, block, s);
 }
 
 // ------------------------------------------------------------ call kernel ---
@@ -1352,6 +1382,13 @@ hipError_t launch_finalize(const int64_t *raw, float *out, int64_t n, double sca
     if (n <= 0) return hipSuccess;
     int grid = (int)std::min<int64_t>((n + 255) / 256, 65536);
     hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(256), 0, s, raw, out, n, scale);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_fields(const RunParams &P, float4 *rec, int quads, hipStream_t s) {
+    const int grid = (int)std::min<int64_t>(((int64_t)P.ncell + 255) / 256, 16384);
+    hipLaunchKernelGGL(pack_fields_kernel, dim3(grid), dim3(256), 0, s, P.k0, P.vx, P.vy, P.vz, P.eps, P.kabs, rec,
+                       quads, (int64_t)P.ncell);
     return hipGetLastError();
 }
 

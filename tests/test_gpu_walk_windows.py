@@ -100,3 +100,26 @@ def test_records_do_not_depend_on_their_lanes(gpu_ctx, n):
     b = np.concatenate([rec(m, 40 + o) for m, o in ((k, 0), (n - k, k)) if m])
     assert np.array_equal(a, b)
     assert np.all(a[:, 18] == 1.0) and np.all(a[:, 19] == 0.0)
+
+
+@pytest.mark.parametrize("vel", [False, True])
+@pytest.mark.parametrize("fields", ["eps", "kabs", "both"])
+def test_cell_records_match_the_fields(gpu_ctx, vel, fields):
+    """A run that reads its cells from packed records (enough packets per cell)
+    and the no-allocation entry point, which reads the fields' own arrays, walk
+    the same packets; the fields may change between runs."""
+    from paper_2608_09340_amd import krt
+    rng = np.random.default_rng(4)
+    p = W.sphere(9, 40.0, 1e-2, phase=0, emis=(8, -9.0, 9.0), vmax=3.0 if vel else 0.0, jbar=True)
+    nc = 9 ** 3
+    if fields != "kabs":
+        p["grid"]["eps"] = (0.2 * rng.random(nc)).astype(np.float32)
+    if fields != "eps":
+        p["grid"]["kabs"] = (2.0 * rng.random(nc)).astype(np.float32)
+    T = krt.Transport(p, ctx=gpu_ctx)
+    for _ in range(2):
+        a, b = T.run(4000, seed=2), T.run(4000, seed=2, noalloc=True)
+        assert a["counters"] == b["counters"] and a["counters"]["destroyed"] > 0
+        for key in ("spec_raw", "emis_raw", "jbar_raw"):
+            assert np.array_equal(a[key], b[key]), key
+        T.k0.mul_(0.5)
