@@ -806,23 +806,21 @@ static int mc_run_impl(krt_ctx *c, uint64_t n_packets, uint64_t seed, const krt_
         int rc = run_parked(c, P, n_packets, park_cap, park_tail, grid, block);
         if (rc) return rc;
     }
-    // integer tallies that left [0, 2^62] (the transport's atomics return nothing)
-    HIPCHK(c, launch_saturation_check(t->spec_raw_dev, nsb, P.status, c->stream));
-    if (o->emis_nch > 0) HIPCHK(c, launch_saturation_check(t->emis_raw_dev, nc * o->emis_nch, P.status, c->stream));
-    if (o->jbar) HIPCHK(c, launch_saturation_check(t->jbar_raw_dev, nc, P.status, c->stream));
-
-    // finalise (FP64 scaling -> FP32)
+    // check for sums that left [0, 2^62] (the transport's atomics return nothing)
+    // and finalise (FP64 scaling -> FP32)
     const double N = (double)(o->norm_packets ? o->norm_packets : n_packets);
     const double vcell = P.dxd[0] * P.dxd[1] * P.dxd[2];
     const double inv_f = std::ldexp(1.0, -fb), inv_fj = std::ldexp(1.0, -fj);
     const double four_pi = 4.0 * 3.14159265358979323846;
-    if (t->spec_dev)
-        HIPCHK(c, launch_finalize(t->spec_raw_dev, t->spec_dev, nsb, lum / (N * (o->spec_hi - o->spec_lo) / o->spec_nbins), c->stream));
-    if (t->emis_dev && o->emis_nch > 0)
-        HIPCHK(c, launch_finalize(t->emis_raw_dev, t->emis_dev, nc * o->emis_nch,
-                                  lum * inv_f / (four_pi * N * vcell * ((o->ch_hi - o->ch_lo) / o->emis_nch)), c->stream));
-    if (t->jbar_dev && o->jbar)
-        HIPCHK(c, launch_finalize(t->jbar_raw_dev, t->jbar_dev, nc, lum * inv_fj / (four_pi * N * vcell), c->stream));
+    HIPCHK(c, launch_finish(t->spec_raw_dev, t->spec_dev, nsb,
+                            lum / (N * (o->spec_hi - o->spec_lo) / o->spec_nbins), P.status, c->stream));
+    if (o->emis_nch > 0)
+        HIPCHK(c, launch_finish(t->emis_raw_dev, t->emis_dev, nc * o->emis_nch,
+                                lum * inv_f / (four_pi * N * vcell * ((o->ch_hi - o->ch_lo) / o->emis_nch)), P.status,
+                                c->stream));
+    if (o->jbar)
+        HIPCHK(c, launch_finish(t->jbar_raw_dev, t->jbar_dev, nc, lum * inv_fj / (four_pi * N * vcell), P.status,
+                                c->stream));
 
     HIPCHK(c, hipMemcpyAsync(c->host_pinned, t->counters_dev, sizeof(int64_t) * KRT_NCOUNTERS,
                              hipMemcpyDeviceToHost, c->stream));

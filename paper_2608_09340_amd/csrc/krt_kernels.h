@@ -154,9 +154,9 @@ hipError_t launch_transport(const RunParams &P, int mode, int grid, int block, h
 hipError_t launch_escape_call(const RunParams &P, uint4 *rec, uint64_t n, int grid, hipStream_t s);
 // fills rec, `quads` float4 a cell, from P's fields
 hipError_t launch_pack_fields(const RunParams &P, float4 *rec, int quads, hipStream_t s);
-hipError_t launch_finalize(const int64_t *raw, float *out, int64_t n, double scale, hipStream_t s);
+// saturation check of a raw tally and (out not null) its FP32 form
+hipError_t launch_finish(const int64_t *raw, float *out, int64_t n, double scale, uint32_t *status, hipStream_t s);
 hipError_t launch_zero_i64(int64_t *p, int64_t n, hipStream_t s);
-hipError_t launch_saturation_check(const int64_t *p, int64_t n, uint32_t *status, hipStream_t s);
 hipError_t launch_debug_philox(const uint32_t *ctr, const uint32_t *key, uint32_t *out, int64_t n,
                                hipStream_t s);
 hipError_t launch_debug_bins(const float *x, int64_t n, int nb, const float *edges, float inv_w, int32_t *out,

@@ -1144,18 +1144,27 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
 }
 
 // -------------------------------------------------------------- finalise ---
-__global__ void finalize_kernel(const int64_t *raw, float *out, int64_t n, double scale) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) out[i] = (float)((double)raw[i] * scale);
-}
-
-// Sets the saturation bit if any integer tally left [0, 2^62].
-__global__ void saturation_check_kernel(const int64_t *p, int64_t n, uint32_t *status) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// One pass over a raw tally after the transport: sets the saturation bit if a
+// sum left [0, 2^62] (the transport's atomics return nothing), and with kOut
+// writes its FP32 form (FP64 scaling).  A stream bound by memory, so the check
+// and the scaling share one read.  kStream: past the 256 MB last-level cache
+// the accesses are marked as not to be kept.  128^3 x 64 sums, 1.6 GB: check and
+// scaling apart 237 + 264 us, together 267, streaming 244 (6.6 TB/s; 16 bytes a
+// lane 257 to 324 with the launch's shape).
+template <bool kOut, bool kStream>
+__global__ void __launch_bounds__(256) finish_kernel(const int64_t *raw, float *out, int64_t n, double scale,
+                                                     uint32_t *status) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     bool bad = false;
-    for (; i < n; i += stride) bad |= (p[i] < 0) || (p[i] > (int64_t(1) << 62));
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const int64_t v = kStream ? __builtin_nontemporal_load(raw + i) : raw[i];
+        bad |= (v < 0) | (v > (int64_t(1) << 62));
+        if constexpr (kOut) {
+            const float o = (float)((double)v * scale);
+            if (kStream) __builtin_nontemporal_store(o, out + i);
+            else out[i] = o;
+        }
+    }
     if (__ballot(bad) != 0ull && __lane_id() == 0) atomicOr(status, (uint32_t)KRT_ST_SATURATE_BIT);
 }
 
@@ -1378,10 +1387,13 @@ hipError_t launch_escape_call(const RunParams &P, uint4 *rec, uint64_t n, int gr
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const int64_t *raw, float *out, int64_t n, double scale, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    int grid = (int)std::min<int64_t>((n + 255) / 256, 65536);
-    hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(256), 0, s, raw, out, n, scale);
+hipError_t launch_finish(const int64_t *raw, float *out, int64_t n, double scale, uint32_t *status, hipStream_t s) {
+    if (n <= 0 || !raw) return hipSuccess;
+    const int grid = (int)std::min<int64_t>((n + 255) / 256, 65536);
+    const bool stream = n > (int64_t(1) << 25);  // 256 MB of sums
+    auto fn = out ? (stream ? finish_kernel<true, true> : finish_kernel<true, false>)
+                  : (stream ? finish_kernel<false, true> : finish_kernel<false, false>);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(256), 0, s, raw, out, n, scale, status);
     return hipGetLastError();
 }
 
@@ -1389,13 +1401,6 @@ hipError_t launch_pack_fields(const RunParams &P, float4 *rec, int quads, hipStr
     const int grid = (int)std::min<int64_t>(((int64_t)P.ncell + 255) / 256, 16384);
     hipLaunchKernelGGL(pack_fields_kernel, dim3(grid), dim3(256), 0, s, P.k0, P.vx, P.vy, P.vz, P.eps, P.kabs, rec,
                        quads, (int64_t)P.ncell);
-    return hipGetLastError();
-}
-
-hipError_t launch_saturation_check(const int64_t *p, int64_t n, uint32_t *status, hipStream_t s) {
-    if (n <= 0 || !p) return hipSuccess;
-    int grid = (int)std::min<int64_t>((n + 255) / 256, 16384);
-    hipLaunchKernelGGL(saturation_check_kernel, dim3(grid), dim3(256), 0, s, p, n, status);
     return hipGetLastError();
 }
 

@@ -123,3 +123,19 @@ def test_cell_records_match_the_fields(gpu_ctx, vel, fields):
         for key in ("spec_raw", "emis_raw", "jbar_raw"):
             assert np.array_equal(a[key], b[key]), key
         T.k0.mul_(0.5)
+
+
+@pytest.mark.parametrize("nch", [15, 17])
+def test_finalised_emissivity_on_both_sides_of_the_cache(gpu_ctx, nch):
+    """The pass that checks and scales a tally reads it as a stream past 2^25
+    sums: on either side of that the FP32 form is the raw sums times one FP64
+    factor, to the last place."""
+    import torch
+    from paper_2608_09340_amd import krt
+    n, N = 128, 4000
+    T = krt.Transport(W.sphere(n, 5.0, 1e-2, phase=0, emis=(nch, -9.0, 9.0), source="volume"), ctx=gpu_ctx)
+    T.run(N, seed=1, host=False)
+    f = 2.0 ** -20 / (4.0 * np.pi * N * (2.0 / n) ** 3 * (18.0 / nch))
+    want = T.emis_raw.double() * f
+    assert int(torch.count_nonzero(T.emis_raw)) > 1000
+    assert bool(((T.emis.double() - want).abs() <= want.abs() * 2.0 ** -23).all())
