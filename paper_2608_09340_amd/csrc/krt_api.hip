@@ -74,11 +74,10 @@ struct krt_ctx {
     float esc_lt_lo = 1.0f, esc_lt_hi = -1.0f;  // log10 tau_c range of its training records
     float esc_ld_min = 0.0f;                    // smallest log10 depth of its training records
     float *mlp_p = nullptr, *mlp_m = nullptr, *mlp_v = nullptr, *mlp_g = nullptr, *mlp_norm = nullptr;
-    float *mlp_loss = nullptr, *mlp_u = nullptr;
+    float *mlp_loss = nullptr;
     float *mlp_part = nullptr;                 // [kGradSplits][kNParams] split gradients
-    uint16_t *mlp_act = nullptr;               // [kActRowsAll][mlp_act_cap] bf16 activation store
-    int64_t mlp_act_cap = 0;
-    int32_t *mlp_idx = nullptr;
+    unsigned char *mlp_act = nullptr;          // activation store of a batch, kActTiles operand tiles per 32 samples
+    uint32_t *mlp_rows = nullptr;              // a batch's rows, kRowDw dwords each
     int mlp_batch_cap = 0;
     int mlp_step = 0;
     unsigned char *mlp_blob = nullptr, *mlp_img = nullptr;
@@ -328,7 +327,7 @@ extern "C" void krt_destroy(krt_ctx *c) {
     if (c->host_pinned) (void)hipHostFree(c->host_pinned);
     if (c->host_edges) (void)hipHostFree(c->host_edges);
     for (void *p : {(void *)c->mlp_p, (void *)c->mlp_m, (void *)c->mlp_v, (void *)c->mlp_g, (void *)c->mlp_norm,
-                    (void *)c->mlp_loss, (void *)c->mlp_u, (void *)c->mlp_idx, (void *)c->mlp_blob,
+                    (void *)c->mlp_loss, (void *)c->mlp_rows, (void *)c->mlp_blob,
                     (void *)c->mlp_img, (void *)c->mlp_calsum, (void *)c->mlp_part, (void *)c->mlp_act})
         if (p) (void)hipFree(p);
     if (c->edges) (void)hipFree(c->edges);
@@ -1188,22 +1187,17 @@ int mlp_zero_state(krt_ctx *c) {
     return KRT_OK;
 }
 
-// batch buffers: indices, levels [batch][5] and the activation store with
-// room for the batch rounded up to 32 samples
+// batch buffers: rows and activation store, for the batch rounded up to 32 samples
 int mlp_ensure_batch(krt_ctx *c, int batch) {
     if (batch <= c->mlp_batch_cap) return KRT_OK;
-    for (void *p : {(void *)c->mlp_idx, (void *)c->mlp_u, (void *)c->mlp_act})
+    for (void *p : {(void *)c->mlp_rows, (void *)c->mlp_act})
         if (p) (void)hipFree(p);
-    c->mlp_idx = nullptr;
-    c->mlp_u = nullptr;
+    c->mlp_rows = nullptr;
     c->mlp_act = nullptr;
     c->mlp_batch_cap = 0;
-    const int64_t cap = 32 * (((int64_t)batch + 31) / 32);
-    HIPCHK(c, hipMalloc(&c->mlp_idx, sizeof(int32_t) * batch));
-    HIPCHK(c, hipMalloc(&c->mlp_u, sizeof(float) * 5 * (size_t)batch));
-    HIPCHK(c, hipMalloc(&c->mlp_act, sizeof(uint16_t) * (size_t)kActRowsAll * cap));
-    HIPCHK(c, launch_mlp_act_init(c->mlp_act, cap, c->stream));
-    c->mlp_act_cap = cap;
+    const size_t chunks = ((size_t)batch + 31) / 32;
+    HIPCHK(c, hipMalloc(&c->mlp_rows, sizeof(uint32_t) * kRowDw * 32 * chunks));
+    HIPCHK(c, hipMalloc(&c->mlp_act, (size_t)kActTiles * kTileBytes * chunks));
     c->mlp_batch_cap = batch;
     return KRT_OK;
 }
@@ -1299,7 +1293,8 @@ extern "C" int krt_escape_fit_norm(krt_ctx *c, const float *samples_dev, uint64_
     if (!c->mlp_ready) return fail(c, KRT_ESTATE, "call krt_escape_init first");
     if (!samples_dev || n == 0) return fail(c, KRT_EINVAL, "bad norm args");
     HIPCHK(c, hipSetDevice(c->device));
-    HIPCHK(c, launch_mlp_norm(samples_dev, (int64_t)n, c->mlp_norm, c->stream));
+    HIPCHK(c, launch_mlp_norm(samples_dev, (int64_t)n, reinterpret_cast<double *>(c->mlp_part), c->mlp_norm,
+                              c->stream));
     // a new normalisation invalidates the calibration of ln E[N_s]
     static_assert(kNormCal % 2 == 0 && kNCal % 2 == 0, "calibration block is int64-aligned");
     HIPCHK(c, launch_zero_i64(reinterpret_cast<int64_t *>(c->mlp_norm + kNormCal), kNCal / 2, c->stream));
@@ -1330,8 +1325,9 @@ extern "C" int krt_escape_grad(krt_ctx *c, const float *samples_dev, const int32
     int rc = mlp_ensure_batch(c, batch);
     if (rc) return rc;
     HIPCHK(c, launch_zero_i64(reinterpret_cast<int64_t *>(c->mlp_loss), 1, c->stream));
-    HIPCHK(c, launch_mlp_grad(c->mlp_blob, samples_dev, idx_dev, u_dev, batch, c->mlp_act, c->mlp_act_cap,
-                              c->mlp_part, c->mlp_loss, c->stream));
+    HIPCHK(c, launch_mlp_rows(samples_dev, idx_dev, u_dev, batch, c->mlp_norm, c->mlp_rows, c->stream));
+    HIPCHK(c, launch_mlp_grad(c->mlp_blob, c->mlp_rows, batch, c->mlp_act, c->mlp_part, c->mlp_loss, nullptr,
+                              c->stream));
     HIPCHK(c, launch_mlp_gsum(c->mlp_part, grad_out_dev, c->stream));
     if (loss_out_dev) HIPCHK(c, hipMemcpyAsync(loss_out_dev, c->mlp_loss, sizeof(float), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1350,15 +1346,25 @@ extern "C" int krt_escape_train(krt_ctx *c, const float *samples_dev, uint64_t n
     if (rc) return rc;
     // each step's loss is summed straight into its slot of the history
     if (loss_hist_dev) HIPCHK(c, hipMemsetAsync(loss_hist_dev, 0, sizeof(float) * (size_t)steps, c->stream));
+    // step k's gradient launch draws step k + 1's rows
+    RowDraw D;
+    D.rec = samples_dev;
+    D.n = (int64_t)n;
+    D.k0 = (uint32_t)seed;
+    D.k1 = (uint32_t)(seed >> 32);
+    D.step = (uint32_t)c->mlp_step + 1;
+    D.batch = batch;
+    D.norm = c->mlp_norm;
+    D.rows = c->mlp_rows;
+    HIPCHK(c, launch_mlp_draw(D, c->stream));
     for (int s = 0; s < steps; ++s) {
         c->mlp_step += 1;
-        HIPCHK(c, launch_mlp_batch((int64_t)n, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)c->mlp_step, batch,
-                                   c->mlp_idx, c->mlp_u, c->stream));
-        HIPCHK(c, launch_mlp_grad(c->mlp_blob, samples_dev, c->mlp_idx, c->mlp_u, batch, c->mlp_act, c->mlp_act_cap,
-                                  c->mlp_part, loss_hist_dev ? loss_hist_dev + s : nullptr, c->stream));
-        HIPCHK(c, launch_mlp_adam(c->mlp_p, c->mlp_m, c->mlp_v, c->mlp_part, (float)lr, c->mlp_step, c->stream));
-        HIPCHK(c, launch_mlp_pack(c->mlp_p, c->mlp_norm, c->mlp_blob, (s == steps - 1) ? c->mlp_img : nullptr,
-                                  c->stream));
+        D.step = (uint32_t)c->mlp_step + 1;
+        const bool last = s == steps - 1;
+        HIPCHK(c, launch_mlp_grad(c->mlp_blob, c->mlp_rows, batch, c->mlp_act, c->mlp_part,
+                                  loss_hist_dev ? loss_hist_dev + s : nullptr, last ? nullptr : &D, c->stream));
+        HIPCHK(c, launch_mlp_adam(c->mlp_p, c->mlp_m, c->mlp_v, c->mlp_part, (float)lr, c->mlp_step, c->mlp_blob,
+                                  last ? c->mlp_img : nullptr, c->stream));
     }
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return KRT_OK;

@@ -271,53 +271,55 @@ __global__ void mlp_init_kernel(float *p, uint32_t k0, uint32_t k1) {
     p[i] = bias ? 0.0f : u * sqrtf(6.0f / fan_in);
 }
 
-// Pack the FP32 master parameters into BF16 A-operand tiles (with the chunk
-// permutation kperm of the reduction index) + FP32 biases + normalisation.
-// One thread per (tile, lane).
-__global__ void mlp_pack_kernel(const float *p, const float *norm, unsigned char *blob) {
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid < kTilesAll * 64) {
-        const int t = gid / 64, lane = gid % 64;
-        const int i = lane % 16, g = lane / 16;
-        uint16_t *dst = reinterpret_cast<uint16_t *>(blob + t * kTileBytes + lane * 16);
-        for (int j = 0; j < 8; ++j) {
-            const int kp = 8 * g + j;  // reduction slot
-            float w = 0.0f;
-            if (t < kTileFwdL2) {  // L1 fwd: W1^T, inputs in natural order, level residual slots tied
-                const int mo = t - kTileFwdL1;
-                if (kp < kMlpIn) w = p[kPW1 + kp * kMlpHid + 16 * mo + i];
-                else if (kp < kMlpOperandIn) w = p[kPW1 + (kMlpLevelIn + kp - kMlpResIn) * kMlpHid + 16 * mo + i];
-            } else if (t < kTileFwdL4) {  // L2/L3 fwd: tile mo*4+c, A[i][k'] = W[kperm(c,k')][16mo+i]
-                const int base = (t < kTileFwdL3) ? kPW2 : kPW3;
-                const int tt = t - ((t < kTileFwdL3) ? kTileFwdL2 : kTileFwdL3);
-                const int mo = tt / 4, c = tt % 4;
-                w = p[base + kperm(c, kp) * kMlpHid + 16 * mo + i];
-            } else if (t < kTilesFwd) {  // L4 fwd: tile 4 ot + c, A[i][k'] = W4[kperm(c,k')][16 ot + i]
-                const int ot = (t - kTileFwdL4) / 4, c = (t - kTileFwdL4) % 4;
-                w = p[kPW4 + kperm(c, kp) * kMlpOut + 16 * ot + i];
-            } else if (t < kTileBwdL3) {  // L4 bwd: tile mi, A[i][k'] = W4[16mi+i][kperm(0,k')]
-                const int mi = t - kTileBwdL4;
-                w = p[kPW4 + (16 * mi + i) * kMlpOut + kperm(0, kp)];
-            } else {  // L3/L2 bwd: tile mi*4+c, A[i][k'] = W[16mi+i][kperm(c,k')]
-                const int base = (t < kTileBwdL2) ? kPW3 : kPW2;
-                const int tt = t - ((t < kTileBwdL2) ? kTileBwdL3 : kTileBwdL2);
-                const int mi = tt / 4, c = tt % 4;
-                w = p[base + (16 * mi + i) * kMlpHid + kperm(c, kp)];
-            }
-            dst[j] = f2bf(w);
+// Slot (lane group g, entry j) of feature f of a 32-wide chunk: kperm's inverse.
+__device__ __forceinline__ int slot_of(int f) { return f < 16 ? 8 * (f >> 2) + (f & 3) : 8 * ((f - 16) >> 2) + 4 + (f & 3); }
+
+// Parameter i's value into every place the packed blob holds it: a weight's
+// bfloat16 slot in its forward tile and (layers 2-4) in its backward tile, a
+// quantile level's weight of layer 1 also in the slot of that level's
+// residual, a bias in FP32 behind the tiles.
+__device__ __forceinline__ void pack_param(unsigned char *blob, int i, float v) {
+    uint16_t *tiles = reinterpret_cast<uint16_t *>(blob);
+    float *bias = reinterpret_cast<float *>(blob + kTilesAll * kTileBytes);
+    auto put = [&](int tile, int row, int slot) {
+        tiles[tile * (kTileBytes / 2) + (16 * (slot >> 3) + row) * 8 + (slot & 7)] = f2bf(v);
+    };
+    if (i < kPB1) {
+        const int in = i / kMlpHid, out = i % kMlpHid;
+        put(kTileFwdL1 + out / 16, out % 16, in);
+        if (in >= kMlpLevelIn && in < kMlpLevelIn + kMlpOperandIn - kMlpResIn)
+            put(kTileFwdL1 + out / 16, out % 16, kMlpResIn + in - kMlpLevelIn);
+    } else if (i < kPW2) {
+        bias[i - kPB1] = v;
+    } else if (i < kPB3) {  // layers 2 and 3
+        const bool l3 = i >= kPW3;
+        const int k = i - (l3 ? kPW3 : kPW2);
+        if (k >= kMlpHid * kMlpHid) {
+            bias[(l3 ? 2 : 1) * kMlpHid + k - kMlpHid * kMlpHid] = v;
+        } else {
+            const int in = k / kMlpHid, out = k % kMlpHid;
+            put((l3 ? kTileFwdL3 : kTileFwdL2) + (out / 16) * 4 + in / 32, out % 16, slot_of(in % 32));
+            put((l3 ? kTileBwdL3 : kTileBwdL2) + (in / 16) * 4 + out / 32, in % 16, slot_of(out % 32));
         }
+    } else if (i < kPW4) {
+        bias[2 * kMlpHid + i - kPB3] = v;
+    } else if (i < kPB4) {
+        const int in = (i - kPW4) / kMlpOut, out = (i - kPW4) % kMlpOut;
+        put(kTileFwdL4 + 4 * (out / 16) + in / 32, out % 16, slot_of(in % 32));
+        put(kTileBwdL4 + in / 16, in % 16, slot_of(out));
+    } else {
+        bias[3 * kMlpHid + i - kPB4] = v;
     }
-    // biases and normalisation (b1 b2 b3 b4 norm)
-    float *fb = reinterpret_cast<float *>(blob + kTilesAll * kTileBytes);
-    if (gid < kBiasFloats) {
-        float b;
-        if (gid < kMlpHid) b = p[kPB1 + gid];
-        else if (gid < 2 * kMlpHid) b = p[kPB2 + gid - kMlpHid];
-        else if (gid < 3 * kMlpHid) b = p[kPB3 + gid - 2 * kMlpHid];
-        else b = p[kPB4 + gid - 3 * kMlpHid];
-        fb[gid] = b;
-    }
-    if (gid < kNNorm) fb[kBiasFloats + gid] = norm[gid];
+}
+
+// The whole blob from the FP32 master parameters: the parameters, the unused
+// operand slots of layer 1 (28-31, zero) and the normalisation.
+__global__ void mlp_pack_kernel(const float *p, const float *norm, unsigned char *blob) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kNParams) pack_param(blob, i, p[i]);
+    if (i < kMlpHid)
+        *reinterpret_cast<uint2 *>(blob + (kTileFwdL1 + i / 16) * kTileBytes + (48 + i % 16) * 16 + 8) = make_uint2(0u, 0u);
+    if (i < kNNorm) reinterpret_cast<float *>(blob + kTilesAll * kTileBytes)[kBiasFloats + i] = norm[i];
 }
 
 // Copy of the forward part (tiles + biases + norm) into one contiguous image,
@@ -354,212 +356,449 @@ __device__ __forceinline__ bool target_value(const float *r, int k, float &y) {
 __device__ __forceinline__ bool conditional_output(int k) { return k >= kOutYS && k <= kOutAlpha; }
 __device__ __forceinline__ bool used_output(int k) { return k <= kOutAlpha || (k >= kOutXAbs && k < kOutXAbs + 6); }
 
-// ----------------------------------------------------- forward + backward ---
-// Activation store of a training step, bf16 [row][cap] (samples contiguous):
-// H0 32 rows (inputs, row 24 = 1 for the bias), H1..H3 144 rows (leaky ReLU
-// activations, row 128 = 1), dZ1..dZ3 128 rows, dZ4 32 rows.  The constant
-// rows are written once when the store is allocated.
-constexpr int kActRowsH0 = 32, kActRowsH = 144;
-constexpr int kActH0 = 0, kActH1 = kActH0 + kActRowsH0, kActH2 = kActH1 + kActRowsH, kActH3 = kActH2 + kActRowsH,
-              kActZ1 = kActH3 + kActRowsH, kActZ2 = kActZ1 + kMlpHid, kActZ3 = kActZ2 + kMlpHid,
-              kActZ4 = kActZ3 + kMlpHid, kActRows = kActZ4 + kMlpOut;   // 880
-static_assert(kActRows == kActRowsAll, "activation store layout");
+// ----------------------------------------------------------- batch rows ---
+// Training quantile levels are uniform, clamped to the encoded range [1e-4, 1 - 1e-4]
+// (the pinball loss uses the clamped level too).
+__device__ __forceinline__ float train_level(uint32_t w) {
+    return fminf(fmaxf(u01(w), kLevelMin), 1.0f - kLevelMin);
+}
 
-// One wave per 16-sample block.  Row si uses record idx[si] and uq[5 si ..] =
-// (u_a, u_b, u_c, u_d, 1 for a conditional row); a conditional row takes the
-// record's exit face and exit frequency as inputs.  Losses (each averaged over
-// the batch): softmax cross-entropy for the exit face, logistic for the side
-// of x_out, pinball for the quantiles at their own levels (|x_out| of face F
-// only on records leaving through F), log-deviance for ln N_s.  Marginal rows
-// train outputs 0-8 and 16-21, conditional rows 9-12.  Samples past the batch
-// (up to the next multiple of 32) get zero gradients.
-__global__ void __launch_bounds__(256) mlp_fwdbwd_kernel(const unsigned char *blob, const float *rec,
-                                                         const int32_t *idx, const float *uq, int batch,
-                                                         uint16_t *act, int64_t cap, float *loss) {
-    const int lane = __lane_id(), w = threadIdx.x / 64;
-    const int block = blockIdx.x * (blockDim.x / 64) + w;
-    const int nblocks = 2 * ((batch + 31) / 32);
-    if (block >= nblocks) return;  // wave-uniform
+// One row of a batch as the gradient pass reads it: 32 dwords, the layer-1
+// operand (28 bfloat16 slots, four zero), then what the losses need.  Made
+// ahead of the pass, one thread a row, so the pass starts with one contiguous
+// load instead of an index, a scattered record, logarithms and inverse
+// hyperbolic sines in a chain (all zero past the batch and for invalid
+// records: no input and no gradient).
+constexpr int kRowFlags = 16;   // 1 live, 2 conditional, 4 x_out >= 0
+constexpr int kRowFace = 17;
+constexpr int kRowY = 18;       // normalised targets: ln N_s, ln <x^2>, the four conditional ones, |x_out|
+constexpr int kRowU = 25;       // the four quantile levels
+static_assert(kRowU + 4 <= kRowDw, "a row holds its levels");
+
+__device__ __forceinline__ void make_row(const float *r, float ua, float ub, float uc, float ud, bool cond,
+                                         const float *norm, uint32_t *row) {
+    uint32_t d[kRowDw] = {};
+    if (r[kRecValid] > 0.5f) {
+        const float xo = r[kRecXOut];
+        const int face = (int)r[kRecFace];
+        float in[kMlpIn];
+        mlp_inputs(r, ua, ub, uc, ud, cond, xo, face, in);
+        pack_inputs(in, d);
+        d[kRowFlags] = 1u | (cond ? 2u : 0u) | (xo >= 0.0f ? 4u : 0u);
+        d[kRowFace] = (uint32_t)face;
+        auto target = [&](int slot, int k) {
+            float raw = 0.0f;
+            (void)target_value(r, k, raw);
+            d[kRowY + slot] = __float_as_uint((raw - norm[k]) / norm[kMlpOut + k]);
+        };
+        if (cond) {
+#pragma unroll
+            for (int k = kOutYS; k <= kOutAlpha; ++k) target(2 + k - kOutYS, k);
+        } else {
+            target(0, kOutLogN);
+            target(1, kOutLogX2);
+            if (face >= 0 && face < 6) target(6, kOutXAbs + face);
+        }
+        d[kRowU] = __float_as_uint(ua);
+        d[kRowU + 1] = __float_as_uint(ub);
+        d[kRowU + 2] = __float_as_uint(uc);
+        d[kRowU + 3] = __float_as_uint(ud);
+    }
+    uint4 *o = reinterpret_cast<uint4 *>(row);
+#pragma unroll
+    for (int k = 0; k < kRowDw / 4; ++k) o[k] = make_uint4(d[4 * k], d[4 * k + 1], d[4 * k + 2], d[4 * k + 3]);
+}
+
+// Row i of a random batch: a record uniform over the set, four quantile levels
+// and the row kind (conditional with probability 1/3).
+__device__ __forceinline__ void draw_row(const RowDraw &D, int i) {
+    uint32_t *row = D.rows + (int64_t)kRowDw * i;
+    if (i >= D.batch) {
+        for (int k = 0; k < kRowDw; ++k) row[k] = 0u;
+        return;
+    }
+    const uint4 r = philox(make_uint4(D.step, (uint32_t)i, 0u, 9u), D.k0, D.k1);
+    const uint4 e = philox(make_uint4(D.step, (uint32_t)i, 1u, 9u), D.k0, D.k1);
+    const int32_t idx = (int32_t)__umulhi(r.x, (uint32_t)D.n);
+    make_row(D.rec + (int64_t)kRec * idx, train_level(r.y), train_level(r.z), train_level(r.w), train_level(e.y),
+             u01(e.x) < (1.0f / 3.0f), D.norm, row);
+}
+
+// Rows of a given batch: row i uses record idx[i] and uq[5 i ..] = (u_a, u_b,
+// u_c, u_d, 1 for a conditional row).
+__global__ void __launch_bounds__(64) mlp_rows_kernel(const float *rec, const int32_t *idx, const float *uq,
+                                                      int batch, const float *norm, uint32_t *rows) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 32 * ((batch + 31) / 32)) return;
+    uint32_t *row = rows + (int64_t)kRowDw * i;
+    if (i >= batch) {
+        for (int k = 0; k < kRowDw; ++k) row[k] = 0u;
+        return;
+    }
+    const float *q = uq + 5 * (int64_t)i;
+    make_row(rec + (int64_t)kRec * idx[i], q[0], q[1], q[2], q[3], q[4] > 0.5f, norm, row);
+}
+
+__global__ void __launch_bounds__(64) mlp_draw_kernel(RowDraw D) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 32 * ((D.batch + 31) / 32)) draw_row(D, i);
+}
+
+// ----------------------------------------------------- forward + backward ---
+// Activation store of a training step: per chunk of 32 samples 52 tiles of
+// 16 features x 32 samples in the operand order of the weight-gradient product
+// (lane l holds feature l%16, samples 8(l/16)..8(l/16)+7): H0 2 tiles (inputs,
+// row 24 = 1 for the bias), H1..H3 8 each, dZ1..dZ3 8 each, dZ4 2.
+constexpr int kActH0 = 0, kActH1 = 2, kActH2 = kActH1 + 8, kActH3 = kActH2 + 8, kActZ1 = kActH3 + 8,
+              kActZ2 = kActZ1 + 8, kActZ3 = kActZ2 + 8, kActZ4 = kActZ3 + 8;
+static_assert(kActZ4 + 2 == kActTiles, "activation store layout");
+
+// Forward and backward pass of one chunk of 32 samples by one workgroup of
+// eight waves.  Losses (each averaged over the batch): softmax cross-entropy
+// for the exit face, logistic for the side of x_out, pinball for the quantiles
+// at their own levels (|x_out| of face F only on records leaving through F),
+// log-deviance for ln N_s.  Marginal rows train outputs 0-8 and 16-21,
+// conditional rows 9-12.
+//
+// A batch of 8192 is 256 chunks, one workgroup per compute unit and two waves
+// per SIMD: the chain of layers bounds it, so the chain is cut short.  Wave w
+// owns row tile w of every layer for both 16-sample blocks (two products per
+// weight tile) and passes its activations to the others through LDS as the
+// next layer's operand: accumulators of tiles 2c, 2c + 1 side by side are
+// operand chunk c.  Weight tiles are asked for two layers before their
+// products (asked for all at once, the compute unit's 280 KB of loads held up
+// the first layer's: it ended after 3.2 of 6.8 us).  Each hidden product is
+// taken a second time with its operands exchanged: the same sums, with lane l
+// holding feature l%16 of four consecutive samples, the weight-gradient
+// product's order, for eight more matrix instructions a layer and wave instead
+// of a transpose through LDS and 2-byte stores.  The activations are written
+// through the L2 (agent scope), so the launch does not end with the write-back
+// of 13.6 MB: 11.9 us and 6.6 us for the product that reads them, against 14.2
+// and 6.7 with plain stores and 12.3 and 9.0 with nontemporal ones, which the
+// memory-side cache does not keep.  8192 samples: 28 us before (16 samples a
+// wave, rows of the store written 2 bytes at a time), 11.9 us now.
+__global__ void __launch_bounds__(512) mlp_fwdbwd_kernel(const unsigned char *blob, const uint32_t *rows, int batch,
+                                                         unsigned char *act, float *loss) {
+    __shared__ __align__(16) v4i16 ex[2][4][2][64][2];  // operand chunks between layers, double-buffered
+    __shared__ __align__(16) uint16_t tr[32][40];       // 32 features x 32 samples, turned (inputs, then dZ4)
+    __shared__ __align__(16) v4i16 dos[2][64][2];       // dZ4 as the output layer's operand
+    __shared__ float lsums[4];
+    const int lane = __lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const int s = lane % 16, g = lane / 16;
-    const int si = block * 16 + s;
-    const int ri = (si < batch) ? idx[si] : idx[0];
-    const float *r = rec + (int64_t)kRec * ri;
-    const bool live = si < batch && r[kRecValid] > 0.5f;
     const float *bias = reinterpret_cast<const float *>(blob + kTilesAll * kTileBytes);
     const float *norm = bias + kBiasFloats;
-    const float *ul = uq + 5 * (int64_t)(si < batch ? si : 0);
-    const float ua = ul[0], ub = ul[1], uc = ul[2], ud = ul[3];
-    const bool cond = ul[4] > 0.5f;
-    float in[kMlpIn];
-    mlp_inputs(r, ua, ub, uc, ud, cond, r[kRecXOut], (int)r[kRecFace], in);
-    if (!live)
-        for (int k = 0; k < kMlpIn; ++k) in[k] = 0.0f;
-    // the hidden activations go to the activation store as the forward pass
-    // makes them; the backward pass keeps only the sign of each
-    // pre-activation (bit 4 tile + component of zpos[layer]), all that the
-    // derivative of the leaky ReLU needs
-    const int64_t col = (int64_t)block * 16 + s;
-    auto store4 = [&](int row0, float a0, float a1, float a2, float a3) {  // rows row0 + 4g + j
-        uint16_t *p = act + (int64_t)(row0 + 4 * g) * cap + col;
-        p[0] = f2bf(a0); p[cap] = f2bf(a1); p[2 * cap] = f2bf(a2); p[3 * cap] = f2bf(a3);
+    const uint32_t *crow = rows + (int64_t)kRowDw * 32 * blockIdx.x;
+    unsigned char *ca = act + (int64_t)blockIdx.x * (kActTiles * kTileBytes);
+    const int ot = w & 1, ob = (w >> 1) & 1;  // output tile and block of waves 0-3
+
+    v8i16 x[4][2];  // operand chunks x blocks
+#pragma unroll
+    for (int b = 0; b < 2; ++b) x[0][b] = *reinterpret_cast<const v8i16 *>(crow + kRowDw * (16 * b + s) + 4 * g);
+    const v8i16 xt = *reinterpret_cast<const v8i16 *>(crow + kRowDw * (16 * (w & 1) + s) + 4 * g);
+    v4f32 bs[3];
+    float bt[3];
+    auto biases = [&](int l) {
+        bs[l] = ld4(bias + l * kMlpHid + 16 * w + 4 * g);
+        bt[l] = bias[l * kMlpHid + 16 * w + s];
     };
-    uint32_t zpos[3] = {0u, 0u, 0u};
-    auto epi = [&](int layer, int mo, const v4f32 &z) __attribute__((always_inline)) {
-        store4((layer == 0 ? kActH1 : (layer == 1 ? kActH2 : kActH3)) + 16 * mo, leaky(z.x), leaky(z.y), leaky(z.z),
-               leaky(z.w));
-        const uint32_t b = (z.x > 0.0f ? 1u : 0u) | (z.y > 0.0f ? 2u : 0u) | (z.z > 0.0f ? 4u : 0u) |
-                           (z.w > 0.0f ? 8u : 0u);
-        zpos[layer] |= b << (4 * mo);
+    v8i16 w1 = tileA(blob, kTileFwdL1 + w, lane), w2[4], w3[4], w4[4], v4, v3[4], v2[4];
+    auto tiles = [&](v8i16(&wt)[4], int tile) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) wt[c] = tileA(blob, tile + c, lane);
     };
-    v4f32 o, ob;
-    mlp_forward_block(blob, bias, xin_operand(in, lane), lane, epi, o, ob);
-    const float ov[8] = {o.x, o.y, o.z, o.w, ob.x, ob.y, ob.z, ob.w};
-    // the six face logits of this lane's sample (lanes s and s + 16)
-    float fl[6];
-    fl[0] = __shfl(o.x, s, 64); fl[1] = __shfl(o.y, s, 64); fl[2] = __shfl(o.z, s, 64); fl[3] = __shfl(o.w, s, 64);
-    fl[4] = __shfl(o.x, s + 16, 64); fl[5] = __shfl(o.y, s + 16, 64);
-    float mx = fl[0];
+    biases(0);
+    __builtin_amdgcn_sched_barrier(0);
+    tiles(w2, kTileFwdL2 + 4 * w);
+    biases(1);
+    __builtin_amdgcn_sched_barrier(0);
+    tiles(w3, kTileFwdL3 + 4 * w);
+    biases(2);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // the inputs' tiles of the store, turned by waves 0 and 1
+    if (w < 2) {
 #pragma unroll
-    for (int f = 1; f < 6; ++f) mx = fmaxf(mx, fl[f]);
-    float se = 0.0f, sm[6];
+        for (int j = 0; j < 8; ++j)
+            tr[8 * g + j][16 * w + s] = g < 3 ? (uint16_t)xt[j] : (uint16_t)(j == 0 ? 0x3F80 : 0);
+    }
+    auto put_turned = [&](int tile) {
+        *reinterpret_cast<v8i16 *>(ca + tile * kTileBytes + lane * 16) =
+            *reinterpret_cast<const v8i16 *>(&tr[16 * w + s][8 * g]);
+    };
+    // four samples 4g.. of block b of feature s: half of a lane's 16 bytes
+    unsigned char *cq = ca + ((g >> 1) * 16 + s) * 16 + (g & 1) * 8;
+    auto put_quad = [&](int tile, int b, v4i16 v) {
+        __hip_atomic_store(reinterpret_cast<uint64_t *>(cq + tile * kTileBytes + b * 512), __builtin_bit_cast(uint64_t, v),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto swap_ops = [&](int buf, v4i16 h0, v4i16 h1) {  // this wave's half chunks out, all chunks in
+        ex[buf][w >> 1][0][lane][w & 1] = h0;
+        ex[buf][w >> 1][1][lane][w & 1] = h1;
+        __syncthreads();
 #pragma unroll
-    for (int f = 0; f < 6; ++f) { sm[f] = __expf(fl[f] - mx); se += sm[f]; }
-    const float ise = 1.0f / se;
-    const int face = (int)r[kRecFace];
-    float flf = 0.0f;
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int f = 0; f < 6; ++f) if (f == face) flf = fl[f];
+            for (int k = 0; k < 2; ++k) x[c][k] = *reinterpret_cast<const v8i16 *>(&ex[buf][c][k][lane][0]);
+    };
+    auto act4 = [](const v4f32 &z) { return pack4(leaky(z.x), leaky(z.y), leaky(z.z), leaky(z.w)); };
+    auto signs = [](const v4f32 &z) {
+        return (z.x > 0.0f ? 1u : 0u) | (z.y > 0.0f ? 2u : 0u) | (z.z > 0.0f ? 4u : 0u) | (z.w > 0.0f ? 8u : 0u);
+    };
+    // signs of the pre-activations, all the backward pass needs of them: bit
+    // 4 b + r in the operand order, 16 + 4 b + r turned
+    uint32_t pos[3] = {0u, 0u, 0u};
+    v4f32 acc[2], at[2];
+    auto layer_out = [&](int l, int tile0) {
+        v4i16 h[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            pos[l] |= (signs(acc[b]) | (signs(at[b]) << 16)) << (4 * b);
+            h[b] = act4(acc[b]);
+        }
+        swap_ops(l & 1, h[0], h[1]);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) put_quad(tile0 + w, b, act4(at[b]));
+    };
+    auto start = [&](int l) {
+        acc[0] = acc[1] = bs[l];
+        at[0] = at[1] = (v4f32){bt[l], bt[l], bt[l], bt[l]};
+    };
+    auto product = [&](const v8i16 &wt, int c) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            acc[b] = mfma32(wt, x[c][b], acc[b]);
+            at[b] = mfma32(x[c][b], wt, at[b]);
+        }
+    };
+    auto hidden = [&](const v8i16(&wt)[4], int l) {
+        start(l);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) product(wt[c], c);
+    };
+    start(0);
+    product(w1, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    tiles(w4, kTileFwdL4 + 4 * ot);
+    const v4f32 bo = ld4(bias + 3 * kMlpHid + 16 * ot + 4 * g);
+    // this lane's row of the losses
+    const uint4 *tq = reinterpret_cast<const uint4 *>(crow + kRowDw * (16 * ob + s) + kRowFlags);
+    const uint4 q0 = tq[0], q1 = tq[1], q2 = tq[2], q3 = tq[3];
+    const float scn = norm[kMlpOut + kOutLogN];
+    v4 = tileA(blob, kTileBwdL4 + w, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    layer_out(0, kActH1);
+    if (w < 2) put_turned(kActH0 + w);
+    hidden(w2, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    tiles(v3, kTileBwdL3 + 4 * w);
+    __builtin_amdgcn_sched_barrier(0);
+    layer_out(1, kActH2);
+    hidden(w3, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    tiles(v2, kTileBwdL2 + 4 * w);
+    __builtin_amdgcn_sched_barrier(0);
+    layer_out(2, kActH3);
+    // gradients of outputs 16 ot + 4g + j of sample s of block ob, the choice of
+    // formula by selects: a branch per lane group would run them one after the other
+    static_assert(kOutSide == 6 && kOutLogN == 7 && kOutLogX2 == 8 && kOutYS == 9 && kOutYT == 10 && kOutMu2 == 11 &&
+                      kOutAlpha == 12 && kOutXAbs == 16, "outputs by lane group");
     const float invB = 1.0f / (float)batch;
-    const float xo = r[kRecXOut];
-    float dO[8], lsum = 0.0f;
+    const bool live = q0.x & 1u, cond = q0.x & 2u;
+    const float side = (q0.x & 4u) ? 1.0f : 0.0f;
+    const int face = (int)q0.y;
+    const float ua = __uint_as_float(q2.y), ub = __uint_as_float(q2.z), uc = __uint_as_float(q2.w),
+                ud = __uint_as_float(q3.x);
+    const float ylog = __uint_as_float(q0.z);
+    v4f32 o = bo;
+    float yq[4] = {}, uq[4] = {ua, ua, ua, ua}, mx = 0.0f, se = 1.0f, flf = 0.0f;
+    bool pin[4] = {};
+    if (w < 4) {  // the outputs
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int k = (j < 4) ? 4 * g + j : 16 + 4 * g + (j - 4);
-        const float oj = ov[j];
-        dO[j] = 0.0f;
-        if (!live || !used_output(k) || conditional_output(k) != cond) continue;
-        if (k < 6) {
-            float smk = 0.0f;
+        for (int c = 0; c < 4; ++c)
+            o = mfma32(w4[c], *reinterpret_cast<const v8i16 *>(&ex[0][c][ob][lane][0]), o);
+        const float ov[4] = {o.x, o.y, o.z, o.w};
+        float dO[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (ot == 0) {  // wave-uniform
+            // the six face logits of this lane's sample (lanes s and s + 16)
+            float fl[6];
+            fl[0] = __shfl(o.x, s, 64); fl[1] = __shfl(o.y, s, 64); fl[2] = __shfl(o.z, s, 64); fl[3] = __shfl(o.w, s, 64);
+            fl[4] = __shfl(o.x, s + 16, 64); fl[5] = __shfl(o.y, s + 16, 64);
+            mx = fl[0];
 #pragma unroll
-            for (int f = 0; f < 6; ++f) if (f == k) smk = sm[f];
-            dO[j] = (smk * ise - (k == face ? 1.0f : 0.0f)) * invB;
-            if (k == 0) lsum += mx + __logf(se) - flf;
-            continue;
-        }
-        if (k == kOutSide) {
-            const float b = (xo >= 0.0f) ? 1.0f : 0.0f;
-            dO[j] = (sigmoid_f(oj) - b) * invB;
-            lsum += fmaxf(oj, 0.0f) + __logf(1.0f + __expf(-fabsf(oj))) - b * oj;
-            continue;
-        }
-        float raw;
-        if (!target_value(r, k, raw)) continue;
-        const float y = (raw - norm[k]) / norm[kMlpOut + k];
-        if (k == kOutLogN) {
+            for (int f = 1; f < 6; ++f) mx = fmaxf(mx, fl[f]);
+            float sm[6];
+            se = 0.0f;
+#pragma unroll
+            for (int f = 0; f < 6; ++f) { sm[f] = __expf(fl[f] - mx); se += sm[f]; }
+            const float ise = 1.0f / se;
+#pragma unroll
+            for (int f = 0; f < 6; ++f) flf = sel(f == face, fl[f], flf);
+            float soft[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float smk = j < 2 ? sel(g == 0, sm[j], sm[4 + (j & 1)]) : sm[j];
+                soft[j] = (smk * ise - (4 * g + j == face ? 1.0f : 0.0f)) * invB;
+            }
+            const float dside = (sigmoid_f(o.z) - side) * invB;
             // weighted, scaled log-deviance w f(d) / s, d = s (y - o), f(d) = e^d - 1 - d,
             // continued linearly beyond d = kDevClamp
-            const float sc = norm[kMlpOut + k];
-            const float d = sc * (y - oj);
-            const float dc = fminf(d, kDevClamp);
-            const float ed = __expf(dc);
-            dO[j] = kDevWeight * (1.0f - ed) * invB;
-            lsum += kDevWeight * (ed - 1.0f - dc + (__expf(kDevClamp) - 1.0f) * fmaxf(d - kDevClamp, 0.0f)) / sc;
-            continue;
+            const float ed = __expf(fminf(scn * (ylog - o.w), kDevClamp));
+            const float dlog = kDevWeight * (1.0f - ed) * invB;
+            const bool m = live && !cond, c = live && cond;
+            dO[0] = sel(m && g < 2, soft[0], 0.0f);
+            dO[1] = sel(m && g < 2, soft[1], 0.0f);
+            dO[2] = sel(m && g < 2, sel(g == 0, soft[2], dside), 0.0f);
+            dO[3] = sel(m && g < 2, sel(g == 0, soft[3], dlog), 0.0f);
+            yq[0] = sel(cond, __uint_as_float(q1.w), __uint_as_float(q0.w));
+            uq[0] = sel(cond, ud, ub);
+            pin[0] = (m && g == 2) || (c && g == 3);
+            yq[1] = __uint_as_float(q1.x);
+            yq[2] = __uint_as_float(q1.y);
+            uq[2] = ub;
+            yq[3] = __uint_as_float(q1.z);
+            uq[3] = uc;
+            pin[1] = pin[2] = pin[3] = c && g == 2;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                yq[j] = __uint_as_float(q2.x);
+                pin[j] = live && !cond && 4 * g + j < 6 && 4 * g + j == face;
+            }
         }
-        // quantile level of this output on its kind of row
-        float u;
-        if (k >= kOutXAbs || k == kOutYS) u = ua;
-        else if (k == kOutLogX2 || k == kOutYT) u = ub;
-        else if (k == kOutMu2) u = uc;
-        else u = ud;
-        const float ind = (y < oj) ? 1.0f : 0.0f;
-        dO[j] = (ind - u) * invB;
-        lsum += (y - oj) * (u - ind);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dO[j] = sel(pin[j], (((yq[j] < ov[j]) ? 1.0f : 0.0f) - uq[j]) * invB, dO[j]);
+        dos[ob][lane][ot] = pack4(dO[0], dO[1], dO[2], dO[3]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) tr[16 * ot + 4 * g + j][16 * ob + s] = f2bf(dO[j]);
     }
-    for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
-    if (lane == 0 && loss) atomicAdd(loss, lsum * invB);
+    __syncthreads();
+    if (w < 2) put_turned(kActZ4 + w);
 
-    // ---- backward through the layers (dZ4 = dO)
-    // the leaky ReLU's derivative at pre-activation component j of tile mi
-    auto dl = [&](int layer, int mi, int j) { return ((zpos[layer] >> (4 * mi + j)) & 1u) ? 1.0f : kLeak; };
-    // inputs (rows 0..23; lane group g holds inputs 8g..8g+7)
-    if (g < 3) {
-        uint16_t *p = act + (int64_t)(kActH0 + 8 * g) * cap + col;
+    // ---- backward through the layers (dZ4 = dO): slots 8g + j of the output
+    // layer's operand hold outputs 4g + j and 16 + 4g + j
+    const v4f32 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 8; ++j) p[j * cap] = f2bf(g == 0 ? in[j] : (g == 1 ? in[8 + j] : in[16 + j]));
-    }
-    store4(kActZ4, dO[0], dO[1], dO[2], dO[3]);
-    store4(kActZ4 + 16, dO[4], dO[5], dO[6], dO[7]);
-    // B operand of the output layer's backward: slots 8g + j hold outputs
-    // 4g + j and 16 + 4g + j, the permutation of the hidden layers' chunks
-    const v8i16 dOb = cat8(pack4(dO[0], dO[1], dO[2], dO[3]), pack4(dO[4], dO[5], dO[6], dO[7]));
-    v4f32 dz[8];
+    for (int b = 0; b < 2; ++b) x[0][b] = *reinterpret_cast<const v8i16 *>(&dos[b][lane][0]);
+    // times the leaky ReLU's derivative, by the pre-activation's sign
+    auto slope = [](const v4f32 &z, uint32_t m) {
+        return pack4(z.x * ((m & 1u) ? 1.0f : kLeak), z.y * ((m & 2u) ? 1.0f : kLeak), z.z * ((m & 4u) ? 1.0f : kLeak),
+                     z.w * ((m & 8u) ? 1.0f : kLeak));
+    };
+    auto grad_store = [&](int l, int tile0) {
 #pragma unroll
-    for (int mi = 0; mi < 8; ++mi) {
-        v4f32 acc = {0.f, 0.f, 0.f, 0.f};
-        acc = mfma32(tileA(blob, kTileBwdL4 + mi, lane), dOb, acc);
-        dz[mi] = (v4f32){acc.x * dl(2, mi, 0), acc.y * dl(2, mi, 1), acc.z * dl(2, mi, 2), acc.w * dl(2, mi, 3)};
-        store4(kActZ3 + 16 * mi, dz[mi].x, dz[mi].y, dz[mi].z, dz[mi].w);
-    }
-    // layer 3 -> dZ2, layer 2 -> dZ1 (unrolled so the activations stay in registers)
+        for (int b = 0; b < 2; ++b) put_quad(tile0 + w, b, slope(at[b], pos[l] >> (16 + 4 * b)));
+    };
+    auto grad_ops = [&](int l, int buf) { swap_ops(buf, slope(acc[0], pos[l]), slope(acc[1], pos[l] >> 4)); };
+    acc[0] = acc[1] = at[0] = at[1] = zero;
+    product(v4, 0);
+    grad_ops(2, 1);
+    grad_store(2, kActZ3);
+    // layer 3 -> dZ2, layer 2 -> dZ1
+    acc[0] = acc[1] = at[0] = at[1] = zero;
 #pragma unroll
-    for (int layer = 3; layer >= 2; --layer) {
-        const int tb = (layer == 3) ? kTileBwdL3 : kTileBwdL2;
-        v4i16 dzb[8];
+    for (int c = 0; c < 4; ++c) product(v3[c], c);
+    grad_ops(1, 0);
+    grad_store(1, kActZ2);
+    at[0] = at[1] = zero;
 #pragma unroll
-        for (int mo = 0; mo < 8; ++mo) dzb[mo] = pack4(dz[mo].x, dz[mo].y, dz[mo].z, dz[mo].w);
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int mi = 0; mi < 8; ++mi) {
-            v4f32 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 2; ++b) at[b] = mfma32(x[c][b], v2[c], at[b]);
+    grad_store(0, kActZ1);
+
+    // the loss itself, while the stores drain
+    if (!loss) return;
+    if (w < 4) {
+        const float ov[4] = {o.x, o.y, o.z, o.w};
+        float lsum = 0.0f;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc = mfma32(tileA(blob, tb + mi * 4 + c, lane), cat8(dzb[2 * c], dzb[2 * c + 1]), acc);
-            const int zl = (layer == 3) ? 1 : 0;
-            dz[mi] = (v4f32){acc.x * dl(zl, mi, 0), acc.y * dl(zl, mi, 1), acc.z * dl(zl, mi, 2), acc.w * dl(zl, mi, 3)};
-            store4((layer == 3 ? kActZ2 : kActZ1) + 16 * mi, dz[mi].x, dz[mi].y, dz[mi].z, dz[mi].w);
+        for (int j = 0; j < 4; ++j)
+            if (pin[j]) lsum += (yq[j] - ov[j]) * (uq[j] - ((yq[j] < ov[j]) ? 1.0f : 0.0f));
+        if (ot == 0 && live && !cond) {
+            if (g == 0) {
+                lsum += mx + __logf(se) - flf;
+            } else if (g == 1) {
+                lsum += fmaxf(o.z, 0.0f) + __logf(1.0f + __expf(-fabsf(o.z))) - side * o.z;
+                const float d = scn * (ylog - o.w);
+                const float dc = fminf(d, kDevClamp);
+                lsum += kDevWeight * (__expf(dc) - 1.0f - dc + (__expf(kDevClamp) - 1.0f) * fmaxf(d - kDevClamp, 0.0f)) / scn;
+            }
         }
+        for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
+        if (lane == 0) lsums[w] = lsum;
     }
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(loss, (lsums[0] + lsums[1] + lsums[2] + lsums[3]) * invB);
 }
 
 // Weight gradients as products over the stored activations: dW_l[in][out] =
-// sum_s H_{l-1}[in][s] dZ_l[out][s], the bias from the constant row.  One wave
+// sum_s H_{l-1}[in][s] dZ_l[out][s], the bias from a row of ones.  One wave
 // per (layer, 16-row tile, pair of 16-column tiles, sample split): the H
 // operand of a chunk feeds both tiles' products.  Results go to
 // part[split][param] (every parameter is written by exactly one wave per
 // split, so the sum over splits in fixed order is deterministic).
+//
+// A batch of 8192 gives 712 waves of 32 chunks, 96 KB each, less than one wave
+// per SIMD: the wait for memory bounds it.  Each tile is one contiguous 1 KB
+// load, eight chunks (24 KB a wave) are on their way at any time, and a split's
+// workgroups sit on one XCD (workgroups go round the eight), whose L2 then
+// holds that split's eighth of the store.  8192 samples: 14.5 us before (rows
+// of 2-byte columns, one chunk at a time), 6.6 us now (16 chunks on their way:
+// no faster).
 constexpr int kGradJobsL1 = 2 * 4, kGradJobsL2 = 9 * 4, kGradJobsL3 = 9 * 4, kGradJobsL4 = 9 * 1;
 constexpr int kGradJobs = kGradJobsL1 + kGradJobsL2 + kGradJobsL3 + kGradJobsL4;   // 89
+constexpr int kGradAhead = 8;
 
-__global__ void __launch_bounds__(256) mlp_wgrad_kernel(const uint16_t *act, int64_t cap, int kcols, float *part) {
-    const int lane = __lane_id(), w = threadIdx.x / 64;
-    const int job = blockIdx.x * (blockDim.x / 64) + w;
-    if (job >= kGradJobs * kGradSplits) return;
-    const int split = job / kGradJobs;
-    int jj = job % kGradJobs;
-    int hrow, zrow, it, jp, nin, ldw, pw, pb;
+__global__ void __launch_bounds__(64) mlp_wgrad_kernel(const unsigned char *act, int nchunk, float *part,
+                                                       RowDraw D) {
+    const int lane = __lane_id();
+    if (blockIdx.x >= kGradJobs * kGradSplits) {
+        const int i = (blockIdx.x - kGradJobs * kGradSplits) * 64 + lane;
+        if (i < 32 * ((D.batch + 31) / 32)) draw_row(D, i);
+        return;
+    }
+    const int split = blockIdx.x % kGradSplits;
+    int jj = blockIdx.x / kGradSplits;
+    int htile, ztile, it, jp, nin, ldw, pw, pb;
     if (jj < kGradJobsL1) {
-        it = jj / 4; jp = jj % 4; hrow = kActH0; zrow = kActZ1; nin = kMlpIn; ldw = kMlpHid; pw = kPW1; pb = kPB1;
+        it = jj / 4; jp = jj % 4; htile = kActH0; ztile = kActZ1; nin = kMlpIn; ldw = kMlpHid; pw = kPW1; pb = kPB1;
     } else if ((jj -= kGradJobsL1) < kGradJobsL2) {
-        it = jj / 4; jp = jj % 4; hrow = kActH1; zrow = kActZ2; nin = kMlpHid; ldw = kMlpHid; pw = kPW2; pb = kPB2;
+        it = jj / 4; jp = jj % 4; htile = kActH1; ztile = kActZ2; nin = kMlpHid; ldw = kMlpHid; pw = kPW2; pb = kPB2;
     } else if ((jj -= kGradJobsL2) < kGradJobsL3) {
-        it = jj / 4; jp = jj % 4; hrow = kActH2; zrow = kActZ3; nin = kMlpHid; ldw = kMlpHid; pw = kPW3; pb = kPB3;
+        it = jj / 4; jp = jj % 4; htile = kActH2; ztile = kActZ3; nin = kMlpHid; ldw = kMlpHid; pw = kPW3; pb = kPB3;
     } else {
         jj -= kGradJobsL3;
-        it = jj; jp = 0; hrow = kActH3; zrow = kActZ4; nin = kMlpHid; ldw = kMlpOut; pw = kPW4; pb = kPB4;
+        it = jj; jp = 0; htile = kActH3; ztile = kActZ4; nin = kMlpHid; ldw = kMlpOut; pw = kPW4; pb = kPB4;
     }
     const int s = lane % 16, g = lane / 16;
+    // row tile 8 of a hidden layer is the ones row alone: no load
+    const bool ones = 16 * it >= kMlpHid;
+    const short one = (short)(s == 0 ? 0x3F80 : 0);
+    const v8i16 onesA = {one, one, one, one, one, one, one, one};
     // this split's columns: chunks of 32 samples
-    const int nchunk = kcols / 32;
     const int c0 = (int)((int64_t)nchunk * split / kGradSplits), c1 = (int)((int64_t)nchunk * (split + 1) / kGradSplits);
-    const uint16_t *ha = act + (int64_t)(hrow + 16 * it + s) * cap + 8 * g;
-    const uint16_t *zb0 = act + (int64_t)(zrow + 32 * jp + s) * cap + 8 * g;
-    const uint16_t *zb1 = zb0 + 16 * cap;
+    const unsigned char *zt = act + (ztile + 2 * jp) * kTileBytes + lane * 16;
+    const unsigned char *ht = ones ? zt : act + (htile + it) * kTileBytes + lane * 16;
+    v8i16 a[kGradAhead], b0[kGradAhead], b1[kGradAhead];
+    auto fetch = [&](int k, int c) {
+        const int64_t o = (int64_t)min(c, nchunk - 1) * (kActTiles * kTileBytes);
+        a[k] = *reinterpret_cast<const v8i16 *>(ht + o);
+        b0[k] = *reinterpret_cast<const v8i16 *>(zt + o);
+        b1[k] = *reinterpret_cast<const v8i16 *>(zt + o + kTileBytes);
+    };
+#pragma unroll
+    for (int k = 0; k < kGradAhead; ++k) fetch(k, c0 + k);
     v4f32 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-    for (int c = c0; c < c1; ++c) {
-        const v8i16 a = *reinterpret_cast<const v8i16 *>(ha + 32 * c);
-        const v8i16 b0 = *reinterpret_cast<const v8i16 *>(zb0 + 32 * c);
-        const v8i16 b1 = *reinterpret_cast<const v8i16 *>(zb1 + 32 * c);
-        acc0 = mfma32(a, b0, acc0);
-        acc1 = mfma32(a, b1, acc1);
+    for (int c = c0; c < c1; c += kGradAhead) {
+#pragma unroll
+        for (int k = 0; k < kGradAhead; ++k) {
+            if (c + k < c1) {  // wave-uniform
+                const v8i16 h = ones ? onesA : a[k];
+                acc0 = mfma32(h, b0[k], acc0);
+                acc1 = mfma32(h, b1[k], acc1);
+            }
+            fetch(k, c + kGradAhead + k);
+        }
     }
     float *dst = part + (int64_t)split * kNParams;
 #pragma unroll
@@ -571,20 +810,9 @@ __global__ void __launch_bounds__(256) mlp_wgrad_kernel(const uint16_t *act, int
         for (int r = 0; r < 4; ++r) {
             const int in = 16 * it + 4 * g + r;
             if (in < nin) dst[pw + in * ldw + out] = v[r];
-            else if (in == nin) dst[pb + out] = v[r];  // the constant row: bias gradient
+            else if (in == nin) dst[pb + out] = v[r];  // the row of ones: bias gradient
         }
     }
-}
-
-// The ones rows of the activation store (bias rows of H0..H3).
-__global__ void mlp_act_init_kernel(uint16_t *act, int64_t cap) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cap) return;
-    const uint16_t one = 0x3F80;  // 1.0 in bf16
-    for (int r = kMlpIn; r < kActRowsH0; ++r) act[(int64_t)(kActH0 + r) * cap + i] = (r == kMlpIn) ? one : 0;
-    for (int l = 0; l < 3; ++l)
-        for (int r = kMlpHid; r < kActRowsH; ++r)
-            act[(int64_t)(kActH1 + l * kActRowsH + r) * cap + i] = (r == kMlpHid) ? one : 0;
 }
 
 // sum of the split partial gradients (fixed order)
@@ -596,113 +824,155 @@ __global__ void mlp_gsum_kernel(const float *part, float *grad) {
     grad[i] = gsum;
 }
 
-// Adam (FP32 master, bias-corrected) on the summed split gradients.
-__global__ void mlp_adam_kernel(float *p, float *m, float *v, const float *part, float lr, float b1, float b2,
-                                float eps, float c1, float c2) {
+// Adam (FP32 master, bias-corrected) on the summed split gradients; the new
+// value goes straight to its places in the packed blob (a launch of 4 us saved).
+constexpr int kAdamThreads = 128;
+__global__ void __launch_bounds__(kAdamThreads) mlp_adam_kernel(float *p, float *m, float *v, const float *part,
+                                                                float lr, float b1, float b2, float eps, float c1,
+                                                                float c2, unsigned char *blob) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= kNParams) return;
     float gi = 0.0f;
+#pragma unroll
     for (int sp = 0; sp < kGradSplits; ++sp) gi += part[(int64_t)sp * kNParams + i];
     float mi = b1 * m[i] + (1.0f - b1) * gi;
     float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
-// Training quantile levels are uniform, clamped to the encoded range [1e-4, 1 - 1e-4]
-// (the pinball loss uses the clamped level too).
-__device__ __forceinline__ float train_level(uint32_t w) {
-    return fminf(fmaxf(u01(w), kLevelMin), 1.0f - kLevelMin);
-}
-
-// Random batch: indices uniform over the records, four quantile levels and the
-// row kind (conditional with probability 1/3).
-__global__ void mlp_batch_kernel(int64_t n, uint32_t k0, uint32_t k1, uint32_t step, int batch, int32_t *idx,
-                                 float *uq) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= batch) return;
-    const uint4 r = philox(make_uint4(step, (uint32_t)i, 0u, 9u), k0, k1);
-    const uint4 e = philox(make_uint4(step, (uint32_t)i, 1u, 9u), k0, k1);
-    idx[i] = (int32_t)__umulhi(r.x, (uint32_t)n);
-    float *q = uq + 5 * (int64_t)i;
-    q[0] = train_level(r.y);
-    q[1] = train_level(r.z);
-    q[2] = train_level(r.w);
-    q[3] = train_level(e.y);
-    q[4] = (u01(e.x) < (1.0f / 3.0f)) ? 1.0f : 0.0f;
+    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    p[i] = pi;
+    pack_param(blob, i, pi);
 }
 
 // Normalisation of the targets: mean and standard deviation over the valid
 // records of each output's own target (|x_out| of face F over the records
 // leaving through F; the face and side logits and the unused outputs keep
-// mean 0, scale 1), FP64 accumulation, one block of 256 threads per output; three more
-// blocks record the ranges of log10 a and log10 tau_c and the smallest log10
-// depth of the valid records (where the network may then be used).
-__global__ void mlp_norm_kernel(const float *rec, int64_t n, float *norm) {
-    __shared__ double s0[256], s1[256], s2[256];
-    const int k = blockIdx.x;
-    double a = 0.0, b = 0.0, c = 0.0;
-    if (k >= kMlpOut) {
-        // ranges over the valid records: log10 a (block kMlpOut), log10 tau_c
-        // (kMlpOut + 1), and the lower end of log10 depth (kMlpOut + 2)
-        const int col = (k == kMlpOut) ? kRecLA : ((k == kMlpOut + 1) ? kRecLT : kRecLD);
-        float lo = 1e30f, hi = -1e30f;
-        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-            const float *r = rec + (int64_t)kRec * i;
-            if (r[kRecValid] < 0.5f) continue;
-            lo = fminf(lo, r[col]);
-            hi = fmaxf(hi, r[col]);
-        }
-        s1[threadIdx.x] = lo;
-        s2[threadIdx.x] = hi;
+// mean 0, scale 1), and the ranges of log10 a and log10 tau_c and the smallest
+// log10 depth of the valid records (where the network may then be used).
+//
+// FP64 sums in a fixed order: chain t of 256 takes records t, t + 256, ...,
+// and the chains are combined as a tree.  A workgroup takes four neighbouring
+// chains: its threads read 512 records at a time, once for all outputs, and
+// leave the targets in LDS, and its first wave carries the chains on, one lane
+// per chain and target.  The next records are read meanwhile, so the additions
+// bound it.  200,000 records: 562 us before (one workgroup per output reading
+// every record, one load at a time), 84 us now.
+constexpr int kNormChains = 256, kNormStride = 4, kNormThreads = 512, kNormRoles = 16;
+constexpr int kNormSteps = kNormThreads / kNormStride;
+// roles: 0-5 outputs 7-12, 6-11 |x_out| of face 0-5, 12-14 log10 a, tau_c, depth
+constexpr int kNormCols = 10;  // six targets, |x_out|, log10 a, tau_c, depth
+__device__ __forceinline__ int norm_role(int k) {  // role of output (or range) k, -1: none
+    return (k >= kOutLogN && k <= kOutAlpha) ? k - kOutLogN
+           : (k >= kOutXAbs && k < kOutXAbs + 6) ? 6 + k - kOutXAbs
+           : k >= kMlpOut ? 12 + k - kMlpOut : -1;
+}
+static_assert(3 * kNormRoles * kNormChains * sizeof(double) <= sizeof(float) * kNParams * kGradSplits,
+              "the sums fit the buffer of the split gradients");
+
+__global__ void __launch_bounds__(kNormThreads) mlp_norm_sums_kernel(const float *rec, int64_t n, double *sums) {
+    __shared__ float val[2][kNormCols][kNormThreads];
+    __shared__ signed char who[2][kNormThreads];  // exit face of a valid record (7: another value), -1: no record
+    const int t = threadIdx.x;
+    const int chain = kNormStride * blockIdx.x + t % kNormStride;
+    const int64_t batches = (n + (int64_t)kNormChains * kNormSteps - 1) / ((int64_t)kNormChains * kNormSteps);
+    float v[12];
+    auto read = [&](int64_t b) {
+        const int64_t i = (b * kNormSteps + t / kNormStride) * kNormChains + chain;
+        const float *r = rec + kRec * (i < n ? i : 0);
+        const int cols[12] = {kRecValid, kRecFace, kRecLogN, kRecLogX2, kRecYS, kRecYT,
+                              kRecMu, kRecAlpha, kRecXOut, kRecLA, kRecLT, kRecLD};
+#pragma unroll
+        for (int k = 0; k < 12; ++k) v[k] = r[cols[k]];
+        if (i >= n) v[0] = 0.0f;
+    };
+    auto leave = [&](int buf) {
+        const int f = (int)v[1];
+        who[buf][t] = v[0] < 0.5f ? (signed char)-1 : (signed char)((f >= 0 && f < 6) ? f : 7);
+        val[buf][0][t] = v[2];
+        val[buf][1][t] = v[3];
+        val[buf][2][t] = asinhf(v[4]);
+        val[buf][3][t] = asinhf(v[5]);
+        val[buf][4][t] = v[6] * v[6];
+        val[buf][5][t] = v[7];
+        val[buf][6][t] = fabsf(v[8]);
+        val[buf][7][t] = v[9];
+        val[buf][8][t] = v[10];
+        val[buf][9][t] = v[11];
+    };
+    // wave 0: lane = 4 role + chain
+    const int role = t / kNormStride;
+    const int col = role < 6 ? role : (role < 12 ? 6 : min(role - 5, kNormCols - 1));
+    double a = 0.0, q = 0.0, c = 0.0;
+    float lo = 1e30f, hi = -1e30f;
+    read(0);
+    for (int64_t b = 0; b < batches; ++b) {
+        const int buf = (int)(b & 1);
+        leave(buf);
         __syncthreads();
-        for (int st = 128; st >= 1; st >>= 1) {
-            if ((int)threadIdx.x < st) {
-                s1[threadIdx.x] = fmin(s1[threadIdx.x], s1[threadIdx.x + st]);
-                s2[threadIdx.x] = fmax(s2[threadIdx.x], s2[threadIdx.x + st]);
+        if (b + 1 < batches) read(b + 1);
+        if (t < 64) {
+#pragma unroll 8
+            for (int j = 0; j < kNormSteps; ++j) {
+                const int e = kNormStride * j + t % kNormStride;
+                const float yf = val[buf][col][e];
+                const int f = who[buf][e];
+                const bool in = f >= 0 && (role < 6 || role >= 12 || f == role - 6);
+                const double y = yf;
+                a = in ? a + y : a;
+                q = in ? q + y * y : q;
+                c = in ? c + 1.0 : c;
+                lo = in ? fminf(lo, yf) : lo;
+                hi = in ? fmaxf(hi, yf) : hi;
             }
-            __syncthreads();
         }
-        if (threadIdx.x == 0) {
-            const int o = kNormARange + 2 * (k - kMlpOut);
-            norm[o] = (float)s1[0];
-            if (k < kMlpOut + 2) norm[o + 1] = (float)s2[0];
-            else norm[o + 1] = 0.0f;  // padding after the depth minimum
+    }
+    if (t < 64) {
+        double *o = sums + (int64_t)role * kNormChains + chain;
+        const bool range = role >= 12;
+        o[0] = range ? (double)lo : a;
+        o[kNormRoles * kNormChains] = range ? (double)hi : q;
+        o[2 * kNormRoles * kNormChains] = c;
+    }
+}
+
+// The chains' tree and the normalisation of output k (one workgroup of 256
+// threads per output, three more for the ranges).
+__global__ void __launch_bounds__(kNormChains) mlp_norm_kernel(const double *sums, float *norm) {
+    __shared__ double s0[kNormChains], s1[kNormChains], s2[kNormChains];
+    const int k = blockIdx.x, t = threadIdx.x, role = norm_role(k);
+    const bool range = k >= kMlpOut;
+    if (role < 0) {  // no target
+        if (t == 0) {
+            norm[k] = 0.0f;
+            norm[kMlpOut + k] = 1.0f;
         }
         return;
     }
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const float *r = rec + (int64_t)kRec * i;
-        float yf;
-        if (r[kRecValid] < 0.5f || !target_value(r, k, yf)) continue;
-        const double y = yf;
-        a += y;
-        b += y * y;
-        c += 1.0;
-    }
-    s1[threadIdx.x] = a;
-    s2[threadIdx.x] = b;
-    s0[threadIdx.x] = c;
+    s1[t] = sums[role * kNormChains + t];
+    s2[t] = sums[(kNormRoles + role) * kNormChains + t];
+    s0[t] = sums[(2 * kNormRoles + role) * kNormChains + t];
     __syncthreads();
-    for (int st = 128; st >= 1; st >>= 1) {
-        if ((int)threadIdx.x < st) {
-            s1[threadIdx.x] += s1[threadIdx.x + st];
-            s2[threadIdx.x] += s2[threadIdx.x + st];
-            s0[threadIdx.x] += s0[threadIdx.x + st];
+    for (int st = kNormChains / 2; st >= 1; st >>= 1) {
+        if (t < st) {
+            s1[t] = range ? fmin(s1[t], s1[t + st]) : s1[t] + s1[t + st];
+            s2[t] = range ? fmax(s2[t], s2[t + st]) : s2[t] + s2[t + st];
+            s0[t] += s0[t + st];
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        if (s0[0] < 1.0) {
-            norm[k] = 0.0f;
-            norm[kMlpOut + k] = 1.0f;
-        } else {
-            const double mean = s1[0] / s0[0];
-            const double var = s2[0] / s0[0] - mean * mean;
-            norm[k] = (float)mean;
-            norm[kMlpOut + k] = (float)sqrt(var > 1e-12 ? var : 1e-12);
-        }
+    if (t != 0) return;
+    if (range) {
+        const int o = kNormARange + 2 * (k - kMlpOut);
+        norm[o] = (float)s1[0];
+        norm[o + 1] = k < kMlpOut + 2 ? (float)s2[0] : 0.0f;  // padding after the depth minimum
+    } else if (s0[0] < 1.0) {
+        norm[k] = 0.0f;
+        norm[kMlpOut + k] = 1.0f;
+    } else {
+        const double mean = s1[0] / s0[0];
+        const double var = s2[0] / s0[0] - mean * mean;
+        norm[k] = (float)mean;
+        norm[kMlpOut + k] = (float)sqrt(var > 1e-12 ? var : 1e-12);
     }
 }
 
@@ -804,33 +1074,39 @@ hipError_t launch_mlp_init(float *p, uint32_t k0, uint32_t k1, hipStream_t s) {
     return hipGetLastError();
 }
 
+static hipError_t launch_mlp_image(const unsigned char *blob, unsigned char *img, hipStream_t s) {
+    hipLaunchKernelGGL(mlp_fwd_image_kernel, dim3((kMlpFwdBytes + 255) / 256), dim3(256), 0, s, blob, img);
+    return hipGetLastError();
+}
+
 hipError_t launch_mlp_pack(const float *p, const float *norm, unsigned char *blob, unsigned char *img,
                            hipStream_t s) {
-    int n = kTilesAll * 64;
-    hipLaunchKernelGGL(mlp_pack_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, norm, blob);
+    hipLaunchKernelGGL(mlp_pack_kernel, dim3((kNParams + 255) / 256), dim3(256), 0, s, p, norm, blob);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !img) return e;
-    int nb = kMlpFwdBytes;
-    hipLaunchKernelGGL(mlp_fwd_image_kernel, dim3((nb + 255) / 256), dim3(256), 0, s, blob, img);
+    return e != hipSuccess ? e : launch_mlp_image(blob, img, s);
+}
+
+hipError_t launch_mlp_rows(const float *rec, const int32_t *idx, const float *uq, int batch, const float *norm,
+                           uint32_t *rows, hipStream_t s) {
+    hipLaunchKernelGGL(mlp_rows_kernel, dim3((batch + 63) / 64), dim3(64), 0, s, rec, idx, uq, batch, norm, rows);
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_act_init(uint16_t *act, int64_t cap, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_act_init_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, act, cap);
+hipError_t launch_mlp_draw(const RowDraw &D, hipStream_t s) {
+    hipLaunchKernelGGL(mlp_draw_kernel, dim3((D.batch + 63) / 64), dim3(64), 0, s, D);
     return hipGetLastError();
 }
 
-// Gradient of the mean loss over a batch into the split partials `part`.
-hipError_t launch_mlp_grad(const unsigned char *blob, const float *rec, const int32_t *idx, const float *uq,
-                           int batch, uint16_t *act, int64_t cap, float *part, float *loss, hipStream_t s) {
-    const int kcols = 32 * ((batch + 31) / 32);
-    const int nblocks = kcols / 16;
-    hipLaunchKernelGGL(mlp_fwdbwd_kernel, dim3((nblocks + 3) / 4), dim3(256), 0, s, blob, rec, idx, uq, batch, act,
-                       cap, loss);
+// Gradient of the mean loss over a batch of rows into the split partials
+// `part`; `next` (if any) draws the rows of the step after it.
+hipError_t launch_mlp_grad(const unsigned char *blob, const uint32_t *rows, int batch, unsigned char *act, float *part,
+                           float *loss, const RowDraw *next, hipStream_t s) {
+    const int nchunk = (batch + 31) / 32;
+    hipLaunchKernelGGL(mlp_fwdbwd_kernel, dim3(nchunk), dim3(512), 0, s, blob, rows, batch, act, loss);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int jobs = kGradJobs * kGradSplits;
-    hipLaunchKernelGGL(mlp_wgrad_kernel, dim3((jobs + 3) / 4), dim3(256), 0, s, act, cap, kcols, part);
+    hipLaunchKernelGGL(mlp_wgrad_kernel, dim3(kGradJobs * kGradSplits + (next ? (next->batch + 63) / 64 : 0)), dim3(64), 0,
+                       s, act, nchunk, part, next ? *next : RowDraw{});
     return hipGetLastError();
 }
 
@@ -839,19 +1115,16 @@ hipError_t launch_mlp_gsum(const float *part, float *grad, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_adam(float *p, float *m, float *v, const float *part, float lr, int step, hipStream_t s) {
+// One Adam step into the master parameters and the packed blob, and (img not
+// null, a training's last step) the inference image.
+hipError_t launch_mlp_adam(float *p, float *m, float *v, const float *part, float lr, int step, unsigned char *blob,
+                           unsigned char *img, hipStream_t s) {
     const float b1 = 0.9f, b2 = 0.999f;
     float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
-    hipLaunchKernelGGL(mlp_adam_kernel, dim3((kNParams + 255) / 256), dim3(256), 0, s, p, m, v, part, lr, b1, b2,
-                       1e-8f, c1, c2);
-    return hipGetLastError();
-}
-
-hipError_t launch_mlp_batch(int64_t n, uint32_t k0, uint32_t k1, uint32_t step, int batch, int32_t *idx,
-                            float *uq, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_batch_kernel, dim3((batch + 255) / 256), dim3(256), 0, s, n, k0, k1, step, batch,
-                       idx, uq);
-    return hipGetLastError();
+    hipLaunchKernelGGL(mlp_adam_kernel, dim3((kNParams + kAdamThreads - 1) / kAdamThreads), dim3(kAdamThreads), 0, s, p,
+                       m, v, part, lr, b1, b2, 1e-8f, c1, c2, blob);
+    hipError_t e = hipGetLastError();
+    return (e != hipSuccess || !img) ? e : launch_mlp_image(blob, img, s);
 }
 
 hipError_t launch_mlp_calib(const unsigned char *blob, const float *rec, int64_t n, double *sums, float *norm,
@@ -864,8 +1137,11 @@ hipError_t launch_mlp_calib(const unsigned char *blob, const float *rec, int64_t
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_norm(const float *rec, int64_t n, float *norm, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_norm_kernel, dim3(kMlpOut + 3), dim3(256), 0, s, rec, n, norm);
+hipError_t launch_mlp_norm(const float *rec, int64_t n, double *scratch, float *norm, hipStream_t s) {
+    hipLaunchKernelGGL(mlp_norm_sums_kernel, dim3(kNormChains / kNormStride), dim3(kNormThreads), 0, s, rec, n, scratch);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(mlp_norm_kernel, dim3(kMlpOut + 3), dim3(kNormChains), 0, s, scratch, norm);
     return hipGetLastError();
 }
 

@@ -185,14 +185,25 @@ hipError_t launch_cell_record(const RecordParams &R, int cus, hipStream_t s);
 hipError_t launch_mlp_init(float *p, uint32_t k0, uint32_t k1, hipStream_t s);
 hipError_t launch_mlp_pack(const float *p, const float *norm, unsigned char *blob, unsigned char *img,
                            hipStream_t s);
-hipError_t launch_mlp_act_init(uint16_t *act, int64_t cap, hipStream_t s);
-hipError_t launch_mlp_grad(const unsigned char *blob, const float *rec, const int32_t *idx, const float *uq,
-                           int batch, uint16_t *act, int64_t cap, float *part, float *loss, hipStream_t s);
+// draw of a training step's rows: records of rec[n], Philox keyed by (k0, k1)
+// and counted by step; rows has room for the batch rounded up to 32
+struct RowDraw {
+    const float *rec = nullptr;
+    int64_t n = 0;
+    uint32_t k0 = 0, k1 = 0, step = 0;
+    int batch = 0;
+    const float *norm = nullptr;
+    uint32_t *rows = nullptr;
+};
+hipError_t launch_mlp_rows(const float *rec, const int32_t *idx, const float *uq, int batch, const float *norm,
+                           uint32_t *rows, hipStream_t s);
+hipError_t launch_mlp_draw(const RowDraw &D, hipStream_t s);
+hipError_t launch_mlp_grad(const unsigned char *blob, const uint32_t *rows, int batch, unsigned char *act, float *part,
+                           float *loss, const RowDraw *next, hipStream_t s);
 hipError_t launch_mlp_gsum(const float *part, float *grad, hipStream_t s);
-hipError_t launch_mlp_adam(float *p, float *m, float *v, const float *part, float lr, int step, hipStream_t s);
-hipError_t launch_mlp_batch(int64_t n, uint32_t k0, uint32_t k1, uint32_t step, int batch, int32_t *idx,
-                            float *uq, hipStream_t s);
-hipError_t launch_mlp_norm(const float *rec, int64_t n, float *norm, hipStream_t s);
+hipError_t launch_mlp_adam(float *p, float *m, float *v, const float *part, float lr, int step, unsigned char *blob,
+                           unsigned char *img, hipStream_t s);
+hipError_t launch_mlp_norm(const float *rec, int64_t n, double *scratch, float *norm, hipStream_t s);
 hipError_t launch_mlp_calib(const unsigned char *blob, const float *rec, int64_t n, double *sums, float *norm,
                             hipStream_t s);
 hipError_t launch_mlp_forward(const unsigned char *blob, const float *inp, int64_t n, float *out, hipStream_t s);

@@ -119,8 +119,10 @@ constexpr int kBiasFloats = 3 * kMlpHid + kMlpOut;
 constexpr int kMlpFwdBytes = kTilesFwd * kTileBytes + kBiasFloats * 4 + kNNorm * 4;  // LDS image for inference
 constexpr int kMlpBlobBytes = kTilesAll * kTileBytes + kBiasFloats * 4 + kNNorm * 4;
 static_assert(kMlpIn <= kMlpInPad && kMlpOut == 32, "inputs fill one 32-wide chunk, outputs two tiles");
-// training: activation-store rows and the sample splits of the weight-gradient product
-constexpr int kActRowsAll = 32 + 3 * 144 + 3 * kMlpHid + kMlpOut;   // 880
+// training: dwords of a batch row, operand tiles of the activation store per
+// chunk of 32 samples, and the sample splits of the weight-gradient product
+constexpr int kRowDw = 32;
+constexpr int kActTiles = 2 + 3 * 8 + 3 * 8 + 2;   // 52
 constexpr int kGradSplits = 8;
 // raw input row of krt_escape_forward: (log10 tau_c, log10 a, |x_in|, q0, q1,
 // q2, log10 depth, m0, m1, m2, u_a, u_b, u_c, u_d, flag, x_out, face)
