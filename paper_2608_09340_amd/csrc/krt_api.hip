@@ -54,8 +54,7 @@ struct krt_ctx {
     float4 *rec = nullptr;           // cell records, filled at each run that uses them
     int64_t rec_cap = 0;             // ... float4 allocated
     unsigned long long *work_counter = nullptr;
-    double *level_consts = nullptr;
-    double *level_power = nullptr;   // per-line partial and total powers of krt_levels_update
+    double *level_power = nullptr;   // per-line sums of krt_levels_update's workgroups
     int64_t *host_pinned = nullptr;
     float *host_edges = nullptr;          // pinned staging of the bin edges for krt_mc_run_noalloc
     unsigned char *scratch_dev = nullptr; // this device's address of the no-allocation scratch array
@@ -289,7 +288,6 @@ extern "C" int krt_create(krt_ctx **out, int hip_device, void *hip_stream) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, hip_device) == hipSuccess && cus > 0)
         c->cus = cus;
     if (hipMalloc(&c->work_counter, sizeof(unsigned long long)) != hipSuccess ||
-        hipMalloc(&c->level_consts, sizeof(double) * 256) != hipSuccess ||
         hipHostMalloc(&c->host_pinned, sizeof(int64_t) * 64, hipHostMallocDefault) != hipSuccess ||
         hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess ||
         hipEventCreate(&c->evn0) != hipSuccess || hipEventCreate(&c->evn1) != hipSuccess ||
@@ -322,7 +320,6 @@ extern "C" void krt_destroy(krt_ctx *c) {
     if (c->cs_par) (void)hipFree(c->cs_par);
     if (c->rec) (void)hipFree(c->rec);
     if (c->work_counter) (void)hipFree(c->work_counter);
-    if (c->level_consts) (void)hipFree(c->level_consts);
     if (c->level_power) (void)hipFree(c->level_power);
     if (c->host_pinned) (void)hipHostFree(c->host_pinned);
     if (c->host_edges) (void)hipHostFree(c->host_edges);
@@ -889,200 +886,259 @@ extern "C" int krt_image(krt_ctx *c, const krt_image_desc *d) {
 extern "C" float krt_last_image_ms(const krt_ctx *c) { return c ? c->last_image_ms : -1.0f; }
 
 // --------------------------------------------------------------- levels ---
-// Per-cell rate matrix, FP64 Gaussian elimination with partial pivoting.
-// consts: E[nl] g[nl] A[nl*nl] Cd[nl*nl] sigma0[nl-1]
+// Constants of a level solve, one kernel argument: for each pair u > l (at
+// pair(u, l)) A_ul, the collisional de-excitation coefficient, g_u / g_l and
+// exp(-(E_u - E_l)); for each line l (l + 1 -> l) g_l / g_(l+1), 4 pi^(3/2)
+// sigma0_l and sigma0_l.
+template <int NL>
+struct LevelConsts {
+    static constexpr int kPairs = NL * (NL - 1) / 2;
+    double A[kPairs], Cd[kPairs], gr[kPairs], ex[kPairs];
+    double gd[NL - 1], gam[NL - 1], s0[NL - 1];
+};
+__host__ __device__ constexpr int level_pair(int u, int l) { return u * (u - 1) / 2 + l; }
+
+// Per-cell rate matrix, FP64 Gaussian elimination with partial pivoting, and
+// (lines' powers asked for) the sum of n_u A_ul over the cells of a workgroup,
+// line_sums[line][workgroup].
 // The level count is a template argument: every index into the matrices is
 // then a compile-time constant after unrolling (the pivot row is swapped by
 // selects over the candidate rows), so they live in registers; a run-time
 // count would index them dynamically and put them in scratch memory.
-template <int NL>
-__global__ void __launch_bounds__(256) levels_kernel(int64_t ncell, const double *K, const double *ncoll,
-                                                     const double *ntot, const float *jbar, double *pops,
-                                                     float *k0_out, float *eps_out, float *emis_out) {
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell) return;
-    const double *E = K, *g = K + NL, *A = K + 2 * NL, *Cd = K + 2 * NL + NL * NL, *s0 = K + 2 * NL + 2 * NL * NL;
-    double R[NL][NL], M[NL][NL], b[NL];
-    const double nc = ncoll[c];
+//
+// FP64 issue bounds it, half of which went into exponentials and quotients of
+// the constants alone; those come from the host now (FP64 as before).  The
+// populations leave through LDS as contiguous stores (a cell's are 8 NL bytes
+// apart from the next one's, so a store per level touched every line NL times)
+// and the lines' powers are summed here instead of by a pass that read them
+// all again once per line.  128^3 cells of 5 levels: 100 us, 65 us now (252 MB,
+// 3.9 TB/s); with the copy of the constants, the power launches and their copy
+// back 130 us a call, 73 us now.
+constexpr int kLevelThreads = 256;
+constexpr int kLevelBlocks = 2048;   // at most; a workgroup takes every gridDim-th 256 cells
+constexpr int kMaxLevels = 8;
+template <int NL, bool kPower>
+__global__ void __launch_bounds__(kLevelThreads) levels_kernel(const LevelConsts<NL> K0, int64_t ncell,
+                                                               const double *ncoll, const double *ntot,
+                                                               const float *jbar, double *pops, float *k0_out,
+                                                               float *eps_out, float *emis_out, double *line_sums) {
+    __shared__ double stage[kLevelThreads / 64][64 * NL];  // a wave's populations, cell by cell as they are stored
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double power[NL - 1] = {};
+    const int64_t nb = (ncell + kLevelThreads - 1) / kLevelThreads;
+    for (int64_t blk = blockIdx.x; blk < nb; blk += gridDim.x) {
+        const int64_t c = blk * kLevelThreads + threadIdx.x;
+        const bool in = c < ncell;
+        const int64_t cl = in ? c : ncell - 1;
+        // the constants are read again for every cell: kept across the loop
+        // they take more scalar registers than there are
+        typedef const __attribute__((address_space(4))) LevelConsts<NL> *Consts;
+        Consts K = (Consts)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(K));
+        double R[NL][NL], M[NL][NL], b[NL];
+        const double nc = ncoll[cl];
 #pragma unroll
-    for (int i = 0; i < NL; ++i)
+        for (int i = 0; i < NL; ++i)
 #pragma unroll
-        for (int j = 0; j < NL; ++j) R[i][j] = 0.0;
+            for (int j = 0; j < NL; ++j) R[i][j] = 0.0;
 #pragma unroll
-    for (int u = 1; u < NL; ++u)
+        for (int u = 1; u < NL; ++u)
 #pragma unroll
-        for (int l = 0; l < u; ++l) {
-            double cd = Cd[u * NL + l] * nc;
-            double cu = cd * (g[u] / g[l]) * exp(-(E[u] - E[l]));
-            R[u][l] += A[u * NL + l] + cd;
-            R[l][u] += cu;
+            for (int l = 0; l < u; ++l) {
+                const int p = level_pair(u, l);
+                const double cd = K->Cd[p] * nc;
+                R[u][l] = K->A[p] + cd;
+                R[l][u] = cd * K->gr[p] * K->ex[p];
+            }
+        if (jbar) {
+#pragma unroll
+            for (int l = 0; l + 1 < NL; ++l) {
+                const double G = K->gam[l] * (double)jbar[(int64_t)l * ncell + cl];
+                R[l][l + 1] += G;
+                R[l + 1][l] += K->gd[l] * G;
+            }
         }
-    const double kGam = 4.0 * 3.14159265358979323846 * 1.77245385090551602730;
-    if (jbar) {
 #pragma unroll
-        for (int l = 0; l + 1 < NL; ++l) {
-            double G = kGam * s0[l] * (double)jbar[(int64_t)l * ncell + c];
-            R[l][l + 1] += G;
-            R[l + 1][l] += (g[l] / g[l + 1]) * G;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        double out = 0.0;
-#pragma unroll
-        for (int j = 0; j < NL; ++j) {
-            M[i][j] = (j != i) ? R[j][i] : 0.0;
-            if (j != i) out += R[i][j];
-        }
-        M[i][i] = -out;
-        b[i] = 0.0;
-    }
-#pragma unroll
-    for (int j = 0; j < NL; ++j) M[NL - 1][j] = 1.0;
-    b[NL - 1] = ntot[c];
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        int p = k;
-        double mx = fabs(M[k][k]);
-#pragma unroll
-        for (int i = k + 1; i < NL; ++i) if (fabs(M[i][k]) > mx) { mx = fabs(M[i][k]); p = i; }
-#pragma unroll
-        for (int i = k + 1; i < NL; ++i) {
-            const bool sw = (i == p);
+        for (int i = 0; i < NL; ++i) {
+            double out = 0.0;
 #pragma unroll
             for (int j = 0; j < NL; ++j) {
-                const double t = M[k][j];
-                M[k][j] = sw ? M[i][j] : t;
-                M[i][j] = sw ? t : M[i][j];
+                M[i][j] = (j != i) ? R[j][i] : 0.0;
+                if (j != i) out += R[i][j];
             }
-            const double t = b[k];
-            b[k] = sw ? b[i] : t;
-            b[i] = sw ? t : b[i];
+            M[i][i] = -out;
+            b[i] = 0.0;
         }
 #pragma unroll
-        for (int i = k + 1; i < NL; ++i) {
-            double f = M[i][k] / M[k][k];
+        for (int j = 0; j < NL; ++j) M[NL - 1][j] = 1.0;
+        b[NL - 1] = ntot[cl];
 #pragma unroll
-            for (int j = k; j < NL; ++j) M[i][j] -= f * M[k][j];
-            b[i] -= f * b[k];
-        }
-    }
+        for (int k = 0; k < NL; ++k) {
+            int p = k;
+            double mx = fabs(M[k][k]);
 #pragma unroll
-    for (int i = NL - 1; i >= 0; --i) {
-        double s = b[i];
+            for (int i = k + 1; i < NL; ++i) if (fabs(M[i][k]) > mx) { mx = fabs(M[i][k]); p = i; }
 #pragma unroll
-        for (int j = i + 1; j < NL; ++j) s -= M[i][j] * b[j];
-        b[i] = s / M[i][i];
-    }
+            for (int i = k + 1; i < NL; ++i) {
+                const bool sw = (i == p);
 #pragma unroll
-    for (int i = 0; i < NL; ++i) pops[c * NL + i] = b[i];
-#pragma unroll
-    for (int l = 0; l + 1 < NL; ++l) {
-        int u = l + 1;
-        if (k0_out) k0_out[(int64_t)l * ncell + c] = (float)(b[l] * s0[l]);
-        // spontaneous emission of the line per unit volume, n_u A_ul (the
-        // Lambda iteration's source)
-        if (emis_out) emis_out[(int64_t)l * ncell + c] = (float)(b[u] * A[u * NL + l]);
-        if (eps_out) {
-            double ctot = 0.0;
-#pragma unroll
-            for (int j = 0; j < NL; ++j) if (j != u) {
-                double cd = (j < u) ? Cd[u * NL + j] * nc : Cd[j * NL + u] * nc * (g[j] / g[u]) * exp(-(E[j] - E[u]));
-                ctot += cd;
+                for (int j = k; j < NL; ++j) {
+                    const double t = M[k][j];
+                    M[k][j] = sw ? M[i][j] : t;
+                    M[i][j] = sw ? t : M[i][j];
+                }
+                const double t = b[k];
+                b[k] = sw ? b[i] : t;
+                b[i] = sw ? t : b[i];
             }
-            eps_out[(int64_t)l * ncell + c] = (float)(ctot / (A[u * NL + l] + ctot));
+#pragma unroll
+            for (int i = k + 1; i < NL; ++i) {
+                double f = M[i][k] / M[k][k];
+#pragma unroll
+                for (int j = k; j < NL; ++j) M[i][j] -= f * M[k][j];
+                b[i] -= f * b[k];
+            }
+        }
+#pragma unroll
+        for (int i = NL - 1; i >= 0; --i) {
+            double s = b[i];
+#pragma unroll
+            for (int j = i + 1; j < NL; ++j) s -= M[i][j] * b[j];
+            b[i] = s / M[i][i];
+        }
+#pragma unroll
+        for (int i = 0; i < NL; ++i) stage[w][NL * lane + i] = b[i];
+        __builtin_amdgcn_wave_barrier();
+        const int64_t wc = c - lane;  // the wave's first cell
+        const int64_t rest = (ncell - wc) * NL;
+        double *po = pops + wc * NL;
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            if (64 * i + lane < rest) po[64 * i + lane] = stage[w][64 * i + lane];
+        __builtin_amdgcn_wave_barrier();
+        if (!in) continue;
+        asm volatile("" : "+s"(K));
+#pragma unroll
+        for (int l = 0; l + 1 < NL; ++l) {
+            const int u = l + 1;
+            const double aul = K->A[level_pair(u, l)];
+            if (k0_out) k0_out[(int64_t)l * ncell + c] = (float)(b[l] * K->s0[l]);
+            // spontaneous emission of the line per unit volume, n_u A_ul (the
+            // Lambda iteration's source)
+            const double em = b[u] * aul;
+            if (emis_out) emis_out[(int64_t)l * ncell + c] = (float)em;
+            if constexpr (kPower) power[l] += em;
+            if (eps_out) {
+                double ctot = 0.0;
+#pragma unroll
+                for (int j = 0; j < NL; ++j) if (j != u) {
+                    const int p = (j < u) ? level_pair(u, j) : level_pair(j, u);
+                    const double cd = (j < u) ? K->Cd[p] * nc : K->Cd[p] * nc * K->gr[p] * K->ex[p];
+                    ctot += cd;
+                }
+                eps_out[(int64_t)l * ncell + c] = (float)(ctot / (aul + ctot));
+            }
         }
     }
+    if constexpr (kPower) {
+        __shared__ double red[kLevelThreads / 64][NL - 1];
+#pragma unroll
+        for (int l = 0; l + 1 < NL; ++l) {
+            double s = power[l];
+            for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+            if (lane == 0) red[w][l] = s;
+        }
+        __syncthreads();
+        if (threadIdx.x < NL - 1) {
+            double s = 0.0;
+            for (int k = 0; k < kLevelThreads / 64; ++k) s += red[k][threadIdx.x];
+            line_sums[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = s;
+        }
+    }
+}
+
+// Line powers from the workgroups' sums, in fixed order: one wave per line.
+// The result goes to pinned host memory, which a copy would reach only after
+// the kernel has ended.
+__global__ void __launch_bounds__(64) line_power_kernel(const double *sums, int n, double *out) {
+    const double *p = sums + (int64_t)blockIdx.x * n;
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = threadIdx.x; b < n; b += 64) s += p[b];
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 template <int NL>
-static void launch_levels_t(int64_t ncell, const double *consts, const double *ncoll, const double *ntot,
-                            const float *jbar, double *pops, float *k0_out, float *eps_out, float *emis_out,
-                            hipStream_t s) {
-    int grid = (int)((ncell + 255) / 256);
-    hipLaunchKernelGGL(levels_kernel<NL>, dim3(grid), dim3(256), 0, s, ncell, consts, ncoll, ntot, jbar, pops,
-                       k0_out, eps_out, emis_out);
-}
-
-hipError_t krt::launch_levels(int nl, int64_t ncell, const double *consts, const double *ncoll,
-                              const double *ntot, const float *jbar, double *pops, float *k0_out,
-                              float *eps_out, float *emis_out, hipStream_t s) {
-    switch (nl) {
-        case 2: launch_levels_t<2>(ncell, consts, ncoll, ntot, jbar, pops, k0_out, eps_out, emis_out, s); break;
-        case 3: launch_levels_t<3>(ncell, consts, ncoll, ntot, jbar, pops, k0_out, eps_out, emis_out, s); break;
-        case 4: launch_levels_t<4>(ncell, consts, ncoll, ntot, jbar, pops, k0_out, eps_out, emis_out, s); break;
-        case 5: launch_levels_t<5>(ncell, consts, ncoll, ntot, jbar, pops, k0_out, eps_out, emis_out, s); break;
-        case 6: launch_levels_t<6>(ncell, consts, ncoll, ntot, jbar, pops, k0_out, eps_out, emis_out, s); break;
-        case 7: launch_levels_t<7>(ncell, consts, ncoll, ntot, jbar, pops, k0_out, eps_out, emis_out, s); break;
-        case 8: launch_levels_t<8>(ncell, consts, ncoll, ntot, jbar, pops, k0_out, eps_out, emis_out, s); break;
-        default: return hipErrorInvalidValue;
+static hipError_t launch_levels(const krt_levels_desc &d, const float *jbar, double *line_sums, int blocks,
+                                hipStream_t s) {
+    const double kGam = 4.0 * 3.14159265358979323846 * 1.77245385090551602730;
+    LevelConsts<NL> K;
+    for (int u = 1; u < NL; ++u)
+        for (int l = 0; l < u; ++l) {
+            const int p = level_pair(u, l);
+            K.A[p] = d.A[u * NL + l];
+            K.Cd[p] = d.Cd[u * NL + l];
+            K.gr[p] = d.g[u] / d.g[l];
+            K.ex[p] = std::exp(-(d.E[u] - d.E[l]));
+        }
+    for (int l = 0; l + 1 < NL; ++l) {
+        K.gd[l] = d.g[l] / d.g[l + 1];
+        K.gam[l] = kGam * d.sigma0[l];
+        K.s0[l] = d.sigma0[l];
     }
+    if (line_sums)
+        hipLaunchKernelGGL((levels_kernel<NL, true>), dim3(blocks), dim3(kLevelThreads), 0, s, K, d.ncell, d.ncoll_dev,
+                           d.ntot_dev, jbar, d.pops_dev, d.k0_out_dev, d.eps_out_dev, d.emis_out_dev, line_sums);
+    else
+        hipLaunchKernelGGL((levels_kernel<NL, false>), dim3(blocks), dim3(kLevelThreads), 0, s, K, d.ncell, d.ncoll_dev,
+                           d.ntot_dev, jbar, d.pops_dev, d.k0_out_dev, d.eps_out_dev, d.emis_out_dev, line_sums);
     return hipGetLastError();
-}
-
-// Line powers: sum over cells of n_u A_ul for each line, FP64, deterministic
-// (per-block partial sums over fixed cell ranges, then a fixed-order sum).
-constexpr int kPowBlocks = 256;
-__global__ void __launch_bounds__(256) line_power_partial_kernel(int nl, int64_t ncell, const double *K,
-                                                                 const double *pops, double *partial) {
-    __shared__ double red[256];
-    const int line = blockIdx.y;
-    const int u = line + 1;
-    const double A_ul = K[2 * nl + u * nl + line];
-    const int64_t c0 = ncell * blockIdx.x / kPowBlocks, c1 = ncell * (blockIdx.x + 1) / kPowBlocks;
-    double acc = 0.0;
-    for (int64_t c = c0 + threadIdx.x; c < c1; c += blockDim.x) acc += pops[c * nl + u] * A_ul;
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int st = 128; st >= 1; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[line * kPowBlocks + blockIdx.x] = red[0];
-}
-
-__global__ void line_power_final_kernel(int nlines, const double *partial, double *out) {
-    const int line = threadIdx.x;
-    if (line >= nlines) return;
-    double s = 0.0;
-    for (int b = 0; b < kPowBlocks; ++b) s += partial[line * kPowBlocks + b];
-    out[line] = s;
 }
 
 extern "C" int krt_levels_update(krt_ctx *c, const krt_levels_desc *d, const float *jbar_dev) {
     if (!c) return KRT_EINVAL;
     if (!d) return fail(c, KRT_EINVAL, "levels desc NULL");
     const int nl = d->n_levels;
-    if (nl < 2 || nl > 8) return fail(c, KRT_EINVAL, "n_levels %d outside 2..8", nl);
+    if (nl < 2 || nl > kMaxLevels) return fail(c, KRT_EINVAL, "n_levels %d outside 2..8", nl);
     if (d->ncell < 1 || d->ncell >= (int64_t(1) << 31)) return fail(c, KRT_EINVAL, "levels ncell %lld", (long long)d->ncell);
     if (!d->E || !d->g || !d->A || !d->Cd || !d->sigma0 || !d->ncoll_dev || !d->ntot_dev || !d->pops_dev)
         return fail(c, KRT_EINVAL, "levels desc has NULL arrays");
-    std::vector<double> K;
-    K.insert(K.end(), d->E, d->E + nl);
-    K.insert(K.end(), d->g, d->g + nl);
-    K.insert(K.end(), d->A, d->A + nl * nl);
-    K.insert(K.end(), d->Cd, d->Cd + nl * nl);
-    K.insert(K.end(), d->sigma0, d->sigma0 + (nl - 1));
-    for (double v : K) if (!std::isfinite(v)) return fail(c, KRT_EINVAL, "non-finite level constant");
+    auto finite = [](const double *v, int n) {
+        for (int k = 0; k < n; ++k) if (!std::isfinite(v[k])) return false;
+        return true;
+    };
+    if (!finite(d->E, nl) || !finite(d->g, nl) || !finite(d->A, nl * nl) || !finite(d->Cd, nl * nl) ||
+        !finite(d->sigma0, nl - 1))
+        return fail(c, KRT_EINVAL, "non-finite level constant");
     HIPCHK(c, hipSetDevice(c->device));
-    HIPCHK(c, hipMemcpyAsync(c->level_consts, K.data(), sizeof(double) * K.size(), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, launch_levels(nl, d->ncell, c->level_consts, d->ncoll_dev, d->ntot_dev, jbar_dev, d->pops_dev,
-                            d->k0_out_dev, d->eps_out_dev, d->emis_out_dev, c->stream));
+    const bool volume_ok = d->cell_volume > 0.0 && std::isfinite(d->cell_volume);
+    double *sums = nullptr;
+    if (d->lum_out && volume_ok) {
+        if (!c->level_power) HIPCHK(c, hipMalloc(&c->level_power, sizeof(double) * kMaxLevels * kLevelBlocks));
+        sums = c->level_power;
+    }
+    const int blocks = (int)std::min<int64_t>((d->ncell + kLevelThreads - 1) / kLevelThreads, kLevelBlocks);
+    hipError_t e = hipErrorInvalidValue;
+    switch (nl) {
+        case 2: e = launch_levels<2>(*d, jbar_dev, sums, blocks, c->stream); break;
+        case 3: e = launch_levels<3>(*d, jbar_dev, sums, blocks, c->stream); break;
+        case 4: e = launch_levels<4>(*d, jbar_dev, sums, blocks, c->stream); break;
+        case 5: e = launch_levels<5>(*d, jbar_dev, sums, blocks, c->stream); break;
+        case 6: e = launch_levels<6>(*d, jbar_dev, sums, blocks, c->stream); break;
+        case 7: e = launch_levels<7>(*d, jbar_dev, sums, blocks, c->stream); break;
+        case 8: e = launch_levels<8>(*d, jbar_dev, sums, blocks, c->stream); break;
+    }
+    HIPCHK(c, e);
     if (d->lum_out) {
-        if (!(d->cell_volume > 0.0) || !std::isfinite(d->cell_volume))
-            return fail(c, KRT_EINVAL, "lum_out needs a finite cell_volume > 0");
-        if (!c->level_power) HIPCHK(c, hipMalloc(&c->level_power, sizeof(double) * 8 * (kPowBlocks + 1)));
-        double *partial = c->level_power, *sums = c->level_power + 8 * kPowBlocks;
-        hipLaunchKernelGGL(line_power_partial_kernel, dim3(kPowBlocks, nl - 1), dim3(256), 0, c->stream, nl,
-                           (int64_t)d->ncell, (const double *)c->level_consts, (const double *)d->pops_dev, partial);
+        if (!volume_ok) return fail(c, KRT_EINVAL, "lum_out needs a finite cell_volume > 0");
+        double *host = reinterpret_cast<double *>(c->host_pinned);
+        static_assert(sizeof(double) == sizeof(int64_t), "the pinned words hold the powers");
+        hipLaunchKernelGGL(line_power_kernel, dim3(nl - 1), dim3(64), 0, c->stream, (const double *)sums, blocks, host);
         HIPCHK(c, hipGetLastError());
-        hipLaunchKernelGGL(line_power_final_kernel, dim3(1), dim3(64), 0, c->stream, nl - 1, (const double *)partial,
-                           sums);
-        HIPCHK(c, hipGetLastError());
-        double host[8];
-        HIPCHK(c, hipMemcpyAsync(host, sums, sizeof(double) * (nl - 1), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
         for (int l = 0; l + 1 < nl; ++l) d->lum_out[l] = host[l] * d->cell_volume;
+        return KRT_OK;
     }
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return KRT_OK;

@@ -207,8 +207,5 @@ hipError_t launch_mlp_norm(const float *rec, int64_t n, double *scratch, float *
 hipError_t launch_mlp_calib(const unsigned char *blob, const float *rec, int64_t n, double *sums, float *norm,
                             hipStream_t s);
 hipError_t launch_mlp_forward(const unsigned char *blob, const float *inp, int64_t n, float *out, hipStream_t s);
-hipError_t launch_levels(int nl, int64_t ncell, const double *consts, const double *ncoll,
-                         const double *ntot, const float *jbar, double *pops, float *k0_out,
-                         float *eps_out, float *emis_out, hipStream_t s);
 
 }  // namespace krt
