@@ -9,19 +9,24 @@
 //   an optional grey absorption, zero when absent),
 // with x_k the lab-frame centre of channel k.
 //
-// Layout.  One lane per (pixel, channel); a wave holds 64 consecutive
-// (pixel, channel) pairs, so its lanes read a cell's fields at one address
-// per pixel of the wave (one or two at 32 channels or more) and the emissivity of consecutive channels from
-// consecutive addresses: the pass streams the emissivity array once.  The
+// Layout.  One lane per pixel and four consecutive channels (one channel in
+// small images), so the lanes of a wave read the emissivity of consecutive
+// channels from consecutive addresses and a cell's fields at one address per
+// pixel of the wave: the pass streams the emissivity array once.  The
 // Voigt table sits in LDS.  The recurrence is affine in I, so a ray can be
 // cut into segments: the wave of segment s folds its cells into a map
 // I -> A_s I + B_s, and the maps are composed in order, far side first,
 // through LDS.  Short rays on small grids take several segments so that the
 // launch still fills the chip; long ones take one.  A wave issues the loads
 // of a chunk of cells together and then folds them in order (the march is a
-// dependent chain, its memory is not); memory latency is hidden by the other
-// waves on the SIMD (eight without a source function), whose number a second
-// register buffer for the next chunk would halve.
+// dependent chain, its memory is not).
+//
+// Memory bounds it: along z and y the cells of a ray are megabytes apart, and
+// what counts is how much a wave takes from each place.  128^3 x 64 channels,
+// velocity, source function and absorption, toward -z (1.1 GB): 258 us with
+// one channel a lane (256 bytes a cell and wave), 212 us with four (1 KB;
+// 5.2 TB/s, the rate of a copy).  More waves with shorter chunks (eight per
+// SIMD) only spread the same reads over more places: 400 us.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -34,31 +39,49 @@
 namespace krt {
 
 constexpr int kImgVoigtFloats = kOffVoigtWing + 4 * kVoigtWingN;  // core and wing of H(a, x)
-constexpr int kImgChunk = 8;            // cells whose loads are in flight together
+// cells whose loads are in flight together
+template <int V>
+constexpr int kImgChunk = V == 1 ? 8 : 4;
 constexpr int kImgWaves = 8;            // waves per block
 constexpr int kImgMaxSeg = kImgWaves;   // segments of one ray (waves of one block)
 constexpr int kImgMinSegCells = 4;      // shortest segment worth a wave
-constexpr int64_t kImgTargetWaves = 16384;  // twice the chip's resident waves at 8 per SIMD
+constexpr int64_t kImgTargetWaves = 16384;  // twice the chip's resident waves at 8 per SIMD, at one channel a lane
+constexpr int64_t kImgQuadWaves = 2048;     // two per SIMD
 
 // fields of a chunk of cells along the ray (the arrays a kernel instance does
 // not read are never written and cost nothing)
+template <int V>
 struct ImgChunk {
-    float k0[kImgChunk], v[kImgChunk], ab[kImgChunk], j[kImgChunk], s[kImgChunk];
+    float k0[kImgChunk<V>], v[kImgChunk<V>], ab[kImgChunk<V>], j[kImgChunk<V>][V], s[kImgChunk<V>][V];
 };
 
-// loads of cells t .. t + m - 1 of the segment (m <= kImgChunk, compile-time
-// in the full-chunk path); cell t sits at offset o (fields) and o * nch (channels)
-template <bool kVel, bool kAbs, bool kSrc, int M>
+// V consecutive channels.  Four a lane are read as a stream (128^3 x 64: 143 us,
+// plain 151); one a lane is the path of small images and few channels, where
+// other waves read the rest of a line (100^3 x 9 channels: 33 us plain, 37 us
+// as a stream).
+template <int V>
+__device__ __forceinline__ void img_stream(const float *p, float (&o)[V]) {
+    typedef float vec __attribute__((ext_vector_type(V), aligned(4)));
+    vec x;
+    if constexpr (V == 1) x = *reinterpret_cast<const vec *>(p);
+    else x = __builtin_nontemporal_load(reinterpret_cast<const vec *>(p));
+#pragma unroll
+    for (int k = 0; k < V; ++k) o[k] = x[k];
+}
+
+// loads of cells t .. t + M - 1 of the segment; cell t sits at offset o
+// (fields) and o * nch (channels)
+template <int V, bool kVel, bool kAbs, bool kSrc, int M>
 __device__ __forceinline__ void img_load(const ImageParams &Q, int64_t o, int64_t step, int64_t cstep,
-                                         const float *pe, const float *ps, ImgChunk &b) {
+                                         const float *pe, const float *ps, ImgChunk<V> &b) {
 #pragma unroll
     for (int u = 0; u < M; ++u) {
         const int64_t oc = o + u * step;
         b.k0[u] = Q.k0[oc];
         if constexpr (kVel) b.v[u] = Q.vel_axis[oc];
         if constexpr (kAbs) b.ab[u] = Q.kabs[oc];
-        b.j[u] = pe[u * cstep];
-        if constexpr (kSrc) b.s[u] = ps[u * cstep];
+        img_stream<V>(pe + u * cstep, b.j[u]);
+        if constexpr (kSrc) img_stream<V>(ps + u * cstep, b.s[u]);
     }
 }
 
@@ -76,27 +99,29 @@ __device__ __forceinline__ float img_voigt(const float *T, float xa) {
     return core ? G : G * w * w * (1.0f / 64.0f);
 }
 
-template <bool kVel, bool kAbs, bool kSrc, int M>
-__device__ __forceinline__ void img_fold(const ImageParams &Q, const float *TV, float xk,
-                                         const ImgChunk &b, float &A, float &B) {
+template <int V, bool kVel, bool kAbs, bool kSrc, int M>
+__device__ __forceinline__ void img_fold(const ImageParams &Q, const float *TV, const float (&xk)[V],
+                                         const ImgChunk<V> &b, float (&A)[V], float (&B)[V]) {
 #pragma unroll
-    for (int u = 0; u < M; ++u) {
-        const float xg = kVel ? xk - Q.sgnf * b.v[u] : xk;
-        const float H = (b.k0[u] > 0.0f) ? img_voigt(TV, fabsf(xg)) : 0.0f;
-        const float dtau = (kAbs ? fmaf(b.k0[u], H, b.ab[u]) : b.k0[u] * H) * Q.dl;
-        const float att = f_exp(-dtau);
-        // (1 - e^{-dtau}) / dtau, with its series below 1e-3
-        const float frac = (dtau < 1e-3f) ? 1.0f - dtau * (0.5f - dtau * (1.0f / 6.0f)) : (1.0f - att) * f_rcp(dtau);
-        B = fmaf(B, att, b.j[u] * Q.dl * frac);
-        if constexpr (kSrc) B = fmaf(b.s[u], dtau * frac, B);
-        A *= att;
-    }
+    for (int u = 0; u < M; ++u)
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const float xg = kVel ? xk[k] - Q.sgnf * b.v[u] : xk[k];
+            const float H = (b.k0[u] > 0.0f) ? img_voigt(TV, fabsf(xg)) : 0.0f;
+            const float dtau = (kAbs ? fmaf(b.k0[u], H, b.ab[u]) : b.k0[u] * H) * Q.dl;
+            const float att = f_exp(-dtau);
+            // (1 - e^{-dtau}) / dtau, with its series below 1e-3
+            const float frac = (dtau < 1e-3f) ? 1.0f - dtau * (0.5f - dtau * (1.0f / 6.0f)) : (1.0f - att) * f_rcp(dtau);
+            B[k] = fmaf(B[k], att, b.j[u][k] * Q.dl * frac);
+            if constexpr (kSrc) B[k] = fmaf(b.s[u][k], dtau * frac, B[k]);
+            A[k] *= att;
+        }
 }
 
-template <bool kVel, bool kAbs, bool kSrc>
+template <int V, bool kVel, bool kAbs, bool kSrc>
 __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int seglen) {
     __shared__ float4 tv4[kImgVoigtFloats / 4];
-    __shared__ float2 part[kImgWaves][64];  // (A_s, B_s) of every wave's segment
+    __shared__ float2 part[kImgWaves][V][64];  // (A_s, B_s) of every wave's segment
     float *TV = reinterpret_cast<float *>(tv4);
     const float4 *src = reinterpret_cast<const float4 *>(Q.tab);
     for (int i = threadIdx.x; i < kImgVoigtFloats / 4; i += blockDim.x) tv4[i] = src[i];
@@ -104,13 +129,19 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int seg = wave % nseg;                // segment of the ray, far side = 0
-    const int grp = wave / nseg;                // group of 64 (pixel, channel) pairs
+    const int grp = wave / nseg;                // group of 64 lanes' (pixel, V channels)
     const int64_t tid = ((int64_t)blockIdx.x * (kImgWaves / nseg) + grp) * 64 + lane;
-    const bool live = tid < Q.npix * (int64_t)Q.nch;
-    float A = 1.0f, B = 0.0f;
+    const int per = (Q.nch + V - 1) / V;        // lanes of a pixel
+    const int64_t pix = tid / per;
+    // the last lane of a pixel takes its last V channels: where V does not
+    // divide nch it repeats some of its neighbour's, to the same bits
+    const int c = min((int)(tid - pix * per) * V, Q.nch - V);
+    const bool live = pix < Q.npix;
+    float *out = Q.out + pix * Q.nch + c;
+    float A[V], B[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) { A[k] = 1.0f; B[k] = 0.0f; }
     if (live) {
-        const int64_t pix = tid / Q.nch;
-        const int c = (int)(tid - pix * Q.nch);
         // pixel -> first cell of its column and the stride along the ray
         const int p0 = (int)(pix % Q.n0), p1 = (int)(pix / Q.n0);
         int64_t cell0;
@@ -125,74 +156,108 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
         int64_t o = cell0 + (int64_t)(Q.sgn > 0 ? t0 : nl - 1 - t0) * Q.stride;
         const float *pe = Q.emis + o * Q.nch + c;
         const float *ps = kSrc ? Q.srcf + o * Q.nch + c : nullptr;
-        const float xk = Q.ch_lo + ((float)c + 0.5f) * Q.ch_w;
-        const int nfull = max(0, t1 - t0) / kImgChunk;
-        ImgChunk cur{};
+        float xk[V];
+#pragma unroll
+        for (int k = 0; k < V; ++k) xk[k] = Q.ch_lo + ((float)(c + k) + 0.5f) * Q.ch_w;
+        const int nfull = max(0, t1 - t0) / kImgChunk<V>;
+        ImgChunk<V> cur{};
         for (int i = 0; i < nfull; ++i) {
-            img_load<kVel, kAbs, kSrc, kImgChunk>(Q, o, step, cstep, pe, ps, cur);
-            img_fold<kVel, kAbs, kSrc, kImgChunk>(Q, TV, xk, cur, A, B);
-            o += kImgChunk * step;
-            pe += kImgChunk * cstep;
-            if constexpr (kSrc) ps += kImgChunk * cstep;
+            img_load<V, kVel, kAbs, kSrc, kImgChunk<V>>(Q, o, step, cstep, pe, ps, cur);
+            img_fold<V, kVel, kAbs, kSrc, kImgChunk<V>>(Q, TV, xk, cur, A, B);
+            o += kImgChunk<V> * step;
+            pe += kImgChunk<V> * cstep;
+            if constexpr (kSrc) ps += kImgChunk<V> * cstep;
         }
-        for (int t = t0 + nfull * kImgChunk; t < t1; ++t) {  // ragged end of the segment
-            img_load<kVel, kAbs, kSrc, 1>(Q, o, step, cstep, pe, ps, cur);
-            img_fold<kVel, kAbs, kSrc, 1>(Q, TV, xk, cur, A, B);
+        for (int t = t0 + nfull * kImgChunk<V>; t < t1; ++t) {  // ragged end of the segment
+            img_load<V, kVel, kAbs, kSrc, 1>(Q, o, step, cstep, pe, ps, cur);
+            img_fold<V, kVel, kAbs, kSrc, 1>(Q, TV, xk, cur, A, B);
             o += step;
             pe += cstep;
             if constexpr (kSrc) ps += cstep;
         }
     }
     if (nseg == 1) {
-        if (live) Q.out[tid] = B;
+        if (live) {
+#pragma unroll
+            for (int k = 0; k < V; ++k) out[k] = B[k];
+        }
         return;
     }
-    part[wave][lane] = make_float2(A, B);
+#pragma unroll
+    for (int k = 0; k < V; ++k) part[wave][k][lane] = make_float2(A[k], B[k]);
     __syncthreads();
     if (seg == 0 && live) {
-        float I = 0.0f;
-        for (int s = 0; s < nseg; ++s) {
-            const float2 p = part[wave + s][lane];
-            I = fmaf(p.x, I, p.y);
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            float I = 0.0f;
+            for (int s = 0; s < nseg; ++s) {
+                const float2 p = part[wave + s][k][lane];
+                I = fmaf(p.x, I, p.y);
+            }
+            out[k] = I;
         }
-        Q.out[tid] = I;
     }
 }
 
-// Without a source function the fold fits the register budget of eight
-// waves per SIMD (64 VGPRs), the occupancy that hides the memory latency;
-// with one it would spill, so that kernel keeps the compiler's budget.
+// Without a source function the fold of one channel a lane fits the register
+// budget of eight waves per SIMD (64 VGPRs), the occupancy that hides the
+// memory latency; the others would spill and keep the compiler's budget.
 template <bool kVel, bool kAbs>
 __global__ void __launch_bounds__(64 * kImgWaves) __attribute__((amdgpu_waves_per_eu(8, 8)))
 image_kernel(ImageParams Q, int nseg, int seglen) {
-    image_body<kVel, kAbs, false>(Q, nseg, seglen);
+    image_body<1, kVel, kAbs, false>(Q, nseg, seglen);
 }
 
 template <bool kVel, bool kAbs>
 __global__ void __launch_bounds__(64 * kImgWaves) image_src_kernel(ImageParams Q, int nseg, int seglen) {
-    image_body<kVel, kAbs, true>(Q, nseg, seglen);
+    image_body<1, kVel, kAbs, true>(Q, nseg, seglen);
 }
 
 template <bool kVel, bool kAbs, bool kSrc>
-static void launch_image_t(const ImageParams &Q, int nseg, int seglen, int64_t blocks, hipStream_t s,
-                           hipEvent_t start, hipEvent_t stop) {
-    if constexpr (kSrc)
-        hipExtLaunchKernelGGL((image_src_kernel<kVel, kAbs>), dim3((unsigned)blocks), dim3(64 * kImgWaves), 0, s,
-                              start, stop, 0, Q, nseg, seglen);
-    else
-        hipExtLaunchKernelGGL((image_kernel<kVel, kAbs>), dim3((unsigned)blocks), dim3(64 * kImgWaves), 0, s,
-                              start, stop, 0, Q, nseg, seglen);
+__global__ void __launch_bounds__(64 * kImgWaves) image_quad_kernel(ImageParams Q, int nseg, int seglen) {
+    image_body<4, kVel, kAbs, kSrc>(Q, nseg, seglen);
 }
 
-// segments per ray: doubled while the launch has fewer waves than the chip
-// keeps busy and the segments stay at least kImgMinSegCells cells long
-static int image_segments(int64_t npix, int nch, int nl) {
-    const int64_t groups = (npix * nch + 63) / 64;
-    int nseg = 1;
-    while (nseg < kImgMaxSeg && groups * nseg < kImgTargetWaves &&
-           (nl + 2 * nseg - 1) / (2 * nseg) >= kImgMinSegCells)
-        nseg *= 2;
-    return nseg;
+struct ImgPlan {
+    int v, nseg;
+    int64_t groups;  // waves per segment
+};
+
+template <bool kVel, bool kAbs, bool kSrc>
+static void launch_image_t(const ImageParams &Q, const ImgPlan &p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+    const int nl = Q.n[Q.d], seglen = (nl + p.nseg - 1) / p.nseg;
+    const int64_t per_block = kImgWaves / p.nseg;
+    const dim3 grid((unsigned)((p.groups + per_block - 1) / per_block)), block(64 * kImgWaves);
+    if (p.v == 4)
+        hipExtLaunchKernelGGL((image_quad_kernel<kVel, kAbs, kSrc>), grid, block, 0, s, start, stop, 0, Q, p.nseg, seglen);
+    else if constexpr (kSrc)
+        hipExtLaunchKernelGGL((image_src_kernel<kVel, kAbs>), grid, block, 0, s, start, stop, 0, Q, p.nseg, seglen);
+    else
+        hipExtLaunchKernelGGL((image_kernel<kVel, kAbs>), grid, block, 0, s, start, stop, 0, Q, p.nseg, seglen);
+}
+
+// Channels a lane and segments of a ray: segments are doubled while the launch
+// has fewer waves than keep the chip busy and they stay at least
+// kImgMinSegCells cells long.
+static ImgPlan image_plan(int64_t npix, int nch, int nl, int v) {
+    ImgPlan p{v, 1, (npix * ((nch + v - 1) / v) + 63) / 64};
+    while (p.nseg < kImgMaxSeg && p.groups * p.nseg < kImgTargetWaves / v &&
+           (nl + 2 * p.nseg - 1) / (2 * p.nseg) >= kImgMinSegCells)
+        p.nseg *= 2;
+    return p;
+}
+
+// Four channels a lane (16-byte loads, 1 KB of a cell's channels a wave) where
+// that leaves kImgQuadWaves waves of full lanes; below, the march's latency
+// bounds the launch and one channel a lane has four times the waves.
+// Kernel times, one channel a lane / four, above the line: 32^3 x 64 with
+// source 8.6 / 6.8 us, 64^3 x 32 15.3 / 10.8, 100^3 x 9 32.7 / 28.8, 90^3 x 63
+// with source 132 / 94; below: 32^3 x 32 4.4 / 5.6, 40^3 x 32 6.3 / 7.2,
+// 64^3 x 5 7.8 / 9.3 (its second lane repeats three channels), 100^3 x 5 with
+// source 22.2 / 26.9.
+static ImgPlan image_plan(int64_t npix, int nch, int nl) {
+    const ImgPlan quad = image_plan(npix, nch, nl, 4);
+    return nch >= 4 && npix * nch / 256 * quad.nseg >= kImgQuadWaves ? quad : image_plan(npix, nch, nl, 1);
 }
 
 hipError_t launch_image_timed(const ImageParams &Q, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
@@ -202,22 +267,17 @@ hipError_t launch_image_timed(const ImageParams &Q, hipStream_t s, hipEvent_t st
         if (stop) { hipError_t e = hipEventRecord(stop, s); if (e != hipSuccess) return e; }
         return hipSuccess;
     }
-    const int nl = Q.n[Q.d];
-    const int nseg = image_segments(Q.npix, Q.nch, nl);
-    const int seglen = (nl + nseg - 1) / nseg;
-    const int64_t groups = (n + 63) / 64;
-    const int64_t per_block = kImgWaves / nseg;
-    const int64_t blocks = (groups + per_block - 1) / per_block;
+    const ImgPlan p = image_plan(Q.npix, Q.nch, Q.n[Q.d]);
     const int key = (Q.vel_axis ? 4 : 0) | (Q.kabs ? 2 : 0) | (Q.srcf ? 1 : 0);
     switch (key) {
-        case 0: launch_image_t<false, false, false>(Q, nseg, seglen, blocks, s, start, stop); break;
-        case 1: launch_image_t<false, false, true>(Q, nseg, seglen, blocks, s, start, stop); break;
-        case 2: launch_image_t<false, true, false>(Q, nseg, seglen, blocks, s, start, stop); break;
-        case 3: launch_image_t<false, true, true>(Q, nseg, seglen, blocks, s, start, stop); break;
-        case 4: launch_image_t<true, false, false>(Q, nseg, seglen, blocks, s, start, stop); break;
-        case 5: launch_image_t<true, false, true>(Q, nseg, seglen, blocks, s, start, stop); break;
-        case 6: launch_image_t<true, true, false>(Q, nseg, seglen, blocks, s, start, stop); break;
-        default: launch_image_t<true, true, true>(Q, nseg, seglen, blocks, s, start, stop); break;
+        case 0: launch_image_t<false, false, false>(Q, p, s, start, stop); break;
+        case 1: launch_image_t<false, false, true>(Q, p, s, start, stop); break;
+        case 2: launch_image_t<false, true, false>(Q, p, s, start, stop); break;
+        case 3: launch_image_t<false, true, true>(Q, p, s, start, stop); break;
+        case 4: launch_image_t<true, false, false>(Q, p, s, start, stop); break;
+        case 5: launch_image_t<true, false, true>(Q, p, s, start, stop); break;
+        case 6: launch_image_t<true, true, false>(Q, p, s, start, stop); break;
+        default: launch_image_t<true, true, true>(Q, p, s, start, stop); break;
     }
     return hipGetLastError();
 }
