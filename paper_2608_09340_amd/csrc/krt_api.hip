@@ -549,7 +549,11 @@ static int run_parked(krt_ctx *c, const RunParams &P0, uint64_t n_packets, uint6
 // are.  Random cells miss the caches for every field, so where packets mostly
 // cross cells the walk is bound by the lines it fetches; the records are made
 // anew at each run (the fields are the caller's and may have changed), which
-// costs about 25 us for 128^3 cells, so they pay from some packets per cell on.
+// costs about 25 us for 128^3 cells, so they pay from a packet in eight cells
+// on.  Fields apart / records: two lines of a Lambda cycle on a 128^3 cloud, 2e6
+// packets each, 4.87 / 4.25 ms; the learned walk there 95.5 / 93.1 ms.  Walks
+// that seldom cross keep the fields (expanding sphere: a record adds a test to
+// every crossing for nothing, 3%).
 // Used by the plain walk of profile mode 0 where a destruction or absorption
 // field makes short walks, and by the learned walk of the default geometry.
 constexpr int64_t kMaxRecordCells = int64_t(1) << 27;

@@ -1,6 +1,6 @@
-// krt_mlp.h -- the learned whole-cell escape: layout constants and the
-// BF16-MFMA forward pass shared by the transport kernel (inference) and the
-// training kernels.  Not part of the C ABI.
+// krt_mlp.h -- the learned whole-cell escape: layout constants, shared by the
+// training kernels, and the BF16-MFMA forward pass of inference (transport,
+// calibration, batched evaluation).  Not part of the C ABI.
 //
 // The network describes how a photon that scatters inside a homogeneous static
 // cubic cell leaves it.  Conditions are taken in the cell's reduced frame: the
@@ -191,9 +191,7 @@ __device__ __forceinline__ v8i16 tileA(const unsigned char *blob, int t, int lan
 // Forward pass of one 16-sample block.  xin: this lane's B operand for layer 1
 // (lane l holds inputs 8(l/16)..8(l/16)+7 of sample l%16).  Returns the two
 // output tiles: lane l holds outputs 4(l/16)+r (oa) and 16+4(l/16)+r (ob) of
-// sample l%16.  epi(layer, tile, z) sees each hidden layer's pre-activations
-// (layer 0..2, row tile 0..7) before the activation: the training pass stores
-// what its backward pass needs; inference passes NoEpi.
+// sample l%16.
 //
 // The 80 products run in one fixed order (fwd_tile): layer 1's 8 row tiles,
 // layers 2 and 3 chunk-major (the 8 row tiles of reduction chunk c, then
@@ -219,13 +217,8 @@ static_assert(kTilesFwd == kFwdSteps, "one product per forward tile");
 
 __device__ __forceinline__ v4f32 ld4(const float *p) { return *reinterpret_cast<const v4f32 *>(p); }
 
-struct NoEpi {
-    __device__ __forceinline__ void operator()(int, int, const v4f32 &) const {}
-};
-
-template <class Epi>
 __device__ __forceinline__ void mlp_forward_block(const unsigned char *tiles, const float *bias, v8i16 xin,
-                                                  int lane, Epi epi, v4f32 &oa, v4f32 &ob) {
+                                                  int lane, v4f32 &oa, v4f32 &ob) {
     const int g = lane >> 4;
     v8i16 w[8];
 #pragma unroll
@@ -246,7 +239,6 @@ __device__ __forceinline__ void mlp_forward_block(const unsigned char *tiles, co
     for (int mo = 0; mo < 8; ++mo) KRT_FWD_STEP(mo, xin, acc[mo]);
 #pragma unroll
     for (int mo = 0; mo < 8; ++mo) {
-        epi(0, mo, acc[mo]);
         h[mo] = pack4(leaky(acc[mo].x), leaky(acc[mo].y), leaky(acc[mo].z), leaky(acc[mo].w));
         acc[mo] = ld4(bias + kMlpHid + 16 * mo + 4 * g);
     }
@@ -262,7 +254,6 @@ __device__ __forceinline__ void mlp_forward_block(const unsigned char *tiles, co
         }
 #pragma unroll
         for (int mo = 0; mo < 8; ++mo) {
-            epi(1 + layer, mo, acc[mo]);
             h[mo] = pack4(leaky(acc[mo].x), leaky(acc[mo].y), leaky(acc[mo].z), leaky(acc[mo].w));
             if (layer == 0) acc[mo] = ld4(bias + 2 * kMlpHid + 16 * mo + 4 * g);
         }

@@ -7,8 +7,9 @@
 // segment (to its next interaction or to the next cell face) and, on an
 // interaction, one resonant scattering.  Fields are SoA binary32 read once per
 // cell entry; the per-line Voigt and atom-velocity tables live in LDS.
-// Tallies are int64 fixed point: per-lane register caches for the current
-// cell, flushed with one atomic per (cell, channel) when the packet leaves.
+// Tallies are int64 fixed point: a window of channels per lane for the current
+// cell, written back with one atomic per (cell, channel) met when the packet
+// leaves.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -25,7 +26,7 @@ namespace krt {
 
 // --------------------------------------------------------- tally helpers ---
 // Integer tally atomics return nothing, so a wave never waits on them; sums
-// past 2^62 are detected after the launch (saturation_check_kernel).
+// past 2^62 are detected after the launch (finish_kernel).
 __device__ __forceinline__ void tally_add_i64(int64_t *p, int64_t v) {
     atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
 }
@@ -134,7 +135,7 @@ __device__ __forceinline__ void mlp_eval_wave(const unsigned char *img, const fl
         const v4i16 hi = {(short)(use ? w[2] & 0xFFFFu : 0u), (short)(use ? w[2] >> 16 : 0u),
                           (short)(use ? w[3] & 0xFFFFu : 0u), (short)(use ? w[3] >> 16 : 0u)};
         v4f32 oa, ob;
-        mlp_forward_block(img, bias, cat8(lo, hi), lane, NoEpi{}, oa, ob);
+        mlp_forward_block(img, bias, cat8(lo, hi), lane, oa, ob);
         // output k of block position p sits in lane 16 ((k % 16) / 4) + p,
         // component k % 4, of tile k / 16
         const bool take = mine && (rank >> 4) == b;
@@ -424,6 +425,12 @@ __device__ __forceinline__ float face_dist(float n, float f, float dx) {
 // unless the frequency is within rounding of a bin edge.  Every product and sum
 // is a fixed one (fmaf where it is fused, contraction off otherwise), so that
 // all variants walk a packet through the same numbers.
+// Measured against the walk of nested branches that scattered ahead of the
+// flight: expanding 128^3 sphere, 4e6 packets (full waves) 5.4e10 to 1.0e11
+// scatterings/s; the longest packet of a thick slab 1146 to 605 ns an event
+// without an emissivity tally, 1708 to 718 with 32 channels.
+// 1024 lanes (16 waves) share a workgroup's copy of the tables in LDS.
+//
 // The launch's parameters re-read where they are used: for the paths a packet
 // takes rarely (crossings, refills, retirements).  Read through P the compiler
 // keeps them all in scalar registers across the loop, which are too few, and
