@@ -479,7 +479,15 @@ static_assert(kActZ4 + 2 == kActTiles, "activation store layout");
 // and 6.7 with plain stores and 12.3 and 9.0 with nontemporal ones, which the
 // memory-side cache does not keep.  8192 samples: 28 us before (16 samples a
 // wave, rows of the store written 2 bytes at a time), 11.9 us now.
-__global__ void __launch_bounds__(512) mlp_fwdbwd_kernel(const unsigned char *blob, const uint32_t *rows, int batch,
+//
+// kPair, for more chunks than compute units: tiles are asked for one layer
+// ahead only, so that two workgroups share a compute unit (128 registers) and
+// one's chain covers the other's waits.  A step of 8704 samples 25.7 us without
+// / 24.6 with, 16384: 36.3 / 31.4, 100000: 128 / 112; up to a workgroup per unit
+// there is nothing to cover (8192: 19.2 / 19.4).
+constexpr int kChipCUs = 256;
+template <bool kPair>
+__global__ void __launch_bounds__(512, kPair ? 4 : 2) mlp_fwdbwd_kernel(const unsigned char *blob, const uint32_t *rows, int batch,
                                                          unsigned char *act, float *loss) {
     __shared__ __align__(16) v4i16 ex[2][4][2][64][2];  // operand chunks between layers, double-buffered
     __shared__ __align__(16) uint16_t tr[32][40];       // 32 features x 32 samples, turned (inputs, then dZ4)
@@ -513,9 +521,12 @@ __global__ void __launch_bounds__(512) mlp_fwdbwd_kernel(const unsigned char *bl
     tiles(w2, kTileFwdL2 + 4 * w);
     biases(1);
     __builtin_amdgcn_sched_barrier(0);
-    tiles(w3, kTileFwdL3 + 4 * w);
-    biases(2);
-    __builtin_amdgcn_sched_barrier(0);
+    auto third = [&]() {
+        tiles(w3, kTileFwdL3 + 4 * w);
+        biases(2);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (!kPair) third();
 
     // the inputs' tiles of the store, turned by waves 0 and 1
     if (w < 2) {
@@ -580,6 +591,13 @@ __global__ void __launch_bounds__(512) mlp_fwdbwd_kernel(const unsigned char *bl
     start(0);
     product(w1, 0);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kPair) third();
+    layer_out(0, kActH1);
+    if (w < 2) put_turned(kActH0 + w);
+    if constexpr (kPair) {
+        hidden(w2, 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     tiles(w4, kTileFwdL4 + 4 * ot);
     const v4f32 bo = ld4(bias + 3 * kMlpHid + 16 * ot + 4 * g);
     // this lane's row of the losses
@@ -588,17 +606,24 @@ __global__ void __launch_bounds__(512) mlp_fwdbwd_kernel(const unsigned char *bl
     const float scn = norm[kMlpOut + kOutLogN];
     v4 = tileA(blob, kTileBwdL4 + w, lane);
     __builtin_amdgcn_sched_barrier(0);
-    layer_out(0, kActH1);
-    if (w < 2) put_turned(kActH0 + w);
-    hidden(w2, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    tiles(v3, kTileBwdL3 + 4 * w);
-    __builtin_amdgcn_sched_barrier(0);
+    auto back3 = [&]() {
+        tiles(v3, kTileBwdL3 + 4 * w);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (!kPair) {
+        hidden(w2, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        back3();
+    }
     layer_out(1, kActH2);
     hidden(w3, 2);
     __builtin_amdgcn_sched_barrier(0);
-    tiles(v2, kTileBwdL2 + 4 * w);
-    __builtin_amdgcn_sched_barrier(0);
+    auto back2 = [&]() {
+        tiles(v2, kTileBwdL2 + 4 * w);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (kPair) back3();
+    else back2();
     layer_out(2, kActH3);
     // gradients of outputs 16 ot + 4g + j of sample s of block ob, the choice of
     // formula by selects: a branch per lane group would run them one after the other
@@ -693,6 +718,7 @@ __global__ void __launch_bounds__(512) mlp_fwdbwd_kernel(const unsigned char *bl
     auto grad_ops = [&](int l, int buf) { swap_ops(buf, slope(acc[0], pos[l]), slope(acc[1], pos[l] >> 4)); };
     acc[0] = acc[1] = at[0] = at[1] = zero;
     product(v4, 0);
+    if constexpr (kPair) back2();
     grad_ops(2, 1);
     grad_store(2, kActZ3);
     // layer 3 -> dZ2, layer 2 -> dZ1
@@ -1104,7 +1130,10 @@ hipError_t launch_mlp_draw(const RowDraw &D, hipStream_t s) {
 hipError_t launch_mlp_grad(const unsigned char *blob, const uint32_t *rows, int batch, unsigned char *act, float *part,
                            float *loss, const RowDraw *next, hipStream_t s) {
     const int nchunk = (batch + 31) / 32;
-    hipLaunchKernelGGL(mlp_fwdbwd_kernel, dim3(nchunk), dim3(512), 0, s, blob, rows, batch, act, loss);
+    if (nchunk > kChipCUs)
+        hipLaunchKernelGGL(mlp_fwdbwd_kernel<true>, dim3(nchunk), dim3(512), 0, s, blob, rows, batch, act, loss);
+    else
+        hipLaunchKernelGGL(mlp_fwdbwd_kernel<false>, dim3(nchunk), dim3(512), 0, s, blob, rows, batch, act, loss);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(mlp_wgrad_kernel, dim3(kGradJobs * kGradSplits + (next ? (next->batch + 63) / 64 : 0)), dim3(64), 0,
