@@ -75,7 +75,9 @@ LEDGER_CALL = {
     "deposit": 6 * (2 * 4 + 10 + 12 + 4) + 2 * 4 + 2 * 26,   # ~6 channels within 3 sd: erf (rcp, exp, poly), int64,
                                                              # atomic; two more erf for the coverage
 }
-PEAK_VALU_TOPS = 256 * 64 * 2.4e9 / 1e12  # 39.32 T lane-slots/s (non-packed 32-bit VALU)
+# 78.64 T lane-slots/s: 128 lanes per CU and clock, a plain 32-bit instruction of a wave every two
+# cycles on each of the four SIMDs (256 CUs x 256 FLOP per clock as fused multiply-adds)
+PEAK_VALU_TOPS = 256 * 128 * 2.4e9 / 1e12
 PEAK_MFMA_BF16_TFLOPS = 2500.0            # dense BF16 matrix cores
 
 
