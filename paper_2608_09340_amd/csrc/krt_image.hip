@@ -137,7 +137,7 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
     // divide nch it repeats some of its neighbour's, to the same bits
     const int c = min((int)(tid - pix * per) * V, Q.nch - V);
     const bool live = pix < Q.npix;
-    float *out = Q.out + pix * Q.nch + c;
+    const int64_t at = V == 1 ? tid : pix * Q.nch + c;  // an index: the address costs a spill at 64 registers
     float A[V], B[V];
 #pragma unroll
     for (int k = 0; k < V; ++k) { A[k] = 1.0f; B[k] = 0.0f; }
@@ -179,7 +179,7 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
     if (nseg == 1) {
         if (live) {
 #pragma unroll
-            for (int k = 0; k < V; ++k) out[k] = B[k];
+            for (int k = 0; k < V; ++k) Q.out[at + k] = B[k];
         }
         return;
     }
@@ -194,7 +194,7 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
                 const float2 p = part[wave + s][k][lane];
                 I = fmaf(p.x, I, p.y);
             }
-            out[k] = I;
+            Q.out[at + k] = I;
         }
     }
 }
