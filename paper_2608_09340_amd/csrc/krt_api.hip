@@ -880,6 +880,7 @@ extern "C" int krt_image(krt_ctx *c, const krt_image_desc *d) {
     Q.srcf = d->src_dev;
     Q.kabs = d->kabs_dev;
     Q.out = d->image_dev;
+    Q.cus = c->cus;
     HIPCHK(c, hipSetDevice(c->device));
     HIPCHK(c, launch_image_timed(Q, c->stream, c->ev0, c->ev1));
     HIPCHK(c, hipStreamSynchronize(c->stream));

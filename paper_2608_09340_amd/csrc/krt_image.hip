@@ -9,8 +9,8 @@
 //   an optional grey absorption, zero when absent),
 // with x_k the lab-frame centre of channel k.
 //
-// Layout.  One lane per pixel and four consecutive channels (one channel in
-// small images), so the lanes of a wave read the emissivity of consecutive
+// Layout.  One lane per pixel and channel, or per pixel and four consecutive
+// channels (image_plan says where), so the lanes of a wave read the emissivity of consecutive
 // channels from consecutive addresses and a cell's fields at one address per
 // pixel of the wave: the pass streams the emissivity array once.  The
 // Voigt table sits in LDS.  The recurrence is affine in I, so a ray can be
@@ -23,13 +23,16 @@
 //
 // Memory bounds it: along z and y the cells of a ray are megabytes apart, and
 // what counts is how much a wave takes from each place.  128^3 x 64 channels,
-// velocity, source function and absorption, toward -z (1.1 GB): 258 us with
-// one channel a lane (256 bytes a cell and wave), 212 us with four (1 KB;
-// 5.2 TB/s, the rate of a copy).  More waves with shorter chunks (eight per
+// velocity, source function and absorption, toward -z (1.1 GB): 247 us with
+// one channel a lane (256 bytes a cell and wave), 205 us with four (1 KB;
+// 5.3 TB/s, the rate of a copy).  More waves with shorter chunks (eight per
 // SIMD) only spread the same reads over more places: 400 us.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
+#include <atomic>
 
 #include "krt_internal.h"
 #include "krt_kernels.h"
@@ -46,7 +49,7 @@ constexpr int kImgWaves = 8;            // waves per block
 constexpr int kImgMaxSeg = kImgWaves;   // segments of one ray (waves of one block)
 constexpr int kImgMinSegCells = 4;      // shortest segment worth a wave
 constexpr int64_t kImgTargetWaves = 16384;  // twice the chip's resident waves at 8 per SIMD, at one channel a lane
-constexpr int64_t kImgQuadWaves = 2048;     // two per SIMD
+constexpr int64_t kImgQuadWaves = 2048;     // two per SIMD of 256 compute units
 
 // fields of a chunk of cells along the ray (the arrays a kernel instance does
 // not read are never written and cost nothing)
@@ -55,10 +58,10 @@ struct ImgChunk {
     float k0[kImgChunk<V>], v[kImgChunk<V>], ab[kImgChunk<V>], j[kImgChunk<V>][V], s[kImgChunk<V>][V];
 };
 
-// V consecutive channels.  Four a lane are read as a stream (128^3 x 64: 143 us,
-// plain 151); one a lane is the path of small images and few channels, where
-// other waves read the rest of a line (100^3 x 9 channels: 33 us plain, 37 us
-// as a stream).
+// V consecutive channels.  Four a lane are whole lines and are read as a stream
+// (128^3 x 64 with source toward +y: 168 us, plain 181); with one a lane other
+// waves read the rest of a line (100^3 x 9 channels: 33 us plain, 37 us as a
+// stream).
 template <int V>
 __device__ __forceinline__ void img_stream(const float *p, float (&o)[V]) {
     typedef float vec __attribute__((ext_vector_type(V), aligned(4)));
@@ -131,13 +134,10 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
     const int seg = wave % nseg;                // segment of the ray, far side = 0
     const int grp = wave / nseg;                // group of 64 lanes' (pixel, V channels)
     const int64_t tid = ((int64_t)blockIdx.x * (kImgWaves / nseg) + grp) * 64 + lane;
-    const int per = (Q.nch + V - 1) / V;        // lanes of a pixel
+    const int per = Q.nch / V;                  // lanes of a pixel (V divides nch)
     const int64_t pix = tid / per;
-    // the last lane of a pixel takes its last V channels: where V does not
-    // divide nch it repeats some of its neighbour's, to the same bits
-    const int c = min((int)(tid - pix * per) * V, Q.nch - V);
+    const int c = (int)(tid - pix * per) * V;
     const bool live = pix < Q.npix;
-    const int64_t at = V == 1 ? tid : pix * Q.nch + c;  // an index: the address costs a spill at 64 registers
     float A[V], B[V];
 #pragma unroll
     for (int k = 0; k < V; ++k) { A[k] = 1.0f; B[k] = 0.0f; }
@@ -179,7 +179,7 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
     if (nseg == 1) {
         if (live) {
 #pragma unroll
-            for (int k = 0; k < V; ++k) Q.out[at + k] = B[k];
+            for (int k = 0; k < V; ++k) Q.out[tid * V + k] = B[k];
         }
         return;
     }
@@ -194,7 +194,7 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
                 const float2 p = part[wave + s][k][lane];
                 I = fmaf(p.x, I, p.y);
             }
-            Q.out[at + k] = I;
+            Q.out[tid * V + k] = I;
         }
     }
 }
@@ -213,9 +213,17 @@ __global__ void __launch_bounds__(64 * kImgWaves) image_src_kernel(ImageParams Q
     image_body<1, kVel, kAbs, true>(Q, nseg, seglen);
 }
 
-template <bool kVel, bool kAbs, bool kSrc>
+template <bool kVel, bool kAbs>
 __global__ void __launch_bounds__(64 * kImgWaves) image_quad_kernel(ImageParams Q, int nseg, int seglen) {
-    image_body<4, kVel, kAbs, kSrc>(Q, nseg, seglen);
+    image_body<4, kVel, kAbs, false>(Q, nseg, seglen);
+}
+
+// Three waves per SIMD (one workgroup per compute unit), although 127 registers
+// would allow four: 128^3 x 64 toward -z 202 us with three, 220 with four.
+template <bool kVel, bool kAbs>
+__global__ void __launch_bounds__(64 * kImgWaves) __attribute__((amdgpu_waves_per_eu(3, 3)))
+image_quad_src_kernel(ImageParams Q, int nseg, int seglen) {
+    image_body<4, kVel, kAbs, true>(Q, nseg, seglen);
 }
 
 struct ImgPlan {
@@ -223,24 +231,11 @@ struct ImgPlan {
     int64_t groups;  // waves per segment
 };
 
-template <bool kVel, bool kAbs, bool kSrc>
-static void launch_image_t(const ImageParams &Q, const ImgPlan &p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
-    const int nl = Q.n[Q.d], seglen = (nl + p.nseg - 1) / p.nseg;
-    const int64_t per_block = kImgWaves / p.nseg;
-    const dim3 grid((unsigned)((p.groups + per_block - 1) / per_block)), block(64 * kImgWaves);
-    if (p.v == 4)
-        hipExtLaunchKernelGGL((image_quad_kernel<kVel, kAbs, kSrc>), grid, block, 0, s, start, stop, 0, Q, p.nseg, seglen);
-    else if constexpr (kSrc)
-        hipExtLaunchKernelGGL((image_src_kernel<kVel, kAbs>), grid, block, 0, s, start, stop, 0, Q, p.nseg, seglen);
-    else
-        hipExtLaunchKernelGGL((image_kernel<kVel, kAbs>), grid, block, 0, s, start, stop, 0, Q, p.nseg, seglen);
-}
-
-// Channels a lane and segments of a ray: segments are doubled while the launch
-// has fewer waves than keep the chip busy and they stay at least
-// kImgMinSegCells cells long.
+// Channels a lane (a divisor of nch) and segments of a ray: segments are
+// doubled while the launch has fewer waves than keep the chip busy and they
+// stay at least kImgMinSegCells cells long.
 static ImgPlan image_plan(int64_t npix, int nch, int nl, int v) {
-    ImgPlan p{v, 1, (npix * ((nch + v - 1) / v) + 63) / 64};
+    ImgPlan p{v, 1, (npix * (nch / v) + 63) / 64};
     while (p.nseg < kImgMaxSeg && p.groups * p.nseg < kImgTargetWaves / v &&
            (nl + 2 * p.nseg - 1) / (2 * p.nseg) >= kImgMinSegCells)
         p.nseg *= 2;
@@ -248,16 +243,56 @@ static ImgPlan image_plan(int64_t npix, int nch, int nl, int v) {
 }
 
 // Four channels a lane (16-byte loads, 1 KB of a cell's channels a wave) where
-// that leaves kImgQuadWaves waves of full lanes; below, the march's latency
-// bounds the launch and one channel a lane has four times the waves.
-// Kernel times, one channel a lane / four, above the line: 32^3 x 64 with
-// source 8.6 / 6.8 us, 64^3 x 32 15.3 / 10.8, 100^3 x 9 32.7 / 28.8, 90^3 x 63
-// with source 132 / 94; below: 32^3 x 32 4.4 / 5.6, 40^3 x 32 6.3 / 7.2,
-// 64^3 x 5 7.8 / 9.3 (its second lane repeats three channels), 100^3 x 5 with
-// source 22.2 / 26.9.
-static ImgPlan image_plan(int64_t npix, int nch, int nl) {
-    const ImgPlan quad = image_plan(npix, nch, nl, 4);
-    return nch >= 4 && npix * nch / 256 * quad.nseg >= kImgQuadWaves ? quad : image_plan(npix, nch, nl, 1);
+//  - a cell's channels are 32, 48 or 64: two lines, three or four.  With fewer,
+//    or with part of a line left over, neighbouring cells share lines that the
+//    stream does not keep (200^3 x 4 toward +x, one channel a lane / four:
+//    43 / 167 us; 120^3 x 33 53 / 65); with more, 256 bytes a wave already
+//    stream (120^3 x 128 169 / 214);
+//  - without a source function or across x: along it, reads of two arrays from
+//    one place lose (64^3 x 64 28 / 32);
+//  - the launch has kImgQuadWaves waves and its last round of workgroups
+//    (`round` of them are resident, one or two a compute unit) is nine tenths
+//    full: a few workgroups past a full round take as long as a whole one
+//    (200^3 x 32 with source, 1.2 rounds: 354 / 397 us);
+//  - 64 channels of emissivity alone, which 256 bytes a wave stream as well,
+//    take one round (180^3: 288 / 308 us).
+// Inside the line, one channel a lane / four: 64^3 x 32 15.5 / 10.8 us,
+// 128^3 x 32 88 / 55, 144^3 x 48 with velocity and absorption 206 / 160,
+// 128^3 x 64 with velocity, source and absorption toward -z 247 / 205.
+static ImgPlan image_plan(const ImageParams &Q, int64_t round) {
+    const int nl = Q.n[Q.d];
+    if (Q.nch % 16 == 0 && Q.nch >= 32 && Q.nch <= 64 && !(Q.srcf && Q.d == 0)) {
+        const ImgPlan quad = image_plan(Q.npix, Q.nch, nl, 4);
+        const int64_t per_block = kImgWaves / quad.nseg, blocks = (quad.groups + per_block - 1) / per_block;
+        const bool full = 10 * blocks >= 9 * round * ((blocks + round - 1) / round);
+        if (full && quad.groups * quad.nseg >= kImgQuadWaves &&
+            (Q.nch < 64 || Q.vel_axis || Q.srcf || blocks <= round))
+            return quad;
+    }
+    return image_plan(Q.npix, Q.nch, nl, 1);
+}
+
+template <bool kVel, bool kAbs, bool kSrc>
+static hipError_t launch_image_t(const ImageParams &Q, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+    auto quad = image_quad_kernel<kVel, kAbs>;
+    auto single = image_kernel<kVel, kAbs>;
+    if constexpr (kSrc) {
+        quad = image_quad_src_kernel<kVel, kAbs>;
+        single = image_src_kernel<kVel, kAbs>;
+    }
+    static std::atomic<int> resident{0};  // workgroups of the quad kernel a compute unit holds
+    int per_cu = resident.load();
+    if (per_cu == 0) {
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, quad, 64 * kImgWaves, 0);
+        if (e != hipSuccess) return e;
+        resident.store(per_cu = std::max(per_cu, 1));
+    }
+    const ImgPlan p = image_plan(Q, (int64_t)Q.cus * per_cu);
+    const int nl = Q.n[Q.d], seglen = (nl + p.nseg - 1) / p.nseg;
+    const int64_t per_block = kImgWaves / p.nseg;
+    const dim3 grid((unsigned)((p.groups + per_block - 1) / per_block)), block(64 * kImgWaves);
+    hipExtLaunchKernelGGL(p.v == 4 ? quad : single, grid, block, 0, s, start, stop, 0, Q, p.nseg, seglen);
+    return hipGetLastError();
 }
 
 hipError_t launch_image_timed(const ImageParams &Q, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
@@ -267,19 +302,17 @@ hipError_t launch_image_timed(const ImageParams &Q, hipStream_t s, hipEvent_t st
         if (stop) { hipError_t e = hipEventRecord(stop, s); if (e != hipSuccess) return e; }
         return hipSuccess;
     }
-    const ImgPlan p = image_plan(Q.npix, Q.nch, Q.n[Q.d]);
     const int key = (Q.vel_axis ? 4 : 0) | (Q.kabs ? 2 : 0) | (Q.srcf ? 1 : 0);
     switch (key) {
-        case 0: launch_image_t<false, false, false>(Q, p, s, start, stop); break;
-        case 1: launch_image_t<false, false, true>(Q, p, s, start, stop); break;
-        case 2: launch_image_t<false, true, false>(Q, p, s, start, stop); break;
-        case 3: launch_image_t<false, true, true>(Q, p, s, start, stop); break;
-        case 4: launch_image_t<true, false, false>(Q, p, s, start, stop); break;
-        case 5: launch_image_t<true, false, true>(Q, p, s, start, stop); break;
-        case 6: launch_image_t<true, true, false>(Q, p, s, start, stop); break;
-        default: launch_image_t<true, true, true>(Q, p, s, start, stop); break;
+        case 0: return launch_image_t<false, false, false>(Q, s, start, stop);
+        case 1: return launch_image_t<false, false, true>(Q, s, start, stop);
+        case 2: return launch_image_t<false, true, false>(Q, s, start, stop);
+        case 3: return launch_image_t<false, true, true>(Q, s, start, stop);
+        case 4: return launch_image_t<true, false, false>(Q, s, start, stop);
+        case 5: return launch_image_t<true, false, true>(Q, s, start, stop);
+        case 6: return launch_image_t<true, true, false>(Q, s, start, stop);
+        default: return launch_image_t<true, true, true>(Q, s, start, stop);
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_image(const ImageParams &Q, hipStream_t s) { return launch_image_timed(Q, s, nullptr, nullptr); }

@@ -45,6 +45,7 @@ struct ImageParams {
     int64_t npix, stride;
     int n[3];
     int d, sgn, n0, nch;
+    int cus;                // compute units of the device (the launch's plan)
     float sgnf, dl, ch_lo, ch_w;
 };
 hipError_t launch_image(const ImageParams &Q, hipStream_t s);
