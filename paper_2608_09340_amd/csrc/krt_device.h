@@ -236,7 +236,8 @@ __device__ __forceinline__ float upar_from(const float *T, const UparMass &q, fl
     const float s = (float)kDelta * f_exp(v);
     const float uw = xa + sel(l1, -s, s);
     const float u = sel(spike, us, sel(l2 & !l1, v, uw));
-    // p(u | -x) = p(-u | x): u takes the sign of x
+    // p(u | -x) = p(-u | x): u takes the sign of x.  A zero is +0 here: the
+    // sources give no -0, and a difference or sum of a walk makes none.
     return __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(u), __float_as_uint(x), 0x80000000u, 0x78));
 }
 

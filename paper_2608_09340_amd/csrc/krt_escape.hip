@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(kRecThreads) cell_record_kernel(RecordParams R
                     }
                     px = q0; py = q1; pz = q2;
                     nx = m0; ny = m1; nz = m2;
-                    x = xin;
+                    x = xin + 0.0f;  // -0 as 0: the sampler takes the sign of the frequency
                     sx2 = 0.0f;
                     ns = 0;
                     state = kLive;

@@ -398,6 +398,7 @@ __device__ __forceinline__ float cont_voigt(const RunParams &P, int voff, float 
 // position in the cell, dx its width.  A zero component gives +inf, or NaN (0
 // times inf) for a packet exactly on the face; the minimum over the axes
 // ignores a NaN as it ignores +inf, and the direction has another component.
+// A subnormal component counts as zero (its reciprocal is +inf).
 __device__ __forceinline__ float face_dist(float n, float f, float dx) {
     const float up = fminf(fmaxf(n * 0x1p126f, 0.0f), 1.0f);  // 1 toward the upper face, 0 toward the lower
     return fabsf(f - up) * dx * f_rcp(fabsf(n));
@@ -1247,7 +1248,7 @@ __global__ void debug_upar_kernel(const float *tab, float a, float thd, float x,
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     uint4 A = philox(make_uint4(ev0 + (uint32_t)i, (uint32_t)packet, (uint32_t)(packet >> 32), 0u), k0, k1);
-    out[i] = upar_lds(T, x, a, thd, u01(A.z), u01(A.w));
+    out[i] = upar_lds(T, x + 0.0f, a, thd, u01(A.z), u01(A.w));  // -0 as 0, as a walk's sources give it
 }
 
 // ---------------------------------------------------------------- launch ---
