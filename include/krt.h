@@ -83,7 +83,13 @@ int64_t krt_last_rounds(const krt_ctx *ctx);
  * emissivity is recorded per cell of a mesh; eq. sigma0: k0 = n_l sigma_0).
  * All field pointers are DEVICE pointers borrowed until the next upload or
  * krt_destroy; the library copies nothing except the volume-emission weights,
- * from which it builds an alias table (Walker/Vose) on the device.
+ * from which it builds an alias table (Walker/Vose) on the device, and, at each
+ * krt_mc_run that profits, the fields into one record per cell: 32 bytes a cell
+ * of device memory on grids with eps_dev or kabs_dev, 16 for the learned escape
+ * on moving ones, up to 2^27 cells, and only where that is at most 1/16 of the
+ * device's free memory (else the fields are read where they are; same tallies).
+ * The memory is kept for the next run and given back by the upload of a grid
+ * that takes another amount and by krt_destroy; krt_mc_run_noalloc has none.
  * Errors: KRT_EINVAL for n <= 0, hi <= lo, bad bc, n_lines outside 1..8,
  * k0 == NULL, ncell >= 2^31, or (with tclass_dev) n_tclass outside 1..8, a
  * ratio outside [0.05, 20] or a class index >= n_tclass (the indices are

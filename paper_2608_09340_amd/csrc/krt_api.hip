@@ -111,6 +111,12 @@ void free_grid(krt_ctx *c) {
     c->have_grid = false;
 }
 
+void free_records(krt_ctx *c) {
+    if (c->rec) (void)hipFree(c->rec);
+    c->rec = nullptr;
+    c->rec_cap = 0;
+}
+
 void free_tables(krt_ctx *c) {
     for (auto p : c->tab) if (p) (void)hipFree(p);
     c->tab.clear();
@@ -318,7 +324,7 @@ extern "C" void krt_destroy(krt_ctx *c) {
     if (c->cv_tab) (void)hipFree(c->cv_tab);
     if (c->cs_tab) (void)hipFree(c->cs_tab);
     if (c->cs_par) (void)hipFree(c->cs_par);
-    if (c->rec) (void)hipFree(c->rec);
+    free_records(c);
     if (c->work_counter) (void)hipFree(c->work_counter);
     if (c->level_power) (void)hipFree(c->level_power);
     if (c->host_pinned) (void)hipHostFree(c->host_pinned);
@@ -391,6 +397,8 @@ extern "C" int krt_grid_upload(krt_ctx *c, const krt_grid_desc *d) {
         if (mx >= d->n_tclass) return fail(c, KRT_EINVAL, "class index %d >= n_tclass %d", (int)mx, d->n_tclass);
     }
     free_grid(c);
+    // records of the grid before, unless this one's runs take as many
+    if (c->rec_cap != ncell * ((d->eps_dev || d->kabs_dev) ? 2 : d->vel_dev ? 1 : 0)) free_records(c);
     c->grid = *d;
     c->cls_line = -1;
     c->br_lo = br_lo;
@@ -563,14 +571,16 @@ static int cell_record_quads(const RunParams &P, bool fused, bool other, uint64_
     if (other || P.profile_mode != 0 || P.tclass || P.bratio) return 0;
     return (P.eps || P.kabs) ? 2 : 0;
 }
-// room for n float4 of records, kept by the context; false (and none) if the
-// device has no memory for them
+// Room for n float4 of records; false (and none) if that is more than
+// kRecordShare of the device's free memory.  The context keeps it for the next
+// run until a grid that takes another amount is uploaded (free_records), so a
+// run never frees.
+constexpr double kRecordShare = 1.0 / 16.0;
 static bool reserve_records(krt_ctx *c, int64_t n) {
     if (c->rec_cap >= n) return true;
-    if (c->rec) (void)hipFree(c->rec);
-    c->rec = nullptr;
-    c->rec_cap = 0;
-    if (hipMalloc(&c->rec, sizeof(float4) * (size_t)n) != hipSuccess) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || (double)n * sizeof(float4) > kRecordShare * (double)free_b ||
+        hipMalloc(&c->rec, sizeof(float4) * (size_t)n) != hipSuccess) {
         (void)hipGetLastError();
         c->rec = nullptr;
         return false;

@@ -139,3 +139,30 @@ def test_finalised_emissivity_on_both_sides_of_the_cache(gpu_ctx, nch):
     want = T.emis_raw.double() * f
     assert int(torch.count_nonzero(T.emis_raw)) > 1000
     assert bool(((T.emis.double() - want).abs() <= want.abs() * 2.0 ** -23).all())
+
+
+def test_cell_records_are_given_back(gpu_ctx):
+    """The memory of the cell records (32 bytes a cell here) goes back to the
+    device when a smaller grid is uploaded; a grid of the same kind and size
+    keeps it."""
+    import torch
+    from paper_2608_09340_amd import krt
+    n = 128
+    p = W.sphere(n, 5.0, 1e-2, phase=0, emis=None)
+    p["grid"]["eps"] = np.full(n ** 3, 0.5, dtype=np.float32)
+    T = krt.Transport(p, ctx=gpu_ctx)
+    S = W.sphere(5, 5.0, 1e-2, phase=0, emis=None)
+    small = torch.from_numpy(S["grid"]["k0"]).cuda()
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    T.run(n ** 3 // 8, seed=1)
+    held = free()
+    T._bind()
+    assert abs(free() - held) < 1 << 20
+    T.run(n ** 3 // 8, seed=1)
+    assert abs(free() - held) < 1 << 20
+    gpu_ctx.krt_grid_upload([5] * 3, [-1.0] * 3, [1.0] * 3, [0] * 3, small)
+    assert free() - held >= 32 * n ** 3 - (2 << 20)
