@@ -41,7 +41,8 @@ __device__ __forceinline__ void tally_add_i64(int64_t *p, int64_t v) {
 // scatterings, eight 8-bit counts in one register pair.  The wave writes all
 // its windows back every kEmisTicks iterations, before a count can pass 255.
 // Dipole phase: the contributions differ, so the window holds int64 sums, in
-// LDS ([slot][thread], each thread its own).
+// LDS ([slot][thread], each thread its own), which stay until the packet leaves
+// the window or the cell.
 // Against four direct-mapped (channel, int64 sum) register slots with a
 // four-way branch per scattering this takes 3 VGPRs instead of 12.
 constexpr int kEmisSlots = 8;
@@ -924,10 +925,12 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 break;
             }
         }
-        if (--ticks == 0) {
-            asm volatile("");
-            ticks = kEmisTicks;
-            if (emis_on) flush_emis();
+        if constexpr (!kDip) {
+            if (--ticks == 0) {
+                asm volatile("");
+                ticks = kEmisTicks;
+                if (emis_on) flush_emis();
+            }
         }
 
         // ---- one flight segment (divergent) --------------------------------
@@ -1062,9 +1065,11 @@ __global__ void __launch_bounds__(kMaxThreads) mc_transport_kernel(RunParams P) 
                 settle();
                 const uint64_t live = __ballot(state == kLive);
                 if (live == 0ull) break;
-                if (ticks <= 64) {
-                    ticks = kEmisTicks;
-                    if (emis_on) flush_emis();
+                if constexpr (!kDip) {
+                    if (ticks <= 64) {
+                        ticks = kEmisTicks;
+                        if (emis_on) flush_emis();
+                    }
                 }
                 k = __popcll(live);
                 left = 64 / k;  // each lane's share of the bank
