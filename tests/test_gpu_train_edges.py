@@ -76,3 +76,57 @@ def test_normalisation_of_ragged_sets(gpu_ctx, n):
     assert norm[o] == R[:, 1].min() and norm[o + 1] == R[:, 1].max()
     assert norm[o + 2] == R[:, 0].min() and norm[o + 3] == R[:, 0].max()
     assert norm[o + 4] == R[:, 6].min()
+
+
+@pytest.mark.parametrize("batch", [33, 257, 8192, 8225, 9001])
+@pytest.mark.parametrize("where", ["last", "first chunk", "last chunk", "split end", "split start", "late split"])
+def test_gradient_of_one_chunk_alone(gpu_ctx, batch, where):
+    """Every row invalid but those of one place (the last sample, the first or
+    last chunk of 32, the chunks on both sides of a boundary between the eight
+    sample splits): the gradient is theirs alone, so a sample lost or doubled
+    there is all of it.  Batches above 8192 take the kernel that shares a
+    compute unit.  Bounds of the full-size check, the loss's relative to the
+    size of its terms (about one each)."""
+    import torch
+    p = _rand_params(31)
+    _put(gpu_ctx, p, NORM)
+    rng = np.random.default_rng(32)
+    rec = _records(rng, 1000)
+    rec[500:, mlp.R_VALID] = 0.0
+    nchunk = (batch + 31) // 32
+    chunk = {"last": nchunk - 1, "first chunk": 0, "last chunk": nchunk - 1, "split end": max(nchunk * 3 // 8 - 1, 0),
+             "split start": nchunk * 3 // 8, "late split": nchunk * 7 // 8}[where]
+    rows = np.arange(32 * chunk, min(batch, 32 * chunk + 32)) if where != "last" else np.array([batch - 1])
+    idx = rng.integers(500, 1000, batch).astype(np.int32)
+    idx[rows] = rng.integers(0, 500, len(rows))
+    u = rng.uniform(0, 1, (batch, 4))
+    cond = rng.uniform(0, 1, batch) < 0.4
+    uq = np.concatenate([u, cond[:, None].astype(np.float64)], axis=1)
+    grad = torch.zeros(NP, dtype=torch.float32, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    gpu_ctx.krt_escape_grad(torch.from_numpy(rec.astype(np.float32)).cuda(), torch.from_numpy(idx).cuda(),
+                            torch.from_numpy(uq.astype(np.float32)).cuda(), grad, loss)
+    g = grad.cpu().numpy().astype(np.float64)
+    R = rec[idx[rows]].astype(np.float32).astype(np.float64)
+    uf = u[rows].astype(np.float32).astype(np.float64)
+    l_ref, g_ref = mlp.loss_and_grad(p, mlp.inputs(R, uf, cond[rows]), mlp.targets_normalised(R, NORM, cond[rows]),
+                                     mlp.levels(uf, cond[rows]), bf=True, s9=NORM[NO + mlp.O_LOGN])
+    share = len(rows) / batch
+    assert np.linalg.norm(g_ref) > 0
+    assert np.linalg.norm(g - share * g_ref) <= 2e-2 * share * np.linalg.norm(g_ref)
+    assert abs(loss.item() - share * l_ref) < 1e-2 * share * (abs(l_ref) + 1.0)
+
+
+def test_gradient_of_large_batches_is_deterministic(gpu_ctx):
+    import torch
+    _put(gpu_ctx, _rand_params(41), NORM)
+    rng = np.random.default_rng(42)
+    rec = torch.from_numpy(_records(rng, 5000).astype(np.float32)).cuda()
+    batch = 9001
+    idx = torch.from_numpy(rng.integers(0, 5000, batch).astype(np.int32)).cuda()
+    u = torch.from_numpy(np.concatenate([rng.uniform(0, 1, (batch, 4)), rng.uniform(0, 1, (batch, 1)) < 0.3], axis=1)
+                         .astype(np.float32)).cuda()
+    g = [torch.zeros(NP, dtype=torch.float32, device="cuda") for _ in range(3)]
+    for out in g:
+        gpu_ctx.krt_escape_grad(rec, idx, u, out)
+    assert torch.equal(g[0], g[1]) and torch.equal(g[0], g[2])
