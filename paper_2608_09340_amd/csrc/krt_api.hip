@@ -1398,7 +1398,7 @@ extern "C" int krt_escape_grad(krt_ctx *c, const float *samples_dev, const int32
     HIPCHK(c, launch_zero_i64(reinterpret_cast<int64_t *>(c->mlp_loss), 1, c->stream));
     HIPCHK(c, launch_mlp_rows(samples_dev, idx_dev, u_dev, batch, c->mlp_norm, c->mlp_rows, c->stream));
     HIPCHK(c, launch_mlp_grad(c->mlp_blob, c->mlp_rows, batch, c->mlp_act, c->mlp_part, c->mlp_loss, nullptr,
-                              c->stream));
+                              c->cus, c->stream));
     HIPCHK(c, launch_mlp_gsum(c->mlp_part, grad_out_dev, c->stream));
     if (loss_out_dev) HIPCHK(c, hipMemcpyAsync(loss_out_dev, c->mlp_loss, sizeof(float), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1433,7 +1433,7 @@ extern "C" int krt_escape_train(krt_ctx *c, const float *samples_dev, uint64_t n
         D.step = (uint32_t)c->mlp_step + 1;
         const bool last = s == steps - 1;
         HIPCHK(c, launch_mlp_grad(c->mlp_blob, c->mlp_rows, batch, c->mlp_act, c->mlp_part,
-                                  loss_hist_dev ? loss_hist_dev + s : nullptr, last ? nullptr : &D, c->stream));
+                                  loss_hist_dev ? loss_hist_dev + s : nullptr, last ? nullptr : &D, c->cus, c->stream));
         HIPCHK(c, launch_mlp_adam(c->mlp_p, c->mlp_m, c->mlp_v, c->mlp_part, (float)lr, c->mlp_step, c->mlp_blob,
                                   last ? c->mlp_img : nullptr, c->stream));
     }

@@ -485,7 +485,6 @@ static_assert(kActZ4 + 2 == kActTiles, "activation store layout");
 // one's chain covers the other's waits.  A step of 8704 samples 25.7 us without
 // / 24.6 with, 16384: 36.3 / 31.4, 100000: 128 / 112; up to a workgroup per unit
 // there is nothing to cover (8192: 19.2 / 19.4).
-constexpr int kChipCUs = 256;
 template <bool kPair>
 __global__ void __launch_bounds__(512, kPair ? 4 : 2) mlp_fwdbwd_kernel(const unsigned char *blob, const uint32_t *rows, int batch,
                                                          unsigned char *act, float *loss) {
@@ -1128,9 +1127,9 @@ hipError_t launch_mlp_draw(const RowDraw &D, hipStream_t s) {
 // Gradient of the mean loss over a batch of rows into the split partials
 // `part`; `next` (if any) draws the rows of the step after it.
 hipError_t launch_mlp_grad(const unsigned char *blob, const uint32_t *rows, int batch, unsigned char *act, float *part,
-                           float *loss, const RowDraw *next, hipStream_t s) {
+                           float *loss, const RowDraw *next, int cus, hipStream_t s) {
     const int nchunk = (batch + 31) / 32;
-    if (nchunk > kChipCUs)
+    if (nchunk > cus)
         hipLaunchKernelGGL(mlp_fwdbwd_kernel<true>, dim3(nchunk), dim3(512), 0, s, blob, rows, batch, act, loss);
     else
         hipLaunchKernelGGL(mlp_fwdbwd_kernel<false>, dim3(nchunk), dim3(512), 0, s, blob, rows, batch, act, loss);

@@ -200,7 +200,7 @@ hipError_t launch_mlp_rows(const float *rec, const int32_t *idx, const float *uq
                            uint32_t *rows, hipStream_t s);
 hipError_t launch_mlp_draw(const RowDraw &D, hipStream_t s);
 hipError_t launch_mlp_grad(const unsigned char *blob, const uint32_t *rows, int batch, unsigned char *act, float *part,
-                           float *loss, const RowDraw *next, hipStream_t s);
+                           float *loss, const RowDraw *next, int cus, hipStream_t s);
 hipError_t launch_mlp_gsum(const float *part, float *grad, hipStream_t s);
 hipError_t launch_mlp_adam(float *p, float *m, float *v, const float *part, float lr, int step, unsigned char *blob,
                            unsigned char *img, hipStream_t s);
