@@ -72,7 +72,7 @@ struct krt_ctx {
     float esc_la_lo = 1.0f, esc_la_hi = -1.0f;  // log10 a range the network was fitted on (empty: none)
     float esc_lt_lo = 1.0f, esc_lt_hi = -1.0f;  // log10 tau_c range of its training records
     float esc_ld_min = 0.0f;                    // smallest log10 depth of its training records
-    float *mlp_p = nullptr, *mlp_m = nullptr, *mlp_v = nullptr, *mlp_g = nullptr, *mlp_norm = nullptr;
+    float *mlp_p = nullptr, *mlp_m = nullptr, *mlp_v = nullptr, *mlp_norm = nullptr;
     float *mlp_loss = nullptr;
     float *mlp_part = nullptr;                 // [kGradSplits][kNParams] split gradients
     unsigned char *mlp_act = nullptr;          // activation store of a batch, kActTiles operand tiles per 32 samples
@@ -329,7 +329,7 @@ extern "C" void krt_destroy(krt_ctx *c) {
     if (c->level_power) (void)hipFree(c->level_power);
     if (c->host_pinned) (void)hipHostFree(c->host_pinned);
     if (c->host_edges) (void)hipHostFree(c->host_edges);
-    for (void *p : {(void *)c->mlp_p, (void *)c->mlp_m, (void *)c->mlp_v, (void *)c->mlp_g, (void *)c->mlp_norm,
+    for (void *p : {(void *)c->mlp_p, (void *)c->mlp_m, (void *)c->mlp_v, (void *)c->mlp_norm,
                     (void *)c->mlp_loss, (void *)c->mlp_rows, (void *)c->mlp_blob,
                     (void *)c->mlp_img, (void *)c->mlp_calsum, (void *)c->mlp_part, (void *)c->mlp_act})
         if (p) (void)hipFree(p);
@@ -928,7 +928,9 @@ __host__ __device__ constexpr int level_pair(int u, int l) { return u * (u - 1) 
 // and the lines' powers are summed here instead of by a pass that read them
 // all again once per line.  128^3 cells of 5 levels: 100 us, 65 us now (252 MB,
 // 3.9 TB/s); with the copy of the constants, the power launches and their copy
-// back 130 us a call, 73 us now.
+// back 130 us a call, 73 us now.  Six to eight levels have more constants than
+// scalar registers all the same (106, 76 and 44 spilled): 182, 246 and 326 us a
+// call, 115, 149 and 198 now.
 constexpr int kLevelThreads = 256;
 constexpr int kLevelBlocks = 2048;   // at most; a workgroup takes every gridDim-th 256 cells
 constexpr int kMaxLevels = 8;
@@ -946,7 +948,7 @@ __global__ void __launch_bounds__(kLevelThreads) levels_kernel(const LevelConsts
         const bool in = c < ncell;
         const int64_t cl = in ? c : ncell - 1;
         // the constants are read again for every cell: kept across the loop
-        // they take more scalar registers than there are
+        // those of five levels take more scalar registers than there are
         typedef const __attribute__((address_space(4))) LevelConsts<NL> *Consts;
         Consts K = (Consts)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(K));
@@ -1242,7 +1244,6 @@ int mlp_alloc(krt_ctx *c) {
     HIPCHK(c, hipMalloc(&c->mlp_m, sizeof(float) * kNParams));
     HIPCHK(c, hipMalloc(&c->mlp_calsum, sizeof(double) * 3 * kNCal));
     HIPCHK(c, hipMalloc(&c->mlp_v, sizeof(float) * kNParams));
-    HIPCHK(c, hipMalloc(&c->mlp_g, sizeof(float) * kNParams));
     HIPCHK(c, hipMalloc(&c->mlp_part, sizeof(float) * kNParams * kGradSplits));
     HIPCHK(c, hipMalloc(&c->mlp_norm, sizeof(float) * kNNorm));
     HIPCHK(c, hipMalloc(&c->mlp_loss, sizeof(float) * 2));

@@ -360,9 +360,10 @@ inline int first_lanes(uint64_t n, uint64_t waves, uint64_t grid) {
 // 4.6 ns, so short items taken one refill at a time wait for it: in a Lambda
 // cycle's transport 4096 waves asked once per iteration, 19 us apart.  A wave
 // that comes back within kPoolSoon iterations therefore takes twice as many as
-// the last time (at most kPoolChunk, and at most half its even share of what is
-// left), and one that comes back later takes what it needs: long items are
-// never held in stock while another wave is idle.
+// the last time (at most kPoolChunk, and no more than its even share of what is
+// left: the cap is between half of it and the whole), and one that comes back
+// later takes what it needs: long items are never held in stock while another
+// wave is idle.
 constexpr uint32_t kPoolChunk = 256;
 constexpr int kPoolSoon = 32;
 // Idle lanes are refilled together: at kRefillLanes of them, or kRefillWait

@@ -272,7 +272,7 @@ __global__ void mlp_init_kernel(float *p, uint32_t k0, uint32_t k1) {
     p[i] = bias ? 0.0f : u * sqrtf(6.0f / fan_in);
 }
 
-// Slot (lane group g, entry j) of feature f of a 32-wide chunk: kperm's inverse.
+// Operand slot 8g + j (lane group g, entry j) of feature f of a 32-wide chunk.
 __device__ __forceinline__ int slot_of(int f) { return f < 16 ? 8 * (f >> 2) + (f & 3) : 8 * ((f - 16) >> 2) + 4 + (f & 3); }
 
 // Parameter i's value into every place the packed blob holds it: a weight's
@@ -354,9 +354,6 @@ __device__ __forceinline__ bool target_value(const float *r, int k, float &y) {
         default: return false;
     }
 }
-
-__device__ __forceinline__ bool conditional_output(int k) { return k >= kOutYS && k <= kOutAlpha; }
-__device__ __forceinline__ bool used_output(int k) { return k <= kOutAlpha || (k >= kOutXAbs && k < kOutXAbs + 6); }
 
 // ----------------------------------------------------------- batch rows ---
 // Training quantile levels are uniform, clamped to the encoded range [1e-4, 1 - 1e-4]

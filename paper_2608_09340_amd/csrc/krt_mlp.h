@@ -37,7 +37,7 @@
 // chunk c is therefore permuted: B slot 8g+j holds feature
 // 32c + 4g + j (j < 4) or 32c + 16 + 4g + (j - 4) (j >= 4), i.e. the
 // accumulators of tiles 2c and 2c+1 side by side, and the weight tiles are
-// packed with the same permutation (kperm), so activations never leave
+// packed with the same permutation, so activations never leave
 // registers.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -128,11 +128,6 @@ constexpr int kGradSplits = 8;
 // q2, log10 depth, m0, m1, m2, u_a, u_b, u_c, u_d, flag, x_out, face)
 constexpr int kFwdRaw = 17;
 static_assert(kMlpFwdBytes % 16 == 0, "the inference image is staged into LDS in 16-byte words");
-
-// Feature held by B-operand slot k' = 8g + j of 32-wide chunk c (see above).
-__host__ __device__ constexpr int kperm(int c, int kp) {
-    return 32 * c + ((kp & 7) < 4 ? 4 * (kp >> 3) + (kp & 7) : 16 + 4 * (kp >> 3) + (kp & 7) - 4);
-}
 
 // Network input of a quantile level u: logit(u) / 4 with u clamped to the
 // trained levels [1e-4, 1 - 1e-4]: beyond them the network would extrapolate
