@@ -24,9 +24,10 @@
 // Memory bounds it: along z and y the cells of a ray are megabytes apart, and
 // what counts is how much a wave takes from each place.  128^3 x 64 channels,
 // velocity, source function and absorption, toward -z (1.1 GB): 247 us with
-// one channel a lane (256 bytes a cell and wave), 205 us with four (1 KB;
-// 5.3 TB/s, the rate of a copy).  More waves with shorter chunks (eight per
-// SIMD) only spread the same reads over more places: 400 us.
+// one channel a lane (256 bytes a cell and wave), 205 us with four (1 KB; by
+// the kernel's own events, as all figures here; 222 us in a trace of first
+// passes, 5.0 TB/s, near the rate of a copy).  More waves with shorter chunks
+// (eight per SIMD) only spread the same reads over more places: 400 us.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
