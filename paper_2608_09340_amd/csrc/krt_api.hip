@@ -479,7 +479,7 @@ static double voigt_crossing(double a) {
 // one fused launch (network inside the transport kernel, a call whenever a
 // scattering qualifies, as here) finishes them, so the last rounds, each a
 // launch pair and a host round trip for few packets, are not run one by one.
-static int run_parked(krt_ctx *c, const RunParams &P0, uint64_t n_packets, uint64_t cap, uint64_t tail, int grid,
+static int run_parked(krt_ctx *c, const RunParams &P0, uint64_t n_packets, uint64_t cap, uint64_t tail, int per_cu,
                       int block_fused) {
     if (c->park_alloc < cap) {
         for (int k = 0; k < 2; ++k) {
@@ -510,14 +510,14 @@ static int run_parked(krt_ctx *c, const RunParams &P0, uint64_t n_packets, uint6
             Q.esc_min_lanes = 1;
             Q.esc_tail_lanes = 1;
             Q.esc_wait = 0;
-            HIPCHK(c, launch_transport(Q, kModeFused, grid, block_fused, c->stream));
+            HIPCHK(c, launch_transport(Q, kModeFused, WalkGrid{c->cus, per_cu, block_fused}, c->stream));
             break;
         }
         Q.park_out = c->park_buf[1 - cur];
         Q.park_count = c->park_counter;
         Q.park_cap = cap;
         HIPCHK(c, launch_zero_i64(reinterpret_cast<int64_t *>(c->park_counter), 1, c->stream));
-        HIPCHK(c, launch_transport(Q, kModePark, grid, 1024, c->stream));
+        HIPCHK(c, launch_transport(Q, kModePark, WalkGrid{c->cus, per_cu, 1024}, c->stream));
         new_done += admit;
         HIPCHK(c, hipMemcpyAsync(c->host_pinned, c->park_counter, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -805,15 +805,14 @@ static int mc_run_impl(krt_ctx *c, uint64_t n_packets, uint64_t seed, const krt_
         HIPCHK(c, launch_pack_fields(P, c->rec, quads, c->stream));
         P.rec = c->rec;
     }
-    int grid = c->cus * per_cu;
     c->last_net_ms = 0.0f;
     c->last_rounds = 1;
     if (!park) {
         HIPCHK(c, hipEventRecord(c->ev0, c->stream));
-        HIPCHK(c, launch_transport(P, esc ? kModeFused : kModePlain, grid, block, c->stream));
+        HIPCHK(c, launch_transport(P, esc ? kModeFused : kModePlain, WalkGrid{c->cus, per_cu, block}, c->stream));
         HIPCHK(c, hipEventRecord(c->ev1, c->stream));
     } else {
-        int rc = run_parked(c, P, n_packets, park_cap, park_tail, grid, block);
+        int rc = run_parked(c, P, n_packets, park_cap, park_tail, per_cu, block);
         if (rc) return rc;
     }
     // check for sums that left [0, 2^62] (the transport's atomics return nothing)

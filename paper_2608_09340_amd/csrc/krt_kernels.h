@@ -150,7 +150,11 @@ constexpr int kModePlain = 0, kModeFused = 1, kModePark = 2;
 // exit direction and the lab exit frequency; the transport resumes it with the
 // next event.
 constexpr int kParkQuads = 4;
-hipError_t launch_transport(const RunParams &P, int mode, int grid, int block, hipStream_t s);
+// workgroups of `block` lanes a walk may take: up to per_cu on each of cus units
+struct WalkGrid {
+    int cus, per_cu, block;
+};
+hipError_t launch_transport(const RunParams &P, int mode, const WalkGrid &g, hipStream_t s);
 // the network call of each of n parked records, in place (learned escape)
 hipError_t launch_escape_call(const RunParams &P, uint4 *rec, uint64_t n, int grid, hipStream_t s);
 // fills rec, `quads` float4 a cell, from P's fields

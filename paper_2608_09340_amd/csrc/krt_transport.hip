@@ -1267,8 +1267,13 @@ static_assert(kMaxTransportLds <= 160 * 1024, "a workgroup's LDS fits one CU (16
 static_assert((kTabFloats + kEdgeFloats) % 4 == 0 && (kTabFloats + kChanEdgeFloats + kMlpFwdBytes / 4) % 4 == 0,
               "the counters are aligned");
 
+// A persistent walk takes no more workgroups than are resident at once: packets
+// are first given out by place, and those of a workgroup that waits for another
+// to end would wait with it (64 workgroups of 1024 lanes asked for per compute
+// unit, one resident, 600,000 packets of a tau0 = 500 sphere: 306 ms, 30 with the
+// one).
 template <int kMode, int kMaxThreads, int kProf, bool kDip, int kRec = 0>
-static hipError_t launch_transport_t(const RunParams &P, int grid, int block, size_t lds, hipStream_t s) {
+static hipError_t launch_transport_t(RunParams P, WalkGrid g, size_t lds, hipStream_t s) {
     auto fn = mc_transport_kernel<kMode, kMaxThreads, kProf, kDip, kRec>;
     static std::atomic<bool> attr_set{false};  // the most any launch of this variant asks for
     if (!attr_set.load()) {
@@ -1277,39 +1282,44 @@ static hipError_t launch_transport_t(const RunParams &P, int grid, int block, si
         if (e != hipSuccess) return e;
         attr_set.store(true);
     }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, s, P);
+    if (g.per_cu > 1) {
+        int resident = 0;
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, fn, g.block, lds);
+        if (e != hipSuccess) return e;
+        g.per_cu = std::min(g.per_cu, std::max(resident, 1));
+    }
+    const int grid = g.cus * g.per_cu;
+    P.first_lanes = first_lanes(P.n_res + P.n_packets, (uint64_t)grid * (uint64_t)(g.block / 64), (uint64_t)grid);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(g.block), lds, s, P);
     return hipGetLastError();
 }
 
 template <int kProf, int kRec = 0>
-static hipError_t launch_plain(const RunParams &P, int grid, int block, hipStream_t s) {
+static hipError_t launch_plain(const RunParams &P, const WalkGrid &g, hipStream_t s) {
     // tables and both edge sets; with dipole phase the emissivity windows' sums
     if (P.phase == KRT_PHASE_DIPOLE_I)
         return launch_transport_t<kModePlain, 1024, kProf, true, kRec>(
-            P, grid, block, kPlainLds + (P.emis_raw ? sizeof(int64_t) * kEmisSlots * (size_t)block : 0), s);
-    return launch_transport_t<kModePlain, 1024, kProf, false, kRec>(P, grid, block, kPlainLds, s);
+            P, g, kPlainLds + (P.emis_raw ? sizeof(int64_t) * kEmisSlots * (size_t)g.block : 0), s);
+    return launch_transport_t<kModePlain, 1024, kProf, false, kRec>(P, g, kPlainLds, s);
 }
 
-hipError_t launch_transport(const RunParams &P0, int mode, int grid, int block, hipStream_t s) {
-    RunParams P = P0;
-    P.first_lanes = first_lanes(P.n_res + P.n_packets, (uint64_t)grid * (uint64_t)(block / 64), (uint64_t)grid);
+hipError_t launch_transport(const RunParams &P, int mode, const WalkGrid &g, hipStream_t s) {
     if (mode == kModeFused) {
         // compiled for the block size: up to 512 lanes 256 VGPRs (2 waves per SIMD;
         // the default), up to 768 lanes 168 VGPRs (spills, 3 waves), above that
         // 128 (4 waves, heavy spills)
-        if (block <= 512 && P.rec) return launch_transport_t<kModeFused, 512, 0, false, 1>(P, grid, block, kFusedLds, s);
-        if (block <= 512) return launch_transport_t<kModeFused, 512, 0, false>(P, grid, block, kFusedLds, s);
-        if (block <= 768) return launch_transport_t<kModeFused, 768, 0, false>(P, grid, block, kFusedLds, s);
-        return launch_transport_t<kModeFused, 1024, 0, false>(P, grid, block, kFusedLds, s);
+        if (g.block <= 512 && P.rec) return launch_transport_t<kModeFused, 512, 0, false, 1>(P, g, kFusedLds, s);
+        if (g.block <= 512) return launch_transport_t<kModeFused, 512, 0, false>(P, g, kFusedLds, s);
+        if (g.block <= 768) return launch_transport_t<kModeFused, 768, 0, false>(P, g, kFusedLds, s);
+        return launch_transport_t<kModeFused, 1024, 0, false>(P, g, kFusedLds, s);
     }
-    if (mode == kModePark)
-        return launch_transport_t<kModePark, 1024, 0, false>(P, grid, block, kPlainLds, s);
+    if (mode == kModePark) return launch_transport_t<kModePark, 1024, 0, false>(P, g, kPlainLds, s);
     // temperature and the profile modes exist for the plain walk only
-    if (P.bratio) return launch_plain<4>(P, grid, block, s);
-    if (P.tclass) return launch_plain<3>(P, grid, block, s);
-    if (P.profile_mode == 1) return launch_plain<1>(P, grid, block, s);
-    if (P.profile_mode == 2) return launch_plain<2>(P, grid, block, s);
-    return P.rec ? launch_plain<0, 2>(P, grid, block, s) : launch_plain<0>(P, grid, block, s);
+    if (P.bratio) return launch_plain<4>(P, g, s);
+    if (P.tclass) return launch_plain<3>(P, g, s);
+    if (P.profile_mode == 1) return launch_plain<1>(P, g, s);
+    if (P.profile_mode == 2) return launch_plain<2>(P, g, s);
+    return P.rec ? launch_plain<0, 2>(P, g, s) : launch_plain<0>(P, g, s);
 }
 
 // ------------------------------------------------------------ call kernel ---

@@ -185,3 +185,26 @@ def test_dipole_windows_hold_long_visits(gpu_ctx):
     one = [T.run(1, seed=1, packet_offset=k)["emis_raw"] for k in range(n)]
     assert np.array_equal(a["emis_raw"], b["emis_raw"]) and np.array_equal(a["emis_raw"], sum(one))
     assert abs(a["emis_raw"].sum() / (a["counters"]["scatterings"] << 20) - 1.0) < 0.05
+
+
+@pytest.mark.parametrize("phase", [0, 1])
+def test_more_workgroups_than_fit(gpu_ctx, phase):
+    """Workgroups asked for beyond those a compute unit holds change neither the
+    tallies nor, by more than the launch itself, the time: packets given to
+    workgroups that wait for others to end would make it a multiple (10 times
+    with 64 of 1024 lanes)."""
+    from paper_2608_09340_amd import krt
+    T = krt.Transport(W.sphere(16, 300.0, 1e-2, phase=phase, emis=(16, -12.0, 12.0)), ctx=gpu_ctx)
+    n, ms, ref = 60000, {}, None
+    for wg, per in ((0, 0), (1024, 4), (1024, 64), (256, 64)):
+        took = []
+        for _ in range(3):
+            r = T.run(n, seed=3, wg_size=wg, wg_per_cu=per)
+            took.append(gpu_ctx.krt_last_transport_ms())
+        ms[wg, per] = min(took)
+        ref = ref or r
+        assert np.array_equal(r["spec_raw"], ref["spec_raw"]) and np.array_equal(r["emis_raw"], ref["emis_raw"])
+        assert r["counters"] == ref["counters"]
+    print(ms)
+    assert ms[1024, 4] < 1.5 * ms[0, 0] and ms[1024, 64] < 1.5 * ms[0, 0], ms
+    assert ms[256, 64] < 4.0 * ms[0, 0], ms  # at most two workgroups of 256 lanes: a half or a quarter of the waves
