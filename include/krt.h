@@ -172,7 +172,7 @@ typedef struct {
     int32_t wg_size;           /* launch geometry: threads per workgroup (0 = 1024 plain, 512
                                   learned; the learned kernel is built for 256 VGPRs at <= 512
                                   lanes, 168 at <= 768, 128 above) */
-    int32_t wg_per_cu;         /* workgroups per CU (0 = 1) */
+    int32_t wg_per_cu;         /* workgroups per CU (0 = 1); no more are launched than a CU holds */
     int32_t emis_frac_bits;    /* fixed-point fraction bits F of the emissivity tally (0 = 20) */
     int32_t jbar_frac_bits;    /* fraction bits of the mean-intensity tally (0 = 36) */
     uint64_t norm_packets;     /* packets for the FP32 normalisation (0 = n_packets) */
