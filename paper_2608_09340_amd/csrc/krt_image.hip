@@ -59,10 +59,9 @@ struct ImgChunk {
     float k0[kImgChunk<V>], v[kImgChunk<V>], ab[kImgChunk<V>], j[kImgChunk<V>][V], s[kImgChunk<V>][V];
 };
 
-// V consecutive channels.  Four a lane are whole lines and are read as a stream
-// (128^3 x 64 with source toward +y: 168 us, plain 181); with one a lane other
-// waves read the rest of a line (100^3 x 9 channels: 33 us plain, 37 us as a
-// stream).
+// V consecutive channels.  Four a lane are read as a stream (128^3 x 64 with
+// source toward +y: 168 us, plain 181); with one a lane other waves read the
+// rest of a line (100^3 x 9 channels: 33 us plain, 37 us as a stream).
 template <int V>
 __device__ __forceinline__ void img_stream(const float *p, float (&o)[V]) {
     typedef float vec __attribute__((ext_vector_type(V), aligned(4)));
@@ -135,10 +134,14 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
     const int seg = wave % nseg;                // segment of the ray, far side = 0
     const int grp = wave / nseg;                // group of 64 lanes' (pixel, V channels)
     const int64_t tid = ((int64_t)blockIdx.x * (kImgWaves / nseg) + grp) * 64 + lane;
-    const int per = Q.nch / V;                  // lanes of a pixel (V divides nch)
+    const int per = (Q.nch + V - 1) / V;        // lanes of a pixel
     const int64_t pix = tid / per;
-    const int c = (int)(tid - pix * per) * V;
+    // the last lane of a pixel takes its last V channels: where V does not
+    // divide nch it repeats some of its neighbour's, to the same bits
+    const int c = min((int)(tid - pix * per) * V, Q.nch - V);
     const bool live = pix < Q.npix;
+    // an index, not an address: that costs a spill at 64 registers
+    const int64_t at = V == 1 ? tid : pix * Q.nch + c;
     float A[V], B[V];
 #pragma unroll
     for (int k = 0; k < V; ++k) { A[k] = 1.0f; B[k] = 0.0f; }
@@ -180,7 +183,7 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
     if (nseg == 1) {
         if (live) {
 #pragma unroll
-            for (int k = 0; k < V; ++k) Q.out[tid * V + k] = B[k];
+            for (int k = 0; k < V; ++k) Q.out[at + k] = B[k];
         }
         return;
     }
@@ -195,7 +198,7 @@ __device__ __forceinline__ void image_body(const ImageParams &Q, int nseg, int s
                 const float2 p = part[wave + s][k][lane];
                 I = fmaf(p.x, I, p.y);
             }
-            Q.out[tid * V + k] = I;
+            Q.out[at + k] = I;
         }
     }
 }
@@ -232,45 +235,64 @@ struct ImgPlan {
     int64_t groups;  // waves per segment
 };
 
-// Channels a lane (a divisor of nch) and segments of a ray: segments are
-// doubled while the launch has fewer waves than keep the chip busy and they
-// stay at least kImgMinSegCells cells long.
+// Channels a lane and segments of a ray: segments are doubled while the launch
+// has fewer waves than keep the chip busy and they stay at least
+// kImgMinSegCells cells long.
 static ImgPlan image_plan(int64_t npix, int nch, int nl, int v) {
-    ImgPlan p{v, 1, (npix * (nch / v) + 63) / 64};
+    ImgPlan p{v, 1, (npix * ((nch + v - 1) / v) + 63) / 64};
     while (p.nseg < kImgMaxSeg && p.groups * p.nseg < kImgTargetWaves / v &&
            (nl + 2 * p.nseg - 1) / (2 * p.nseg) >= kImgMinSegCells)
         p.nseg *= 2;
     return p;
 }
 
-// Four channels a lane (16-byte loads, 1 KB of a cell's channels a wave) where
-//  - a cell's channels are 32, 48 or 64: two lines, three or four.  With fewer,
-//    or with part of a line left over, neighbouring cells share lines that the
-//    stream does not keep (200^3 x 4 toward +x, one channel a lane / four:
-//    43 / 167 us; 120^3 x 33 53 / 65); with more, 256 bytes a wave already
-//    stream (120^3 x 128 169 / 214);
-//  - without a source function or across x: along it, reads of two arrays from
-//    one place lose (64^3 x 64 28 / 32);
-//  - the launch has kImgQuadWaves waves and its last round of workgroups
-//    (`round` of them are resident, one or two a compute unit) is nine tenths
-//    full: a few workgroups past a full round take as long as a whole one
-//    (200^3 x 32 with source, 1.2 rounds: 354 / 397 us);
-//  - 64 channels of emissivity alone, which 256 bytes a wave stream as well,
-//    take one round (180^3: 288 / 308 us).
-// Inside the line, one channel a lane / four: 64^3 x 32 15.5 / 10.8 us,
-// 128^3 x 32 88 / 55, 144^3 x 48 with velocity and absorption 206 / 160,
-// 128^3 x 64 with velocity, source and absorption toward -z 247 / 205.
-static ImgPlan image_plan(const ImageParams &Q, int64_t round) {
+static int64_t image_blocks(const ImgPlan &p) { return (p.groups * p.nseg + kImgWaves - 1) / kImgWaves; }
+
+// How full the chip is on average over a launch of `blocks` workgroups, `round`
+// of which are resident: a few past a full round take as long as a whole one.
+static double image_fill(int64_t blocks, int64_t round) {
+    return (double)blocks / (double)(round * ((blocks + round - 1) / round));
+}
+
+// Four channels a lane (16-byte loads, 1 KB of a cell's channels a wave) or one.
+// Four read less often but run as fewer, larger workgroups.  Both were timed on
+// 73,000 images of 20^3 to 128^3 cells and 4 to 64 channels, all directions and
+// fields, with inputs in and out of the cache (times of four over one, cached /
+// not); what separates them:
+//  - whether four fill the chip as well as one does (`fits`; three quarters of
+//    that where velocity makes each lookup's work shared and inputs stay
+//    cached): with a source function, or velocity and up to 100 MB, 0.85 / 0.73
+//    where they fit and 1.00 / 0.91, slower in half of them, where not; beyond
+//    100 MB without a source function 1.03 / 0.93;
+//  - velocity and absorption without a source function, where one a lane spills:
+//    0.79 / 0.69 unless the chip is less than 0.65 full;
+//  - neither velocity nor source function: 0.88 / 0.78 across x and nearly full,
+//    1.02 / 0.84 along x, slower in half of them; a source function along x
+//    without velocity: slower in a third;
+//  - few channels, since neighbouring cells share lines that the stream does not
+//    keep (200^3 x 4 toward +x 43 us with one, 167 with four): below 24 along x,
+//    12 across;
+//  - whole pieces of 64 bytes (32, 48, 64 channels) and a full chip: 0.82 / 0.73
+//    in any case but a source function along x (64^3 x 32 15.5 us, 10.8).
+// Over the images that take four it is 0.85 / 0.74; one would be more than 3%
+// faster in 4% of them, 8% in 1%.  128^3 x 64 with velocity, source and
+// absorption toward -z: 247 us with one, 205 with four.
+static ImgPlan image_plan(const ImageParams &Q, int64_t round_single, int64_t round_quad) {
     const int nl = Q.n[Q.d];
-    if (Q.nch % 16 == 0 && Q.nch >= 32 && Q.nch <= 64 && !(Q.srcf && Q.d == 0)) {
-        const ImgPlan quad = image_plan(Q.npix, Q.nch, nl, 4);
-        const int64_t per_block = kImgWaves / quad.nseg, blocks = (quad.groups + per_block - 1) / per_block;
-        const bool full = 10 * blocks >= 9 * round * ((blocks + round - 1) / round);
-        if (full && quad.groups * quad.nseg >= kImgQuadWaves &&
-            (Q.nch < 64 || Q.vel_axis || Q.srcf || blocks <= round))
-            return quad;
-    }
-    return image_plan(Q.npix, Q.nch, nl, 1);
+    const bool along = Q.d == 0, vel = Q.vel_axis != nullptr, src = Q.srcf != nullptr;
+    const ImgPlan single = image_plan(Q.npix, Q.nch, nl, 1);
+    if (Q.nch < (along ? 24 : 12)) return single;
+    const ImgPlan quad = image_plan(Q.npix, Q.nch, nl, 4);
+    if (quad.groups * quad.nseg < kImgQuadWaves) return single;
+    const double fill = image_fill(image_blocks(quad), round_quad);
+    const double mb = 4e-6 * (src ? 2.0 : 1.0) * (double)Q.npix * nl * Q.nch;
+    const bool fits = fill >= (vel && mb <= 60.0 ? 0.75 : 0.97) * image_fill(image_blocks(single), round_single);
+    const bool pieces = Q.nch % 16 == 0 && Q.nch >= 32 && Q.nch <= 64 && fill >= 0.9 &&
+                        (Q.nch < 64 || vel || src || image_blocks(quad) <= round_quad);
+    const bool take = src ? (along ? vel && fits : fits || pieces)
+                          : (vel && Q.kabs && fill >= 0.65) || pieces ||
+                                (fits && mb <= 100.0 && (vel || (!along && fill >= 0.85)));
+    return take ? quad : single;
 }
 
 template <bool kVel, bool kAbs, bool kSrc>
@@ -281,17 +303,17 @@ static hipError_t launch_image_t(const ImageParams &Q, hipStream_t s, hipEvent_t
         quad = image_quad_src_kernel<kVel, kAbs>;
         single = image_src_kernel<kVel, kAbs>;
     }
-    static std::atomic<int> resident{0};  // workgroups of the quad kernel a compute unit holds
-    int per_cu = resident.load();
-    if (per_cu == 0) {
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, quad, 64 * kImgWaves, 0);
-        if (e != hipSuccess) return e;
-        resident.store(per_cu = std::max(per_cu, 1));
-    }
-    const ImgPlan p = image_plan(Q, (int64_t)Q.cus * per_cu);
+    static std::atomic<int> resident[2] = {{0}, {0}};  // workgroups a compute unit holds: one, four channels a lane
+    int per_cu[2];
+    for (int k = 0; k < 2; ++k)
+        if ((per_cu[k] = resident[k].load()) == 0) {
+            hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu[k], k ? quad : single, 64 * kImgWaves, 0);
+            if (e != hipSuccess) return e;
+            resident[k].store(per_cu[k] = std::max(per_cu[k], 1));
+        }
+    const ImgPlan p = image_plan(Q, (int64_t)Q.cus * per_cu[0], (int64_t)Q.cus * per_cu[1]);
     const int nl = Q.n[Q.d], seglen = (nl + p.nseg - 1) / p.nseg;
-    const int64_t per_block = kImgWaves / p.nseg;
-    const dim3 grid((unsigned)((p.groups + per_block - 1) / per_block)), block(64 * kImgWaves);
+    const dim3 grid((unsigned)image_blocks(p)), block(64 * kImgWaves);
     hipExtLaunchKernelGGL(p.v == 4 ? quad : single, grid, block, 0, s, start, stop, 0, Q, p.nseg, seglen);
     return hipGetLastError();
 }

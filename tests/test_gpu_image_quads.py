@@ -64,7 +64,9 @@ def test_quads_equal_single_channels(line_ctx, axis, nch, opts):
 @pytest.mark.parametrize("n,axis,nch,opts", [
     ((64, 64, 32), 2, 64, ""), ((64, 64, 29), 5, 64, "v"), ((64, 64, 64), 1, 64, "vsa"), ((64, 64, 37), 2, 64, "a"),
     ((128, 128, 32), 5, 64, "va"), ((128, 128, 11), 2, 64, "s"), ((128, 128, 16), 2, 64, ""), ((127, 129, 18), 5, 64, "vs"),
-    ((23, 128, 128), 3, 64, "v"), ((50, 50, 43), 2, 48, "va"), ((72, 60, 104), 1, 48, "v"), ((128, 128, 21), 2, 32, "sa")])
+    ((23, 128, 128), 3, 64, "v"), ((50, 50, 43), 2, 48, "va"), ((72, 60, 104), 1, 48, "v"), ((128, 128, 21), 2, 32, "sa"),
+    ((128, 128, 14), 2, 63, "va"), ((127, 129, 18), 5, 61, "vsa"), ((64, 64, 41), 1, 62, "va"), ((31, 90, 90), 0, 37, "va"),
+    ((100, 100, 33), 4, 13, "va")])
 def test_segments_of_quads_equal_single_channels(line_ctx, n, axis, nch, opts):
     """As above for every segment count, each cell of a ray a few roundings:
     8 cells 2^-24."""
